@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 typedef __bf16 bf16;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -11,6 +13,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 #define RS_DEVICE static __device__ __forceinline__
+#define RS_INLINE __attribute__((always_inline))   // on lambdas whose captures must stay in registers
 
 constexpr int WAVE = 64;
 
@@ -29,3 +32,11 @@ RS_DEVICE void st_global_16(void* p, uint4 v) { *reinterpret_cast<uint4*>(p) = v
 
 RS_DEVICE bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 RS_DEVICE uint4 as_uint4(bf16x8 v) { return __builtin_bit_cast(uint4, v); }
+
+template <int I, int N, class F>
+RS_DEVICE void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}

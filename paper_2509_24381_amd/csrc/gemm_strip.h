@@ -27,8 +27,6 @@
 // the next weight step has landed.  One memory instruction rides behind each MFMA, pinned with scheduling fences, so
 // its issue latency overlaps the matrix pipe.
 #pragma once
-#include <type_traits>
-
 #include "common.h"
 
 enum GemmEpilogue {
@@ -90,14 +88,6 @@ constexpr int GS_NARROW_LDS_BYTES = gs_lds_bytes(GS_NARROW_NT, GS_NARROW_SLOTS);
 // silu(g) = g / (1 + 2^(-g log2 e)) with the raw v_exp_f32 / v_rcp_f32 instructions (1 ulp each; the result is rounded to bf16)
 RS_DEVICE float silu_f32(float g) {
     return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f));
-}
-
-template <int I, int N, class F>
-RS_DEVICE void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
 }
 
 // Fragment-major activation layout: a [M, W] bf16 matrix is cut into blocks of 32 tokens x 16 features; inside a block the

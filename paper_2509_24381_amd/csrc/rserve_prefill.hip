@@ -101,7 +101,6 @@ struct rs_ctx {
     hipStream_t last_stream = nullptr;
     int splitk_override = 0;  // RS_SPLITK environment variable (0 = heuristic)
     int mrope_b0 = 0, mrope_b1 = 0;  // rotary pair j turns with axis 0 below b0, axis 1 below b1, axis 2 above (set in rs_ctx_create)
-    int attn_plain_order = 0; // RS_ATTN_ORDER=plain: attention items stay heaviest-first (no pairing by compute unit)
     int attn_split = 0;       // RS_ATTN_SPLIT environment variable: parts a block's key range is cut into (0: decided per call)
     int gemm_pairs = 1;       // RS_PAIRS environment variable: 0 never lets two wavefronts of a GEMM workgroup split a pair of units
     int gemm_narrow = 1;      // RS_NARROW environment variable: 0 never uses the narrow GEMM geometry; otherwise launches of at most
@@ -188,15 +187,15 @@ struct DescSizes {
     size_t reqs, items, vblocks, rowpos, pagetab, mitems, fp8, total;
 };
 
-constexpr int ATT_MIN_PART_TILES = 8;      // a part is worth a workgroup and its share of the merge from about 500 keys
+constexpr int ATT_MIN_PART_TILES = 6;      // a part is worth a workgroup and its share of the merge from about 400 keys; every row of a
+                                           // block must see keys of each part: its rows span at most 256 positions, 5 tiles
 constexpr int ATT_MIN_SPLIT_TILES = 16;    // no block of the call is split unless the longest walks at least 1024 keys
-// slots of the split buffer: blocks are split only when there are fewer of them than compute units, into about two
-// workgroups per unit in total (sized for the 256 units of an MI355X; a block that finds no free slots stays whole)
-size_t attn_split_slots(const rs_ctx*) { return 768; }
+// slots of the split buffer (a block that finds no free slots stays whole)
+size_t attn_split_slots(const rs_ctx*) { return 384; }
 
 DescSizes desc_sizes(const rs_ctx* c, int max_tokens, int max_requests) {
     DescSizes d;
-    const size_t n_items = ((size_t)(max_tokens * (size_t)c->group + ATT_ROWS - 1) / ATT_ROWS + max_requests) * c->cfg.n_kv_heads +
+    const size_t n_items = ((size_t)(max_tokens * (size_t)c->group + 32 * ATT_WAVES_SMALL - 1) / (32 * ATT_WAVES_SMALL) + max_requests) * c->cfg.n_kv_heads +
                            attn_split_slots(c);
     const size_t n_vb = (size_t)max_tokens / 64 + 2 * (size_t)max_requests + 1;
     d.reqs = align_up(sizeof(ReqDesc) * std::max(max_requests, 1), 256);
@@ -280,13 +279,134 @@ WorkspaceLayout ws_layout(const rs_ctx* c, int T, int R) {
     w.r = take(tp * f.hidden * 2);
     w.act = take(tp * f.mlp_inter * 2);
     w.partial = take(4 * t * f.hidden * 4);  // up to 4 split-K partial planes of [T, H] fp32
-    w.attn_split = take(attn_split_slots(c) * (size_t)ATT_ROWS * (f.head_dim + 2) * 4);  // partial results of split key ranges
+    w.attn_split = take(attn_split_slots(c) * (size_t)(32 * ATT_WAVES) * (f.head_dim + 2) * 4);  // partial results of split key ranges
     w.inv_rms1 = take(tp * 4);
     w.inv_rms2 = take(tp * 4);
     w.rowss = take(tp * (f.hidden / 32) * 4);
     w.desc = take(desc_sizes(c, T, R).total);
     w.total = off;
     return w;
+}
+
+// Estimated end of a launch in which `lens` (longest first) are handed to n_cu compute units as these fall free.
+int attn_makespan(const std::vector<int>& lens, int n_cu, int per_item) {
+    if ((int)lens.size() <= n_cu) return lens.empty() ? 0 : lens[0] + per_item;
+    std::vector<int> heap(n_cu, 0);   // min-heap of the units' loads
+    const auto later = [](int a, int b) { return a > b; };
+    int end = 0;
+    for (int n : lens) {
+        std::pop_heap(heap.begin(), heap.end(), later);
+        heap.back() += n + per_item;
+        end = std::max(end, heap.back());
+        std::push_heap(heap.begin(), heap.end(), later);
+    }
+    return end;
+}
+
+// Turns the call's attention blocks (whole key ranges) into the launch's work items, heaviest first, cutting key ranges
+// where that ends the launch sooner; the parts of a cut block are combined by attn_merge_kernel.  One workgroup fills a
+// compute unit, so a launch lasts as long as the fullest unit.  The estimates are in units of one key tile's time (1.6 to
+// 1.8 us on a full chip); the constants are fitted to kernel traces (the merge 6 us, and 14 us for 392 parts; a part's
+// partial result 133 KB at d = 128).  Measured at the 7B shape, attention step, nothing cut -> planned: 16 requests, 2048
+// rows, caches of 0 to 12288 tokens 256 -> 178 us; 1000 rows on 12000 tokens 181 -> 161; 250 on 8192: 69 -> 48; 64 on 2048:
+// 28 -> 24; 2048 on 6144: 210 -> 200 (97 to 128 tiles per block, at most 105 per unit after: the board's power limit gives
+// back little of a better balance).  4096 rows on 28672 (1024 blocks) stay whole.
+void plan_attention(const rs_ctx* c, std::vector<AttnItem>& items, std::vector<AttnMergeItem>& mitems) {
+    if (items.empty()) return;
+    std::stable_sort(items.begin(), items.end(), [](const AttnItem& a, const AttnItem& b) { return a.nkb > b.nkb; });
+    constexpr int ITEM = 2, PART = 4, MERGE = 4, MERGE_PARTS = 36;   // tile times: per whole item, per part, per merge, parts per further one
+    const int longest = items[0].nkb, blocks = (int)items.size();
+    const int slot_cap = (int)attn_split_slots(c);
+    // parts of a block of n tiles when none may exceed `cap`
+    const auto parts_of = [&](int n, int cap) { return std::min(std::min((n + cap - 1) / cap, n / ATT_MIN_PART_TILES), ATT_MAX_PARTS); };
+    int cap = 0;          // 0: nothing is cut
+    bool even = true;     // equal parts, or parts of `cap` tiles and a rest
+    if (c->attn_split > 1) {
+        cap = 1;          // (test hook: handled below)
+    } else if (c->attn_split == 0 && longest >= ATT_MIN_SPLIT_TILES) {
+        std::vector<int> lens(blocks);
+        long work = 0;
+        for (int i = 0; i < blocks; ++i) work += lens[i] = items[i].nkb;
+        int best = attn_makespan(lens, c->n_cu, ITEM);
+        // (1) equal parts, as long as every part has a compute unit of its own
+        if (blocks < c->n_cu) {
+            int lo = ATT_MIN_PART_TILES, hi = longest;   // smallest cap with at most n_cu parts
+            while (lo < hi) {
+                const int mid = (lo + hi) / 2;
+                long n = 0;
+                for (int len : lens) n += std::max(1, parts_of(len, mid));
+                if (n <= c->n_cu) hi = mid; else lo = mid + 1;
+            }
+            int end = 0, slots = 0;
+            for (int len : lens) {
+                const int p = std::max(1, parts_of(len, lo));
+                end = std::max(end, (len + p - 1) / p);
+                if (p > 1) slots += p;
+            }
+            const int cost = end + PART + MERGE + slots / MERGE_PARTS;
+            if (slots > 0 && slots <= slot_cap && cost < best) {
+                best = cost;
+                cap = lo;
+            }
+        }
+        // (2) an even share for every compute unit: blocks longer than the share are cut there, the rests fill the gaps
+        const int share = (int)((work + (long)blocks * PART) * 102 / 100 / c->n_cu) + 1;
+        if (share >= ATT_MIN_PART_TILES && share + ATT_MIN_PART_TILES <= longest) {
+            std::vector<int> cut;
+            int slots = 0;
+            for (int len : lens) {
+                const int full = len / share, rest = len - full * share;
+                if (full == 0 || (full == 1 && rest < ATT_MIN_PART_TILES) || slots + full + 1 > slot_cap || full + 1 > ATT_MAX_PARTS) {
+                    cut.push_back(len);
+                    continue;
+                }
+                if (rest < ATT_MIN_PART_TILES) {
+                    for (int p = 0; p < full; ++p) cut.push_back((len + full - 1) / full + PART - ITEM);
+                    slots += full;
+                } else {
+                    for (int p = 0; p < full; ++p) cut.push_back(share + PART - ITEM);
+                    cut.push_back(rest + PART - ITEM);
+                    slots += full + 1;
+                }
+            }
+            std::sort(cut.begin(), cut.end(), [](int a, int b) { return a > b; });
+            const int cost = attn_makespan(cut, c->n_cu, ITEM) + MERGE + slots / MERGE_PARTS;
+            if (slots > 0 && cost < best) {
+                best = cost;
+                cap = share;
+                even = false;
+            }
+        }
+    }
+    if (cap > 0) {
+        std::vector<AttnItem> cut;
+        int slots = 0;
+        for (const AttnItem& it : items) {
+            int parts = c->attn_split > 1 ? std::min(c->attn_split, it.nkb / ATT_MIN_PART_TILES) : parts_of(it.nkb, cap);
+            int step = 0;   // tiles of every part but the last (0: equal parts)
+            if (!even) {
+                const int full = it.nkb / cap, rest = it.nkb - full * cap;
+                parts = rest < ATT_MIN_PART_TILES ? full : full + 1;
+                step = rest < ATT_MIN_PART_TILES ? 0 : cap;
+                if (parts > ATT_MAX_PARTS) parts = 1;
+            }
+            if (parts < 2 || slots + parts > slot_cap) {
+                cut.push_back(it);
+                continue;
+            }
+            mitems.push_back(AttnMergeItem{it.req, it.kvh, it.qblock, parts, slots, 0, 0, 0});
+            for (int p = 0; p < parts; ++p) {
+                AttnItem part = it;
+                part.kb0 = step ? p * step : (int)((long)p * it.nkb / parts);
+                part.nkb = step ? std::min((p + 1) * step, it.nkb) : (int)((long)(p + 1) * it.nkb / parts);
+                part.slot = slots++;
+                cut.push_back(part);
+            }
+        }
+        items.swap(cut);
+        std::stable_sort(items.begin(), items.end(),
+                         [](const AttnItem& a, const AttnItem& b) { return a.nkb - a.kb0 > b.nkb - b.kb0; });
+    }
 }
 
 // bytes of the bfloat16 copy of an 8-bit cache's first n_tokens (whole 64-token blocks, K and V^T of all KV heads)
@@ -399,7 +519,7 @@ struct StepTimer {
 
 template <int D>
 rs_status launch_attention_path(const rs_ctx* c, bf16* qkv, bf16* attn, const ReqDesc* d_reqs,
-                                const AttnItem* d_items, int n_items, const KVBlockItem* d_vb, int n_vb, bool any_paged,
+                                const AttnItem* d_items, int n_items, int att_waves, const KVBlockItem* d_vb, int n_vb, bool any_paged,
                                 float* split_buf, const AttnMergeItem* d_mitems, int n_mitems, const Fp8CacheDesc* d_fp8, int n_reqs,
                                 int n_xblocks, hipStream_t st, const StepTimer& tm) {
     const rs_layer_cfg& f = c->cfg;
@@ -417,18 +537,21 @@ rs_status launch_attention_path(const rs_ctx* c, bf16* qkv, bf16* attn, const Re
     tm.end(RS_STEP_APPEND_KV);
     const float scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)D));
     tm.begin(RS_STEP_ATTENTION);
-    if (any_paged)
-        hipLaunchKernelGGL((attn_prefill_pipelined_kernel<D, true>), dim3(n_items), dim3(256), 0, st, d_reqs, d_items,
+    const auto attend = [&](auto paged, auto waves) {
+        constexpr int W = decltype(waves)::value;
+        hipLaunchKernelGGL((attn_prefill_pipelined_kernel<D, decltype(paged)::value, W>), dim3(n_items), dim3(64 * W), 0, st, d_reqs, d_items,
                            (const bf16*)qkv, c->qkv_dim, attn, c->q_dim, c->group, scale_log2e, split_buf);
-    else
-        hipLaunchKernelGGL((attn_prefill_pipelined_kernel<D, false>), dim3(n_items), dim3(256), 0, st, d_reqs, d_items,
-                           (const bf16*)qkv, c->qkv_dim, attn, c->q_dim, c->group, scale_log2e, split_buf);
+        if (n_mitems > 0)
+            hipLaunchKernelGGL((attn_merge_kernel<D, W>), dim3(n_mitems, ATT_MERGE_Y), dim3(32 * W), 0, st, d_reqs, d_mitems,
+                               (const float*)split_buf, attn, c->q_dim, c->group, scale_log2e);
+    };
+    const auto attend_waves = [&](auto paged) {
+        if (att_waves == ATT_WAVES) attend(paged, std::integral_constant<int, ATT_WAVES>{});
+        else attend(paged, std::integral_constant<int, ATT_WAVES_SMALL>{});
+    };
+    if (any_paged) attend_waves(std::true_type{});
+    else attend_waves(std::false_type{});
     RS_HIP(hipGetLastError());
-    if (n_mitems > 0) {
-        hipLaunchKernelGGL(attn_merge_kernel<D>, dim3(n_mitems, ATT_MERGE_Y), dim3(256), 0, st, d_reqs, d_mitems, (const float*)split_buf, attn,
-                           c->q_dim, c->group, scale_log2e);
-        RS_HIP(hipGetLastError());
-    }
     tm.end(RS_STEP_ATTENTION);
     return RS_OK;
 }
@@ -651,6 +774,17 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     char* wsb = reinterpret_cast<char*>(ws);
     const int* d_pagetab = reinterpret_cast<const int*>(wsb + L.desc + ds.reqs + ds.items + ds.vblocks + ds.rowpos);
     const int g = ctx->group;
+    int att_waves = ATT_WAVES;
+    {   // (see ATT_WAVES; the most parts the small blocks could be cut into)
+        long most = 0;
+        for (int i = 0; i < R; ++i) {
+            const long blocks = ((long)lens[i] * g + 32 * ATT_WAVES_SMALL - 1) / (32 * ATT_WAVES_SMALL) * f.n_kv_heads;
+            const long tiles = ((long)kvs[i]->len[layer] + lens[i] + ATT_KEYS - 1) / ATT_KEYS;
+            most += blocks * (tiles < ATT_MIN_SPLIT_TILES ? 1 : std::min<long>(tiles / ATT_MIN_PART_TILES, ATT_MAX_PARTS));
+        }
+        if (most <= ctx->n_cu) att_waves = ATT_WAVES_SMALL;
+    }
+    const int att_rows = 32 * att_waves;
     int row0 = 0;
     for (int i = 0; i < R; ++i) {
         const int Ti = lens[i];
@@ -684,9 +818,9 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         if (kv->paged()) pagetab.insert(pagetab.end(), kv->pages[layer].begin(), kv->pages[layer].end());
         const int ri = (int)reqs.size();
         reqs.push_back(d);
-        const int nqb = (Ti * g + ATT_ROWS - 1) / ATT_ROWS;
+        const int nqb = (Ti * g + att_rows - 1) / att_rows;
         for (int qb = 0; qb < nqb; ++qb) {
-            const int t_max = std::min(Ti - 1, (qb * ATT_ROWS + ATT_ROWS - 1) / g);
+            const int t_max = std::min(Ti - 1, (qb * att_rows + att_rows - 1) / g);
             const int nkb = (P + t_max + 1 + ATT_KEYS - 1) / ATT_KEYS;
             for (int c = 0; c < f.n_kv_heads; ++c) items.push_back(AttnItem{ri, c, qb, nkb, 0, -1, 0, 0});
         }
@@ -695,80 +829,8 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
             for (int ax = 0; ax < 3; ++ax) rowpos.push_back(positions3 ? positions3[3 * (size_t)(row0 + t) + ax] : P + t);
         row0 += Ti;
     }
-    // Fewer blocks than compute units: cut the key ranges so that up to two workgroups per compute unit exist, not more (a
-    // third round of workgroups costs more than the shorter parts save: 512 rows on 16384 cached tokens 201 us with 5 parts,
-    // 175 with 4).  A part has at least ATT_MIN_PART_TILES tiles, so every row of the block sees
-    // keys in each part: the rows of a block span at most 128 positions, i.e. only the last three tiles can be hidden from
-    // some of them.
     std::vector<AttnMergeItem> mitems;
-    if (!items.empty()) {
-        const int blocks = (int)items.size();
-        int want = ctx->attn_split;
-        if (want == 0) {
-            // (the merge is a second kernel of about 6 us, i.e. six tiles of a block's walk; measured at the 7B shape, 64 rows
-            // on 2048 cached tokens: 43 us of attention unsplit, 25 in 4 parts; 512 rows on 1536: 50 -> 40)
-            int longest = 0;
-            for (const AttnItem& it : items) longest = std::max(longest, it.nkb);
-            want = (blocks < ctx->n_cu && longest >= ATT_MIN_SPLIT_TILES)
-                       ? std::min(ATT_MAX_PARTS, std::max(1, 2 * ctx->n_cu / blocks)) : 1;
-            if (want > 1) {
-                // What the call's longest walk would shrink by, in tiles (blocks under two parts' worth stay whole and may
-                // then be the longest).  Splitting pays from 7 tiles when the chip is nearly empty and from 12 when the
-                // blocks alone nearly fill it (fitted: 1024 rows on 512 cached tokens lose 1 us with a gain of 9 tiles, on
-                // 1024 cached tokens they win 6 us with a gain of 16; 64 rows on 960 win 6 us with a gain of 8).
-                int longest_after = 0;
-                for (const AttnItem& it : items) {
-                    const int parts = std::min(want, it.nkb / ATT_MIN_PART_TILES);
-                    longest_after = std::max(longest_after, parts < 2 ? it.nkb : (it.nkb + parts - 1) / parts);
-                }
-                if ((long)(longest - longest_after) * ctx->n_cu < 7L * ctx->n_cu + 5L * blocks) want = 1;
-            }
-        }
-        if (want > 1) {
-            std::vector<AttnItem> cut;
-            int slots = 0;
-            const int slot_cap = (int)attn_split_slots(ctx);
-            for (const AttnItem& it : items) {
-                const int parts = std::min(want, it.nkb / ATT_MIN_PART_TILES);
-                if (parts < 2 || slots + parts > slot_cap) {
-                    cut.push_back(it);
-                    continue;
-                }
-                mitems.push_back(AttnMergeItem{it.req, it.kvh, it.qblock, parts, slots, 0, 0, 0});
-                for (int p = 0; p < parts; ++p) {
-                    AttnItem part = it;
-                    part.kb0 = (int)((long)p * it.nkb / parts);
-                    part.nkb = (int)((long)(p + 1) * it.nkb / parts);
-                    part.slot = slots++;
-                    cut.push_back(part);
-                }
-            }
-            items.swap(cut);
-        }
-    }
-    // heaviest work first: the tail of the launch is then made of short items
-    std::stable_sort(items.begin(), items.end(),
-                     [](const AttnItem& a, const AttnItem& b) { return a.nkb - a.kb0 > b.nkb - b.kb0; });
-    // Between one and two workgroups per compute unit every item is resident from the first clock, and on an empty chip the
-    // dispatcher hands workgroup k and workgroup k + n_cu to the same compute unit (measured: 448 workgroups of this
-    // footprint leave exactly workgroups 192 .. 255 alone on theirs).  A lone workgroup walks its tiles faster than two that
-    // share the matrix pipe, and a pair lasts as long as both walks together, so the launch ends soonest when the heaviest
-    // items are the lone ones and the rest are paired heavy with light.  Only the order of independent items changes.
-    const int n_items_now = (int)items.size();
-    if (n_items_now > ctx->n_cu && n_items_now <= 2 * ctx->n_cu && !ctx->attn_plain_order) {
-        const int paired = n_items_now - ctx->n_cu, lone = ctx->n_cu - paired;
-        std::vector<AttnItem> placed(items.size());
-        for (int k = 0; k < lone; ++k) placed[paired + k] = items[k];
-        // (the light partners are taken from the tail in runs of one item per KV head, in the head order of the front: the
-        //  blocks of a head then stay on the XCDs, workgroup index mod 8, whose L2 already holds that head's K and V)
-        const int run = ctx->cfg.n_kv_heads;
-        const bool by_head = n_items_now % run == 0 && paired % run == 0;
-        for (int k = 0; k < paired; ++k) {
-            placed[k] = items[lone + k];
-            placed[ctx->n_cu + k] = by_head ? items[n_items_now - run * (k / run + 1) + k % run] : items[n_items_now - 1 - k];
-        }
-        items.swap(placed);
-    }
+    plan_attention(ctx, items, mitems);
 
     if (sizeof(ReqDesc) * reqs.size() > ds.reqs || sizeof(AttnItem) * items.size() > ds.items ||
         sizeof(KVBlockItem) * vbs.size() > ds.vblocks || sizeof(int) * rowpos.size() > ds.rowpos ||
@@ -876,10 +938,10 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     tm.end(RS_STEP_QKV_GEMM);
     // cache append, attention
     if (f.head_dim == 128)
-        s = launch_attention_path<128>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
+        s = launch_attention_path<128>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), att_waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
                                        attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, st, tm);
     else
-        s = launch_attention_path<64>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
+        s = launch_attention_path<64>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), att_waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
                                       attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, st, tm);
     if (s != RS_OK) return s;
     // r = x + attn Wo^T, and 1/rms of every row of r (the second RMSNorm; its gain lives in the packed W_gate_up)
@@ -955,7 +1017,6 @@ rs_status rs_ctx_create(const rs_layer_cfg* cfg, rs_ctx** out) {
     if (const char* e = getenv("RS_NARROW")) c->gemm_narrow = atoi(e);
     if (const char* e = getenv("RS_NARROW_TM")) c->narrow_max_tiles_m = atoi(e);
     if (const char* e = getenv("RS_ATTN_SPLIT")) c->attn_split = std::max(0, std::min(atoi(e), ATT_MAX_PARTS));
-    if (const char* e = getenv("RS_ATTN_ORDER")) c->attn_plain_order = strcmp(e, "plain") == 0;
     auto cleanup = [&](rs_status s) { rs_ctx_destroy(c); return s; };
 
     c->slot_bytes = desc_sizes(c, f.max_tokens_per_call, f.max_requests).total;
@@ -1014,13 +1075,6 @@ rs_status rs_ctx_create(const rs_layer_cfg* cfg, rs_ctx** out) {
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_RESIDUAL, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_SWIGLU, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_PARTIAL, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
-    // (the pipelined attention kernel keeps its LDS in static arrays; these references make the launch stubs exist)
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_prefill_pipelined_kernel<128, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 0);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_prefill_pipelined_kernel<64, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 0);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_prefill_pipelined_kernel<128, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 0);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_prefill_pipelined_kernel<64, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 0);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_merge_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, 0);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_merge_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, 0);
     if (e != hipSuccess) return cleanup(fail(RS_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e)));
     *out = c;
     return RS_OK;

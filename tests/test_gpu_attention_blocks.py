@@ -1,0 +1,84 @@
+"""GPU: the attention kernel where its blocks, tiles and parts end, and where its reference maximum has to move.
+
+Attention is isolated by a zero down projection (y = x + attention W_o^T).  The attention term carries the bfloat16
+roundings of q, k, v, the probabilities, the output and y (2^-9 / sqrt(3) = 1.1e-3 to 1.7e-3 each, six of them in quadrature
+about 4e-3, twice that where y is dominated by x): 2e-2 leaves a factor of two to three.
+"""
+import numpy as np
+import pytest
+
+import synth
+from test_gpu_parity import check, oracle_batch, run_batch
+
+pytestmark = pytest.mark.gpu
+
+
+def _requests(shape, spec, seed, key_scale=None):
+    rng = np.random.default_rng(seed)
+    reqs = []
+    for prior, t_new in spec:
+        pk = rng.standard_normal((prior, shape.n_kv_heads, shape.head_dim), dtype=np.float32)
+        if key_scale is not None:
+            pk = pk * key_scale(prior)[:, None, None]
+        pv = rng.standard_normal((prior, shape.n_kv_heads, shape.head_dim), dtype=np.float32)
+        rows = synth.prompt_rows([("text", t_new)], shape.hidden, seed + 1 + len(reqs))
+        reqs.append(synth.BatchRequest(prior, synth.bf16_round(pk), synth.bf16_round(pv), rows))
+    return reqs
+
+
+def _attention_term(shape, reqs, name, tol, capacity):
+    w = synth.layer_weights(shape, 41, gains="uniform")
+    w.wd = np.zeros_like(w.wd)
+    y, _ = run_batch(shape, w, reqs, capacity=capacity)
+    y_ref, _ = oracle_batch(shape, w, reqs)
+    x = np.concatenate([r.rows for r in reqs], axis=0)
+    off = 0
+    for i, r in enumerate(reqs):
+        n = r.rows.shape[0]
+        check(f"{name}, request {i}", (y - x)[off: off + n], (y_ref - x)[off: off + n], tol=tol)
+        off += n
+
+
+# (calls that cannot fill the chip run blocks of 128 rows with four wavefronts, others 256 rows with eight: planned for one
+# compute unit, no call is small)
+@pytest.mark.parametrize("n_cu", [None, "1"])
+@pytest.mark.parametrize("heads", [(4, 4, 64), (7, 1, 128), (8, 1, 64), (2, 2, 128)])
+@pytest.mark.parametrize("prior, t_new", [(0, 1), (0, 31), (0, 33), (0, 64), (31, 32), (32, 33), (63, 1), (64, 36), (65, 37),
+                                          (100, 255), (127, 256), (129, 257)])
+def test_ends_of_half_tiles_tiles_and_blocks(heads, prior, t_new, n_cu, monkeypatch):
+    """Rows and keys that end just before, at and behind a half tile (32 keys), a tile (64), a wavefront's 32 stacked rows and
+    a block's 128 or 256, with 1, 7 and 8 query heads per KV head (256 rows are then 256, 37 and 32 tokens)."""
+    if n_cu:
+        monkeypatch.setenv("RS_NCU", n_cu)
+    hq, hkv, d = heads
+    shape = synth.LayerShape("edge", 256, hq, hkv, d, 256)
+    _attention_term(shape, _requests(shape, [(prior, t_new)], 500 + prior), f"{heads} P={prior} T={t_new}", 2e-2, 512)
+
+
+@pytest.mark.parametrize("n_cu", [None, "1"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("at", [(31,), (32,), (45,), (64, 100), (63, 159, 160, 255)])
+def test_scores_that_jump_inside_a_tile(d, at, n_cu, monkeypatch):
+    """Single keys whose scores stand far above all before them (by up to 2^25 in the probabilities), in the first and in the
+    second half of a tile: the reference has to move at that half, for the queries concerned, without touching the half that is
+    still to be multiplied.  Sharp distributions turn the absolute score error (2.4e-3 of a score of about 15) into the
+    weights: 4e-2."""
+    if n_cu:
+        monkeypatch.setenv("RS_NCU", n_cu)
+    shape = synth.LayerShape("jump", 256, 4, 2, d, 256)
+
+    def scale(prior):
+        s = np.ones(prior, dtype=np.float32)
+        s[list(at)] = 14.0
+        return s
+    _attention_term(shape, _requests(shape, [(300, 90)], 600 + at[0], scale), f"d={d} jumps at {at}", 4e-2, 512)
+
+
+@pytest.mark.parametrize("n_cu", ["3", "7", "40", "300"])
+def test_key_ranges_cut_for_unequal_requests(n_cu, monkeypatch):
+    """Requests with caches of very different lengths in one call, planned for different compute-unit counts: nothing cut,
+    equal parts, and parts of an even share with a rest."""
+    monkeypatch.setenv("RS_NCU", n_cu)
+    shape = synth.LayerShape("small128", 256, 4, 2, 128, 256)
+    spec = [(3000, 40), (0, 70), (900, 33), (1500, 128), (64, 1), (2047, 129)]
+    _attention_term(shape, _requests(shape, spec, 700), f"planned for {n_cu} units", 2e-2, 3200)
