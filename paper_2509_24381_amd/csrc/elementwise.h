@@ -170,6 +170,235 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const bf16* __restrict__ w
     }
 }
 
+// The same for 3 rows and more, on the matrix pipe.  The fp32 row is cut into three bfloat16 pieces whose sum it is exactly
+// (hi = bf16(h), mid = bf16(h - hi), lo = h - hi - mid: 8 significand bits each, signs included, cover fp32's 24); products
+// of a piece with a bfloat16 weight are exact in fp32.  The pieces of up to 10 rows are the columns of ONE 32-column B
+// operand (column 10 s + r = piece s of row r), so the kernel streams the vocabulary once per 10 NG rows and spends one
+// 32x32x16 MFMA per 32 vocabulary rows, 16 k and 10 rows, far below the stream's time.
+//   operand layout: [group of 10 rows][k-step of 16][half][column 32][8 bfloat16]: a wavefront's load is one contiguous KB.
+// One workgroup per compute unit owns an even share of the vocabulary and walks it 64 rows at a time; each of its 4
+// wavefronts takes a quarter of K and streams its part of the rows global -> LDS by DMA (a row's 128 bytes are then 8
+// neighbouring lanes: whole cache lines; loaded straight into the MFMA layout, where neighbouring lanes are different rows,
+// the stream reached 3.5 TB/s) through a ring of its own, three steps of 8 KB ahead and on across the tiles, without a
+// barrier; they meet in LDS at the end of a tile.  The accumulators are emptied after every 64 k, and those sums after every
+// 256: short chains keep the error against 64 bits below that of the fp32 kernel above (3584: 1.0e-7 against 1.2e-7;
+// 8192: 1.2e-7 against 1.4e-7).
+// Measured on 152064 x 3584, us (LDS kernel, which streams the vocabulary once per 4 rows -> this one): 2 rows 205 -> 206,
+// 3: 271 -> 210, 8: 609 -> 217 (5.03 TB/s; a copy reaches 4.9), 10: 805 -> 218, 11: 860 -> 257 (a second group's operand comes
+// from L2 beside the stream).
+constexpr int LM_MFMA_ROWS = 3;   // from this many rows on
+constexpr int LM_GROUP = 10;      // rows per B operand
+constexpr int LM_MAX_GROUPS = 2;  // B operands per launch (three spill: 525 us for 30 rows, two passes take 470)
+constexpr int LM_VROWS = 64;      // vocabulary rows per workgroup
+__global__ __launch_bounds__(256) void final_norm_split_kernel(const bf16* __restrict__ x, const bf16* __restrict__ gain,
+                                                               bf16* __restrict__ hb, int rows, int H, float eps) {
+    // one workgroup per place of a group of rows (grid x: LM_GROUP, + 1 for the two columns that hold no row; grid y: groups)
+    const int rg = blockIdx.x;
+    const int row = blockIdx.y * LM_GROUP + rg;
+    const size_t base = (size_t)blockIdx.y * (size_t)(H / 16) * 512;   // elements
+    const auto place = [&](int col, int c) {   // chunk c (8 features) of a column: k-step c / 2, half c % 2
+        return hb + base + (size_t)(c >> 1) * 512 + (size_t)(c & 1) * 256 + (size_t)col * 8;
+    };
+    const bf16x8 zero = {};
+    if (rg == LM_GROUP || row >= rows) {
+        for (int c = threadIdx.x; c < H / 8; c += blockDim.x) {
+            if (rg == LM_GROUP) {
+                for (int col = 3 * LM_GROUP; col < 32; ++col) *reinterpret_cast<bf16x8*>(place(col, c)) = zero;
+            } else {
+                for (int s = 0; s < 3; ++s) *reinterpret_cast<bf16x8*>(place(s * LM_GROUP + rg, c)) = zero;
+            }
+        }
+        return;
+    }
+    // (every wavefront sums the whole row in the order of final_norm_kernel: the same factor, no exchange)
+    const int lane = threadIdx.x & 63;
+    const bf16* xr = x + (size_t)row * H;
+    float ss = 0.0f;
+    for (int c = lane; c < H / 8; c += WAVE) {
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(xr + c * 8);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss += bf16_to_f32(v[e]) * bf16_to_f32(v[e]);
+    }
+    ss = wave_sum(ss);
+    const float inv = rsqrtf(ss / (float)H + eps);
+    for (int c = threadIdx.x; c < H / 8; c += blockDim.x) {
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(xr + c * 8);
+        const bf16x8 g = *reinterpret_cast<const bf16x8*>(gain + c * 8);
+        bf16x8 hi, mid, lo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float h = bf16_to_f32(v[e]) * inv * bf16_to_f32(g[e]);
+            hi[e] = f32_to_bf16(h);
+            const float r1 = h - bf16_to_f32(hi[e]);
+            mid[e] = f32_to_bf16(r1);
+            lo[e] = f32_to_bf16(r1 - bf16_to_f32(mid[e]));
+        }
+        *reinterpret_cast<bf16x8*>(place(rg, c)) = hi;
+        *reinterpret_cast<bf16x8*>(place(LM_GROUP + rg, c)) = mid;
+        *reinterpret_cast<bf16x8*>(place(2 * LM_GROUP + rg, c)) = lo;
+    }
+}
+
+constexpr int LM_SLOTS = 4;
+template <int NG>
+__global__ __launch_bounds__(256, 1) void lm_head_mfma_kernel(const bf16* __restrict__ w, const bf16* __restrict__ hb,
+                                                              float* __restrict__ logits, int R, int vocab, int H) {
+    constexpr int PAD = 33;   // a column's 32 sums, padded: neighbouring columns start in different banks
+    constexpr int SLOT = LM_VROWS * 128;   // one wavefront's step: 64 rows x 64 k
+    static_assert(3 * (8 + 4 * NG) <= 63, "the wait for a step must fit the vmcnt field");
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    // (separate objects, so that the compiler can tell the slot being read from those being filled)
+    __shared__ __attribute__((aligned(16))) char ring0[4 * SLOT];
+    __shared__ __attribute__((aligned(16))) char ring1[4 * SLOT];
+    __shared__ __attribute__((aligned(16))) char ring2[4 * SLOT];
+    __shared__ __attribute__((aligned(16))) char ring3[4 * SLOT];
+    __shared__ float red[4][32 * PAD];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    // this workgroup's vocabulary rows [row0, row0 + n_rows)
+    const int share = vocab / gridDim.x, extra = vocab % gridDim.x;
+    const int row0 = (int)blockIdx.x * share + min((int)blockIdx.x, extra);
+    const int n_rows = share + ((int)blockIdx.x < extra ? 1 : 0);
+    const int tiles = (n_rows + LM_VROWS - 1) / LM_VROWS;
+    // this wavefront's groups of 64 k
+    const int nk = H >> 6, kg0 = wave * nk / 4, ns = (wave + 1) * nk / 4 - kg0;
+    const int ns4 = (ns + LM_SLOTS - 1) / LM_SLOTS * LM_SLOTS;   // steps per tile, whole rounds of the ring
+    // (rows past the share, and steps past the last one, fall outside the buffer: they read as zeros and move no data)
+    const __amdgpu_buffer_rsrc_t rw =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(w + (size_t)row0 * H), 0, (int)((uint32_t)n_rows * (uint32_t)H * 2u), 0x00020000);
+    constexpr uint32_t DEAD = 0x80000000u;
+    // load instruction i fills rows [8 i, 8 i + 8) of the slot; 16-byte chunk c of row r sits at place c ^ ((r >> 1) & 7)
+    const uint32_t row_bytes = (uint32_t)H * 2u;
+    uint32_t src[2];   // rows 8 i + lane / 8 for even and odd i: the swizzle repeats every 16 rows
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        const uint32_t r = (uint32_t)(o * 8 + (lane >> 3));
+        src[o] = r * row_bytes + (((uint32_t)(lane & 7) ^ ((r >> 1) & 7u)) * 16u);
+    }
+    const uint32_t frag0 = (uint32_t)l32 * 128u;
+    const uint32_t swz = (uint32_t)(l32 >> 1) & 7u;
+    int l_tile = 0, l_s = 0;   // the step the load stream is at
+    bf16x8 b[LM_SLOTS][NG][4];
+    const auto load_step = [&](auto slotc, char* ring) RS_INLINE {
+        constexpr int slot = decltype(slotc)::value;
+        const bool live = l_tile < tiles && l_s < ns;
+        const int kg = kg0 + (l_s < ns ? l_s : 0);
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) b[slot][g][j] = *reinterpret_cast<const bf16x8*>(hb + ((size_t)g * (H >> 4) + kg * 4 + j) * 512 + lane * 8);
+        const uint32_t off = live ? (uint32_t)(l_tile * LM_VROWS) * row_bytes + (uint32_t)kg * 128u : DEAD;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr)(uintptr_t)(uint32_t)(uintptr_t)(ring + wave * SLOT + i * 1024), 16,
+                                                     src[i & 1] + off + (uint32_t)(i >> 1) * 16u * row_bytes, 0, 0, 0);
+        if (++l_s == ns4) {
+            l_s = 0;
+            ++l_tile;
+        }
+    };
+    f32x16 round[NG][2], sum[NG][2];   // sums over the steps of one round of the ring, and over the rounds
+    const auto each = [&](auto&& f) RS_INLINE {
+        static_for<0, NG>([&](auto gc) RS_INLINE {
+            static_for<0, 2>([&](auto tc) RS_INLINE {
+                static_for<0, 16>([&](auto rc) RS_INLINE { f(gc, tc, rc); });
+            });
+        });
+    };
+    const auto multiply = [&](auto slotc, const char* ring) RS_INLINE {
+        constexpr int slot = decltype(slotc)::value;
+        f32x16 acc[NG][2];
+        bf16x8 a[2][4];
+        // loads retire in order: this step's have landed when at most those of the three steps behind it are in flight (the
+        // compiler does not see LDS written by DMA; nor may it move the refill of a slot above the reads of it)
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * (8 + 4 * NG)) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                a[t][j] = *reinterpret_cast<const bf16x8*>(ring + wave * SLOT + t * 4096 + frag0 + (((uint32_t)(j * 2 + half) ^ swz) * 16u));
+        const f32x16 zero = {};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[g][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][j], b[slot][g][j], j == 0 ? zero : acc[g][t], 0, 0, 0);
+        each([&](auto gc, auto tc, auto rc) RS_INLINE {
+            constexpr int g = decltype(gc)::value, t = decltype(tc)::value, r = decltype(rc)::value;
+            round[g][t][r] = slot == 0 ? acc[g][t][r] : round[g][t][r] + acc[g][t][r];
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+    };
+    if (ns > 0) {
+        load_step(std::integral_constant<int, 0>{}, ring0);
+        load_step(std::integral_constant<int, 1>{}, ring1);
+        load_step(std::integral_constant<int, 2>{}, ring2);
+    }
+    for (int tile = 0; tile < tiles; ++tile) {
+        each([&](auto gc, auto tc, auto rc) RS_INLINE { sum[decltype(gc)::value][decltype(tc)::value][decltype(rc)::value] = 0.0f; });
+        for (int s = 0; s < ns4; s += LM_SLOTS) {
+            // (a slot is refilled behind the step that read it: its fragments are in registers by then)
+            load_step(std::integral_constant<int, 3>{}, ring3);
+            multiply(std::integral_constant<int, 0>{}, ring0);
+            load_step(std::integral_constant<int, 0>{}, ring0);
+            multiply(std::integral_constant<int, 1>{}, ring1);
+            load_step(std::integral_constant<int, 1>{}, ring1);
+            multiply(std::integral_constant<int, 2>{}, ring2);
+            load_step(std::integral_constant<int, 2>{}, ring2);
+            multiply(std::integral_constant<int, 3>{}, ring3);
+            each([&](auto gc, auto tc, auto rc) RS_INLINE {
+                constexpr int g = decltype(gc)::value, t = decltype(tc)::value, r = decltype(rc)::value;
+                sum[g][t][r] += round[g][t][r];
+            });
+        }
+        // the four quarters of K, and the three pieces of every row, meet: 32 vocabulary rows and one group at a time
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the last reader of red is done; the DMA stays in flight)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) red[wave][l32 * PAD + 8 * (r >> 2) + 4 * half + (r & 3)] = sum[g][t][r];
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                const int rows = min(R - g * LM_GROUP, LM_GROUP);
+                for (int i = threadIdx.x; i < rows * 32; i += 256) {
+                    const int r = i >> 5, v = tile * LM_VROWS + t * 32 + (i & 31);   // v: inside the share
+                    float piece[3];
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) {
+                        const int at = (s * LM_GROUP + r) * PAD + (i & 31);
+                        piece[s] = (red[0][at] + red[1][at]) + (red[2][at] + red[3][at]);
+                    }
+                    if (v < n_rows) {
+                        float out = piece[0] + (piece[1] + piece[2]);
+                        if (__builtin_expect(!(fabsf(out) <= 3.402823466e38f), 0)) {
+                            // not finite: a weight may be infinite, and inf times the pieces is not inf times h (0 * inf,
+                            // inf - inf).  Once more in plain fp32, unless the whole row is NaN
+                            const bf16* hg = hb + (size_t)g * (H >> 4) * 512;
+                            const bf16* wv = w + (size_t)(row0 + v) * H;
+                            if (bf16_to_f32(hg[r * 8]) == bf16_to_f32(hg[r * 8])) {
+                                out = 0.0f;
+                                for (int k = 0; k < H; ++k) {
+                                    const bf16* pk = hg + (size_t)(k >> 4) * 512 + ((k >> 3) & 1) * 256 + (k & 7);
+                                    out += (bf16_to_f32(pk[r * 8]) + (bf16_to_f32(pk[(LM_GROUP + r) * 8]) + bf16_to_f32(pk[(2 * LM_GROUP + r) * 8]))) *
+                                           bf16_to_f32(wv[k]);
+                                }
+                            }
+                        }
+                        logits[(size_t)(g * LM_GROUP + r) * vocab + row0 + v] = out;
+                    }
+                }
+            }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stream's last (empty) loads still target this workgroup's LDS
+}
+
 // ---------------------------------------------------------------- K / V append
 struct KVBlockItem {
     int req;

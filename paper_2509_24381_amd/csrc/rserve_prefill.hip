@@ -1580,9 +1580,14 @@ rs_status rs_prefill_model_batch_mrope(rs_ctx* ctx, const rs_layer_weights* pack
     return model_batch(ctx, packed_layers, n_layers, kvs, chunk_lens, R, positions, x, y, workspace, workspace_bytes, stream);
 }
 
+static size_t lm_head_bytes_f32(const rs_ctx* c, int n_rows) { return align_up((size_t)n_rows * c->cfg.hidden * 4, 256); }
+static size_t lm_head_bytes_split(const rs_ctx* c, int n_rows) {
+    return (size_t)((n_rows + LM_GROUP - 1) / LM_GROUP) * c->cfg.hidden * 64;   // 32 bfloat16 columns per group of rows
+}
+
 size_t rs_lm_head_workspace_bytes(const rs_ctx* c, int n_rows) {
     if (!c || n_rows <= 0) return 0;
-    return align_up((size_t)n_rows * c->cfg.hidden * 4, 256);
+    return std::max(lm_head_bytes_f32(c, n_rows), n_rows >= LM_MFMA_ROWS ? lm_head_bytes_split(c, n_rows) : 0);
 }
 
 rs_status rs_lm_head(rs_ctx* c, const void* final_norm_gain, const void* w_lm, int vocab, const void* x, int n_rows, void* logits,
@@ -1594,8 +1599,8 @@ rs_status rs_lm_head(rs_ctx* c, const void* final_norm_gain, const void* w_lm, i
     if (!final_norm_gain || !w_lm || !x || !logits || !workspace) return fail(RS_EINVAL, "null argument");
     if (!aligned(final_norm_gain, 16) || !aligned(w_lm, 16) || !aligned(x, 16) || !aligned(logits, 4) || !aligned(workspace, 256))
         return fail(RS_EINVAL, "misaligned argument");
-    if (workspace_bytes < rs_lm_head_workspace_bytes(c, n_rows))
-        return fail(RS_EWORKSPACE, "workspace has %zu bytes, this call needs %zu", workspace_bytes, rs_lm_head_workspace_bytes(c, n_rows));
+    if (workspace_bytes < lm_head_bytes_f32(c, n_rows))
+        return fail(RS_EWORKSPACE, "workspace has %zu bytes, this call needs %zu", workspace_bytes, lm_head_bytes_f32(c, n_rows));
     // the kernel keeps its group of normalised rows (fp32) in LDS: as many rows per launch, up to LM_ROWS, as 160 KB hold
     constexpr size_t LDS_BYTES = 160 * 1024;
     const int H = c->cfg.hidden;
@@ -1607,6 +1612,30 @@ rs_status rs_lm_head(rs_ctx* c, const void* final_norm_gain, const void* w_lm, i
         c->lm_rows = rows;
     }
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    // Three rows and more go through the matrix pipe, up to 20 per pass over the vocabulary.  One or two, which the LDS kernel
+    // streams as fast (189 and 205 us on 152064 x 3584, against 206), and a workspace of 4 H bytes per row, which holds no
+    // split rows, take that kernel.
+    if (n_rows >= LM_MFMA_ROWS && workspace_bytes >= lm_head_bytes_split(c, n_rows)) {
+        bf16* hb = reinterpret_cast<bf16*>(workspace);
+        hipLaunchKernelGGL(final_norm_split_kernel, dim3(LM_GROUP + 1, (n_rows + LM_GROUP - 1) / LM_GROUP), dim3(256), 0, st, (const bf16*)x,
+                           (const bf16*)final_norm_gain, hb, n_rows, H, c->cfg.rms_eps);
+        RS_HIP(hipGetLastError());
+        // (one workgroup per compute unit; more if a share would not fit the kernel's 32-bit offsets)
+        const size_t w_bytes = (size_t)vocab * H * 2;
+        const dim3 grid((unsigned)std::min<size_t>(std::max<size_t>(c->n_cu, (w_bytes >> 30) + 1), (vocab + LM_VROWS - 1) / LM_VROWS));
+        for (int r0 = 0; r0 < n_rows; r0 += LM_MAX_GROUPS * LM_GROUP) {
+            const int R = std::min(LM_MAX_GROUPS * LM_GROUP, n_rows - r0), groups = (R + LM_GROUP - 1) / LM_GROUP;
+            const bf16* hg = hb + (size_t)(r0 / LM_GROUP) * H * 32;
+            float* lg = reinterpret_cast<float*>(logits) + (size_t)r0 * vocab;
+            const auto launch = [&](auto ng) {
+                hipLaunchKernelGGL(lm_head_mfma_kernel<decltype(ng)::value>, grid, dim3(256), 0, st, (const bf16*)w_lm, hg, lg, R, vocab, H);
+            };
+            if (groups == 1) launch(std::integral_constant<int, 1>{});
+            else launch(std::integral_constant<int, 2>{});
+            RS_HIP(hipGetLastError());
+        }
+        return RS_OK;
+    }
     float* h = reinterpret_cast<float*>(workspace);
     hipLaunchKernelGGL(final_norm_kernel, dim3((n_rows + 3) / 4), dim3(256), 0, st, (const bf16*)x, (const bf16*)final_norm_gain, h,
                        n_rows, H, c->cfg.rms_eps);

@@ -1,0 +1,72 @@
+"""GPU: the first-token head's matrix path (3 rows and more) at the edges of its groups, shares and K ranges, against the
+oracle, and where it must hand over to plain fp32 arithmetic.
+
+Both kernels keep the rows' fp32 values exactly and sum in fp32: the error against 64 bits is 1.0e-7 to 1.5e-7 measured on
+3584 and 8192 features (2-norm); 1e-6 leaves a margin for small vocabularies.
+"""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import first_token_logits, rel_fro
+
+pytestmark = pytest.mark.gpu
+
+
+def _head(hidden, vocab, n_rows, seed=71):
+    from paper_2509_24381_amd import runner
+    shape = synth.LayerShape("lm", hidden, 2, 1, 64, 64)
+    ctx = runner.Context(runner.config_for(shape, max_tokens=32, max_requests=1, max_pos=64))
+    rng = np.random.default_rng(seed)
+    g = synth.bf16_round(rng.uniform(0.5, 1.5, hidden).astype(np.float32))
+    w = synth.bf16_round((rng.standard_normal((vocab, hidden)) * 0.02).astype(np.float32))
+    x = synth.bf16_round(rng.standard_normal((n_rows, hidden)).astype(np.float32))
+    return runner, ctx, shape, g, w, x
+
+
+@pytest.mark.parametrize("hidden, vocab, n_rows", [(64, 64, 3), (128, 63, 4), (192, 65, 10), (256, 1, 11), (320, 16385, 20),
+                                                   (704, 5000, 21), (3584, 777, 41), (8192, 300, 9)])
+def test_logits_of_three_rows_and_more(hidden, vocab, n_rows):
+    """One to eleven groups of 64 features for four wavefronts (some without any), vocabularies of one row, of a tile and one
+    more or less, and of a share with a remainder; one and two groups of rows, and passes of 20 with a rest."""
+    runner, ctx, shape, g, w, x = _head(hidden, vocab, n_rows)
+    got = ctx.lm_head(runner.to_device_bf16(g), runner.to_device_bf16(w), runner.to_device_bf16(x)).cpu().numpy()
+    err = rel_fro(got, first_token_logits(x, g, w, shape.rms_eps))
+    print(f"[parity] logits H={hidden} V={vocab} R={n_rows}: {err:.2e}", flush=True)
+    assert err <= 1e-6
+
+
+def test_a_workspace_of_four_bytes_per_value_is_still_enough():
+    """4 H bytes per row (rounded up to 256) is all the fp32 kernel needs; the same call with the full size takes the matrix
+    path.  Both meet the bar; a smaller workspace is refused."""
+    runner, ctx, shape, g, w, x = _head(1024, 3000, 5)
+    gd, wd, xd = (runner.to_device_bf16(a) for a in (g, w, x))
+    out = torch.empty((5, 3000), dtype=torch.float32, device="cuda")
+    ws = torch.empty(ctx.lib.rs_lm_head_workspace_bytes(ctx.handle, 5), dtype=torch.uint8, device="cuda")
+    want = first_token_logits(x, g, w, shape.rms_eps)
+    for n, ok in [(5 * 1024 * 4, True), (ws.numel(), True), (5 * 1024 * 4 - 256, False)]:
+        out.fill_(0)
+        st = ctx.lib.rs_lm_head(ctx.handle, gd.data_ptr(), wd.data_ptr(), 3000, xd.data_ptr(), 5, out.data_ptr(), ws.data_ptr(),
+                                C.c_size_t(n), torch.cuda.current_stream().cuda_stream or None)
+        assert st == (0 if ok else -3)
+        if ok:
+            assert rel_fro(out.cpu().numpy(), want) <= 1e-6
+
+
+def test_infinite_weights_and_nan_rows_stay_where_they_are():
+    """An infinite weight gives infinite logits of h's sign in its vocabulary row only; a row of x with a NaN gives NaN in
+    that row only."""
+    runner, ctx, shape, g, w, x = _head(256, 200, 6)
+    w[17, 5], w[130, 200] = np.inf, -np.inf
+    x[2, 9] = np.nan
+    got = ctx.lm_head(runner.to_device_bf16(g), runner.to_device_bf16(w), runner.to_device_bf16(x)).cpu().numpy()
+    rows = [0, 1, 3, 4, 5]
+    assert np.all(np.isnan(got[2]))
+    np.testing.assert_array_equal(got[rows, 17], np.where(x[rows, 5] > 0, np.inf, -np.inf))
+    np.testing.assert_array_equal(got[rows, 130], np.where(x[rows, 200] > 0, -np.inf, np.inf))
+    fin = np.delete(np.arange(200), [17, 130])
+    want = first_token_logits(x[rows], g, w[fin], shape.rms_eps)
+    assert rel_fro(got[np.ix_(rows, fin)], want) <= 1e-6
