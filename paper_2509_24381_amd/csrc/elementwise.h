@@ -489,7 +489,7 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const bf16* __restrict__
     }
 }
 
-// ---------------------------------------------------------------- cache export / import (canonical [tokens][Hkv][d])
+// ---------------------------------------------------------------- tiles of a cache in export / import (kv_transfer.h)
 // The cache is described like a request (ReqDesc: contiguous planes, or the pool base for a paged cache).  The page
 // numbers of a paged cache travel in the kernel arguments, a window of KV_PAGE_WINDOW blocks per launch starting at
 // block `block0`; tokens [t0, t0 + n) are handled, t0 a multiple of 64 inside the window.
@@ -504,37 +504,4 @@ RS_DEVICE bf16* kv_window_tile(const ReqDesc& rq, const KVPageWindow& win, int b
     if (rq.pages == nullptr)   // (any non-null value marks a paged cache here; the numbers come from the window)
         return (v ? rq.vtcache : rq.kcache) + ((size_t)c * (size_t)(rq.cap >> 6) + (size_t)block) * TILE;
     return rq.kcache + ((size_t)win.page[block - block0] * 2 * rq.hkv + (size_t)(v ? rq.hkv : 0) + (size_t)c) * TILE;
-}
-
-template <int D>
-__global__ __launch_bounds__(256) void kv_export_kernel(ReqDesc rq, KVPageWindow win, int block0, bf16* __restrict__ k_out,
-                                                        bf16* __restrict__ v_out, int t0, int n) {
-    const int Hkv = rq.hkv;
-    const size_t total = (size_t)n * Hkv * D;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int dd = (int)(i % D);
-        const int c = (int)((i / D) % Hkv);
-        const int t = t0 + (int)(i / ((size_t)D * Hkv));
-        const size_t o = (size_t)t0 * Hkv * D + i;
-        k_out[o] = kv_window_tile<D>(rq, win, block0, false, c, t >> 6)[(size_t)(t & 63) * D + dd];
-        v_out[o] = kv_window_tile<D>(rq, win, block0, true, c, t >> 6)[(size_t)dd * 64 + (t & 63)];
-    }
-}
-
-template <int D>
-__global__ __launch_bounds__(256) void kv_import_kernel(ReqDesc rq, KVPageWindow win, int block0, const bf16* __restrict__ k_in,
-                                                        const bf16* __restrict__ v_in, int t0, int n) {
-    const int Hkv = rq.hkv;
-    const int n_pad = (n + 63) & ~63;  // the last touched V block is zero-filled beyond t0 + n
-    const size_t total = (size_t)n_pad * Hkv * D;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int dd = (int)(i % D);
-        const int c = (int)((i / D) % Hkv);
-        const int tl = (int)(i / ((size_t)D * Hkv));
-        const int t = t0 + tl;
-        const bool live = tl < n;
-        const size_t o = (size_t)t0 * Hkv * D + i;
-        if (live) kv_window_tile<D>(rq, win, block0, false, c, t >> 6)[(size_t)(t & 63) * D + dd] = k_in[o];
-        kv_window_tile<D>(rq, win, block0, true, c, t >> 6)[(size_t)dd * 64 + (t & 63)] = live ? v_in[o] : f32_to_bf16(0.0f);
-    }
 }

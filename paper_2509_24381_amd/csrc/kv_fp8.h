@@ -186,60 +186,10 @@ __global__ __launch_bounds__(256) void kv_expand_fp8_kernel(const ReqDesc* __res
     }
 }
 
-// ---------------------------------------------------------------- export / import (canonical [tokens][Hkv][d])
-// Tokens [t0, t0 + n) of one layer, t0 a multiple of 64.  The cache is described by an Fp8CacheDesc whose `pages` is only a
-// marker here (non-null: paged): the page numbers of blocks [block0, block0 + KV_PAGE_WINDOW) ride in the kernel
-// arguments, as for the bfloat16 caches.  With code outputs (inputs) given the bytes travel as they are; otherwise the
-// bfloat16 values are produced (consumed) through the read (store) formula above.
+// ---------------------------------------------------------------- tiles of a cache in export / import (kv_transfer.h)
+// The page numbers of blocks [block0, block0 + KV_PAGE_WINDOW) ride in the kernel arguments, as for the bfloat16 caches.
 template <int D>
 RS_DEVICE uint8_t* fp8_window_tile(const Fp8CacheDesc& fc, const KVPageWindow& win, int block0, bool v, int c, int block) {
     if (fc.pages == nullptr) return (v ? fc.vc : fc.kc) + fp8_tile_offset(fc.cap, c, block, D);
     return fc.kc + ((size_t)win.page[block - block0] * 2 * fc.hkv + (size_t)(v ? fc.hkv : 0) + (size_t)c) * 64 * D;
-}
-
-template <int D>
-__global__ __launch_bounds__(256) void kv_fp8_export_kernel(Fp8CacheDesc fc, KVPageWindow win, int block0, bf16* __restrict__ k_out,
-                                                            bf16* __restrict__ v_out, uint8_t* __restrict__ kc_out,
-                                                            uint8_t* __restrict__ vc_out, int t0, int n) {
-    const int Hkv = fc.hkv;
-    const size_t total = (size_t)n * Hkv * D;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int dd = (int)(i % D);
-        const int c = (int)((i / D) % Hkv);
-        const int t = t0 + (int)(i / ((size_t)D * Hkv));
-        const size_t o = (size_t)t0 * Hkv * D + i;
-        const uint8_t ck = fp8_window_tile<D>(fc, win, block0, false, c, t >> 6)[(size_t)(t & 63) * D + dd];
-        const uint8_t cv = fp8_window_tile<D>(fc, win, block0, true, c, t >> 6)[(size_t)dd * 64 + (t & 63)];
-        if (kc_out) {
-            kc_out[o] = ck;
-            vc_out[o] = cv;
-        } else {
-            k_out[o] = bf16_from_e4m3(ck, fc.k_scale);
-            v_out[o] = bf16_from_e4m3(cv, fc.v_scale);
-        }
-    }
-}
-
-template <int D>
-__global__ __launch_bounds__(256) void kv_fp8_import_kernel(Fp8CacheDesc fc, KVPageWindow win, int block0, const bf16* __restrict__ k_in,
-                                                            const bf16* __restrict__ v_in, const uint8_t* __restrict__ kc_in,
-                                                            const uint8_t* __restrict__ vc_in, int t0, int n) {
-    const int Hkv = fc.hkv;
-    const int n_pad = (n + 63) & ~63;  // the last touched V block is zero beyond t0 + n
-    const size_t total = (size_t)n_pad * Hkv * D;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int dd = (int)(i % D);
-        const int c = (int)((i / D) % Hkv);
-        const int tl = (int)(i / ((size_t)D * Hkv));
-        const int t = t0 + tl;
-        const bool live = tl < n;
-        const size_t o = (size_t)t0 * Hkv * D + i;
-        uint8_t cv = 0;
-        if (live) {
-            const uint8_t ck = kc_in ? kc_in[o] : e4m3_from_bf16(k_in[o], fc.k_inv);
-            cv = vc_in ? vc_in[o] : e4m3_from_bf16(v_in[o], fc.v_inv);
-            fp8_window_tile<D>(fc, win, block0, false, c, t >> 6)[(size_t)(t & 63) * D + dd] = ck;
-        }
-        fp8_window_tile<D>(fc, win, block0, true, c, t >> 6)[(size_t)dd * 64 + (t & 63)] = cv;
-    }
 }

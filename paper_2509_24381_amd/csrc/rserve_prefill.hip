@@ -18,6 +18,7 @@
 #include "common.h"
 #include "elementwise.h"
 #include "kv_fp8.h"
+#include "kv_transfer.h"
 #include "gemm_strip.h"
 #include "last_error.h"
 
@@ -581,16 +582,29 @@ void for_each_fp8_window(const rs_kv* kv, int layer, int n, Launch&& launch) {
     }
 }
 
-// Tokens [0, len) of an 8-bit cache's layer as bfloat16 values or as codes (whichever pair of outputs is given).
-rs_status fp8_export(const rs_kv* kv, int layer, bf16* k_out, bf16* v_out, uint8_t* kc_out, uint8_t* vc_out, hipStream_t st) {
-    const int kv_dim = kv->ctx->kv_dim;
-    const bool d128 = kv->ctx->cfg.head_dim == 128;
+// One launch of the export or import kernel over a window's tokens (see kv_transfer.h).
+template <class T, class C>
+void launch_export(const rs_ctx* c, const ReqDesc& rq, const Fp8CacheDesc& fc, const KVPageWindow& win, int b0, C* k, C* v, int t0, int nt,
+                   hipStream_t st) {
+    const dim3 grid((nt + 63) / 64, c->cfg.n_kv_heads);
+    const int wide = aligned(k, 8 * sizeof(C)) && aligned(v, 8 * sizeof(C));
+    if (c->cfg.head_dim == 128) hipLaunchKernelGGL((kv_export_kernel<128, T, C>), grid, dim3(256), 0, st, rq, fc, win, b0, k, v, t0, nt, wide);
+    else hipLaunchKernelGGL((kv_export_kernel<64, T, C>), grid, dim3(256), 0, st, rq, fc, win, b0, k, v, t0, nt, wide);
+}
+template <class T, class C>
+void launch_import(const rs_ctx* c, const ReqDesc& rq, const Fp8CacheDesc& fc, const KVPageWindow& win, int b0, const C* k, const C* v, int t0,
+                   int nt, hipStream_t st) {
+    const dim3 grid((nt + 63) / 64, c->cfg.n_kv_heads);
+    const int wide = aligned(k, 8 * sizeof(C)) && aligned(v, 8 * sizeof(C));
+    if (c->cfg.head_dim == 128) hipLaunchKernelGGL((kv_import_kernel<128, T, C>), grid, dim3(256), 0, st, rq, fc, win, b0, k, v, t0, nt, wide);
+    else hipLaunchKernelGGL((kv_import_kernel<64, T, C>), grid, dim3(256), 0, st, rq, fc, win, b0, k, v, t0, nt, wide);
+}
+
+// Tokens [0, len) of an 8-bit cache's layer as bfloat16 values (C = bf16) or as codes (C = uint8_t).
+template <class C>
+rs_status fp8_export(const rs_kv* kv, int layer, C* k_out, C* v_out, hipStream_t st) {
     for_each_fp8_window(kv, layer, kv->len[layer], [&](const Fp8CacheDesc& fc, const KVPageWindow& win, int b0, int t0, int nt) {
-        const int blocks = (int)std::min<size_t>(((size_t)nt * kv_dim + 255) / 256, 4096);
-        if (d128)
-            hipLaunchKernelGGL(kv_fp8_export_kernel<128>, dim3(blocks), dim3(256), 0, st, fc, win, b0, k_out, v_out, kc_out, vc_out, t0, nt);
-        else
-            hipLaunchKernelGGL(kv_fp8_export_kernel<64>, dim3(blocks), dim3(256), 0, st, fc, win, b0, k_out, v_out, kc_out, vc_out, t0, nt);
+        launch_export<uint8_t>(kv->ctx, ReqDesc{}, fc, win, b0, k_out, v_out, t0, nt, st);
     });
     RS_HIP(hipGetLastError());
     return RS_OK;
@@ -598,16 +612,10 @@ rs_status fp8_export(const rs_kv* kv, int layer, bf16* k_out, bf16* v_out, uint8
 
 // Fills tokens [0, n) of an 8-bit cache's layer from bfloat16 values or from codes (the caller has checked n against the
 // capacity and, for a paged cache, taken the pages).
-rs_status fp8_import(rs_kv* kv, int layer, const bf16* k_in, const bf16* v_in, const uint8_t* kc_in, const uint8_t* vc_in, int n,
-                     hipStream_t st) {
-    const int kv_dim = kv->ctx->kv_dim;
-    const bool d128 = kv->ctx->cfg.head_dim == 128;
+template <class C>
+rs_status fp8_import(rs_kv* kv, int layer, const C* k_in, const C* v_in, int n, hipStream_t st) {
     for_each_fp8_window(kv, layer, n, [&](const Fp8CacheDesc& fc, const KVPageWindow& win, int b0, int t0, int nt) {
-        const int blocks = (int)std::min<size_t>((align_up((size_t)nt, 64) * kv_dim + 255) / 256, 4096);
-        if (d128)
-            hipLaunchKernelGGL(kv_fp8_import_kernel<128>, dim3(blocks), dim3(256), 0, st, fc, win, b0, k_in, v_in, kc_in, vc_in, t0, nt);
-        else
-            hipLaunchKernelGGL(kv_fp8_import_kernel<64>, dim3(blocks), dim3(256), 0, st, fc, win, b0, k_in, v_in, kc_in, vc_in, t0, nt);
+        launch_import<uint8_t>(kv->ctx, ReqDesc{}, fc, win, b0, k_in, v_in, t0, nt, st);
     });
     RS_HIP(hipGetLastError());
     return RS_OK;
@@ -1340,17 +1348,10 @@ rs_status rs_kv_export(const rs_kv* kv, int layer, void* k_out, void* v_out, voi
     if (n == 0) return RS_OK;
     if (!k_out || !v_out) return fail(RS_EINVAL, "k_out / v_out is null");
     if (!kv->ctx->has_device) return fail(RS_EHIP, "no HIP device");
-    const rs_layer_cfg& f = kv->ctx->cfg;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const int kv_dim = kv->ctx->kv_dim;
-    if (kv->fp8) return fp8_export(kv, layer, (bf16*)k_out, (bf16*)v_out, nullptr, nullptr, st);
+    if (kv->fp8) return fp8_export(kv, layer, (bf16*)k_out, (bf16*)v_out, st);
     for_each_kv_window(kv, layer, n, [&](const ReqDesc& rq, const KVPageWindow& win, int b0, int t0, int nt) {
-        const size_t total = (size_t)nt * kv_dim;
-        const int blocks = (int)std::min<size_t>((total + 255) / 256, 4096);
-        if (f.head_dim == 128)
-            hipLaunchKernelGGL(kv_export_kernel<128>, dim3(blocks), dim3(256), 0, st, rq, win, b0, (bf16*)k_out, (bf16*)v_out, t0, nt);
-        else
-            hipLaunchKernelGGL(kv_export_kernel<64>, dim3(blocks), dim3(256), 0, st, rq, win, b0, (bf16*)k_out, (bf16*)v_out, t0, nt);
+        launch_export<bf16>(kv->ctx, rq, Fp8CacheDesc{}, win, b0, (bf16*)k_out, (bf16*)v_out, t0, nt, st);
     });
     RS_HIP(hipGetLastError());
     return RS_OK;
@@ -1369,25 +1370,18 @@ rs_status rs_kv_import(rs_kv* kv, int layer, const void* k, const void* v, int n
     }
     if (!k || !v) return fail(RS_EINVAL, "k / v is null");
     if (!kv->ctx->has_device) return fail(RS_EHIP, "no HIP device");
-    const rs_layer_cfg& f = kv->ctx->cfg;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const int kv_dim = kv->ctx->kv_dim;
     if (kv->paged()) {
         kv->take_pages(layer, n_tokens);
         kv->give_back_pages(layer, n_tokens);
     }
     if (kv->fp8) {
-        const rs_status s = fp8_import(kv, layer, (const bf16*)k, (const bf16*)v, nullptr, nullptr, n_tokens, st);
+        const rs_status s = fp8_import(kv, layer, (const bf16*)k, (const bf16*)v, n_tokens, st);
         if (s == RS_OK) kv->len[layer] = n_tokens;
         return s;
     }
     for_each_kv_window(kv, layer, n_tokens, [&](const ReqDesc& rq, const KVPageWindow& win, int b0, int t0, int nt) {
-        const size_t total = align_up((size_t)nt, 64) * kv_dim;
-        const int blocks = (int)std::min<size_t>((total + 255) / 256, 4096);
-        if (f.head_dim == 128)
-            hipLaunchKernelGGL(kv_import_kernel<128>, dim3(blocks), dim3(256), 0, st, rq, win, b0, (const bf16*)k, (const bf16*)v, t0, nt);
-        else
-            hipLaunchKernelGGL(kv_import_kernel<64>, dim3(blocks), dim3(256), 0, st, rq, win, b0, (const bf16*)k, (const bf16*)v, t0, nt);
+        launch_import<bf16>(kv->ctx, rq, Fp8CacheDesc{}, win, b0, (const bf16*)k, (const bf16*)v, t0, nt, st);
     });
     RS_HIP(hipGetLastError());
     kv->len[layer] = n_tokens;
@@ -1401,7 +1395,7 @@ rs_status rs_kv_export_codes(const rs_kv* kv, int layer, void* k_codes, void* v_
     if (kv->len[layer] == 0) return RS_OK;
     if (!k_codes || !v_codes) return fail(RS_EINVAL, "k_codes / v_codes is null");
     if (!kv->ctx->has_device) return fail(RS_EHIP, "no HIP device");
-    return fp8_export(kv, layer, nullptr, nullptr, (uint8_t*)k_codes, (uint8_t*)v_codes, reinterpret_cast<hipStream_t>(stream));
+    return fp8_export(kv, layer, (uint8_t*)k_codes, (uint8_t*)v_codes, reinterpret_cast<hipStream_t>(stream));
 }
 
 rs_status rs_kv_import_codes(rs_kv* kv, int layer, const void* k_codes, const void* v_codes, int n_tokens, void* stream) {
@@ -1422,8 +1416,7 @@ rs_status rs_kv_import_codes(rs_kv* kv, int layer, const void* k_codes, const vo
         kv->take_pages(layer, n_tokens);
         kv->give_back_pages(layer, n_tokens);
     }
-    const rs_status s = fp8_import(kv, layer, nullptr, nullptr, (const uint8_t*)k_codes, (const uint8_t*)v_codes, n_tokens,
-                                   reinterpret_cast<hipStream_t>(stream));
+    const rs_status s = fp8_import(kv, layer, (const uint8_t*)k_codes, (const uint8_t*)v_codes, n_tokens, reinterpret_cast<hipStream_t>(stream));
     if (s == RS_OK) kv->len[layer] = n_tokens;
     return s;
 }
