@@ -458,34 +458,39 @@ __global__ __launch_bounds__(256) void append_kv_kernel(const bf16* __restrict__
 }
 
 // ---------------------------------------------------------------- weight packing (one-time)
-// dst[prow][k] = bf16(src[srow][k] * gain[k]): the RMSNorm gain is folded into the weight columns of the GEMM that follows
-// the norm, and rows are reordered so that what an epilogue combines sits in one 32-row unit (one MFMA tile), in rows t and
-// t + 16, which one lane holds:
+// packed[prow][k] = bf16(src[srow][k] * gain[k]), stored fragment-major (units of 32 rows, see frag_offset_bytes in
+// gemm_strip.h): the RMSNorm gain is folded into the weight columns of the GEMM that follows the norm (gain null: copied
+// as they are), and rows are reordered so that what an epilogue combines sits in one 32-row unit (one MFMA tile), in rows
+// t and t + 16, which one lane holds:
 //   PACK_GATE_UP (p0 = I):  unit u = 16 gate rows 16u..16u+15, then the up rows I + 16u..
 //   PACK_QKV_ROPE (p0 = head_dim, p1 = number of q and k rows): unit u of a head = features 16u..16u+15 of the head's
 //                 first half, then their rotate-half partners head_dim/2 + 16u..; v rows keep their order
+// One workgroup per unit: 8 neighbouring 16-byte chunks of its 32 rows at a time (whole cache lines read, 512 contiguous
+// bytes written per chunk).  `wide`: the source can be read 16 bytes at a time.
 enum PackMode { PACK_IDENTITY = 0, PACK_GATE_UP = 1, PACK_QKV_ROPE = 2 };
 __global__ __launch_bounds__(256) void pack_rows_kernel(const bf16* __restrict__ src, const bf16* __restrict__ gain,
-                                                        bf16* __restrict__ dst, int K, int mode, int p0, int p1) {
-    const int prow = blockIdx.x;
+                                                        bf16* __restrict__ dst, int K, int mode, int p0, int p1, int wide) {
+    const int u = blockIdx.x, t = threadIdx.x & 31;
+    const int prow = u * 32 + t;
     int srow = prow;
-    const int t = prow & 31;
     if (mode == PACK_GATE_UP) {
-        const int u = prow >> 5;
         srow = (t < 16) ? (u * 16 + t) : (p0 + u * 16 + (t - 16));
     } else if (mode == PACK_QKV_ROPE && prow < p1) {
         const int head = prow / p0, uh = (prow % p0) >> 5;
         srow = head * p0 + ((t < 16) ? (uh * 16 + t) : (p0 / 2 + uh * 16 + (t - 16)));
     }
     const bf16* s = src + (size_t)srow * K;
-    bf16* d = dst + (size_t)prow * K;
-    for (int c = threadIdx.x; c < K / 8; c += blockDim.x) {
-        bf16x8 v = *reinterpret_cast<const bf16x8*>(s + c * 8);
-        bf16x8 g = *reinterpret_cast<const bf16x8*>(gain + c * 8);
-        bf16x8 o;
+    bf16* d = dst + (size_t)u * 32 * K + t * 8;
+    for (int c = threadIdx.x >> 5; c < K / 8; c += 8) {
+        uint4 v = load8(s + c * 8, wide != 0);
+        if (gain != nullptr) {
+            const bf16x8 h = as_bf16x8(v), g = *reinterpret_cast<const bf16x8*>(gain + c * 8);
+            bf16x8 o;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = f32_to_bf16(bf16_to_f32(v[e]) * bf16_to_f32(g[e]));
-        *reinterpret_cast<bf16x8*>(d + c * 8) = o;
+            for (int e = 0; e < 8; ++e) o[e] = f32_to_bf16(bf16_to_f32(h[e]) * bf16_to_f32(g[e]));
+            v = as_uint4(o);
+        }
+        st_global_16(d + (size_t)c * 256, v);
     }
 }
 

@@ -13,11 +13,11 @@
 // start and end at any unit.  The 4 wavefronts of a workgroup are stacked along the token dimension (64 rows each, 2 x NT
 // MFMA tiles, up to 256 fp32 accumulators per lane, one wavefront per SIMD).
 //
-// The weight rows travel global -> LDS directly (buffer_load ... lds, 16 bytes per lane, no VGPR staging) through a ring
+// Both operands are stored fragment-major.  The weights travel global -> LDS directly (buffer_load ... lds, 16 bytes per lane, no VGPR staging) through a ring
 // of slots, one step of K = 64 per slot; the load stream runs SLOTS - 1 steps ahead of the multiply and does not stop at
-// tile boundaries, so the next tile's first slabs arrive while the current tile's epilogue runs.  A slot row is 128
-// bytes; 16-byte chunk c of row r sits at place c ^ ((r >> 1) & 7), which keeps both the linear 1 KB-per-wavefront DMA
-// fills and the row-strided fragment reads free of bank conflicts.  The token rows are stored fragment-major and go
+// tile boundaries, so the next tile's first slabs arrive while the current tile's epilogue runs.  A unit's k-step is
+// one contiguous kilobyte in memory and in the slot, which the DMA fills and the fragment reads walk in lane order: no bank
+// conflicts.  (Row-major weights with swizzled slots ran as fast here; gemm_skinny.h needs this order.)  The token rows go
 // global -> registers, XD steps ahead.  Rows past M fall outside the buffer resource and read as zeros.
 //
 // The compiler cannot see LDS written by DMA (it would wait for every outstanding load before any LDS read), so the
@@ -40,7 +40,7 @@ enum GemmEpilogue {
 
 struct GemmArgs {
     const bf16* X;      // [M, K] activations, fragment-major (frag_offset_bytes with width K), blocks of 32 tokens
-    const bf16* W;      // [N, K] packed weights, row stride K
+    const bf16* W;      // [N, K] packed weights, fragment-major (frag_offset_bytes with width K), units of 32 rows
     bf16* out;          // [M, ldo], row-major or (out_frag) fragment-major of width ldo
     const bf16* bias;   // [N] in the original feature order, or null
     const bf16* resid;  // [M, ldr], row-major or (resid_frag) fragment-major of width ldr
@@ -121,15 +121,15 @@ RS_DEVICE u32x4 pair_runs(bf16x4 even_run, bf16x4 odd_run) {
 // the pipeline's in-flight fragments to scratch memory to make room (about 100 dwords per lane and tile, written and read
 // back).  The empty asm statement at the top of each unit's iteration pins that unit's tile in accumulation registers up to
 // there, so the copies are made 16 registers at a time and nothing spills.
-template <int EPI, int NT, int USTRIDE = 1>
-RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][2], int m_base, int unit0, int half, int l32, int split,
-                             float (&row_val)[2]) {
+template <int EPI, int NT, int USTRIDE = 1, int NJ = 2>
+RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_base, int unit0, int half, int l32, int split,
+                             float (&row_val)[NJ]) {
     // row_val[j], one value per lane and token block j: EPI_SWIGLU reads the row's factor 1/rms there; EPI_RESIDUAL adds
     // the sum of squares of what it stores of the row (this lane's 16 of each unit's 32 features)
     constexpr int RSRC_FLAGS = 0x00020000;
     const int m_pad = (a.M + 31) & ~31;  // fragment-major buffers hold whole blocks of 32 tokens
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         const int m = m_base + j * 32 + l32;
         if constexpr (EPI == EPI_SWIGLU) {
             // the output is the next GEMM's token operand: always fragment-major.  Unit u holds features 16u..16u+15 = one
@@ -270,6 +270,48 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][2], int m_base
     }
 }
 
+// The row factors of EPI_SWIGLU for the NJ rows mj of a lane.  With rowss the residual GEMM in front left rowss_parts partial
+// sums of squares per row, [part][M]: half 0 of the wavefront adds the even parts, half 1 the odd ones, in ascending order
+// (one fixed order: the result does not depend on anything else), and close_row_factors puts the two together.
+template <int NJ, int B>
+RS_DEVICE void load_row_sums(const GemmArgs& a, const int (&mj)[NJ], int half, float (&row_val)[NJ]) {
+    for (int p0 = half; p0 < a.rowss_parts; p0 += 2 * B) {   // B loads in flight per row: a pass covers 2 B parts
+        float v[NJ][B];
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int p = p0 + 2 * u;
+                v[j][u] = a.rowss[(size_t)min(p, a.rowss_parts - 1) * a.M + mj[j]];
+                if (p >= a.rowss_parts) v[j][u] = 0.0f;
+            }
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) row_val[j] += v[j][u];
+    }
+}
+template <int NJ>
+RS_DEVICE void load_row_factors(const GemmArgs& a, const int (&mj)[NJ], int half, float (&row_val)[NJ]) {
+    if (a.rowss == nullptr) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) row_val[j] = a.row_scale[mj[j]];
+    } else if (a.rowss_parts <= 32) {   // (32 strips at 2048 rows: one pass)
+        load_row_sums<NJ, 16>(a, mj, half, row_val);
+    } else {                            // (a part per unit from gemm_skinny.h: 112 at the 7B shape, two passes)
+        load_row_sums<NJ, 32>(a, mj, half, row_val);
+    }
+}
+template <int NJ>
+RS_DEVICE void close_row_factors(const GemmArgs& a, float (&row_val)[NJ]) {
+    if (a.rowss == nullptr) return;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const float ss = row_val[j] + __shfl_xor(row_val[j], 32, WAVE);
+        row_val[j] = rsqrtf(ss / (float)a.K + a.rms_eps);
+    }
+}
+
 #define RS_DS_READ_B128(dst, addr, off) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
 #define RS_FENCE() __builtin_amdgcn_sched_barrier(0)
 
@@ -337,7 +379,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     const int steps_total = a.K / GS_BK;
     const int st0 = split * a.steps_per_split;
     const int ns = min(a.steps_per_split, steps_total - st0);  // K steps per tile (>= 1)
-    const uint32_t k0 = (uint32_t)st0 * (GS_BK * 2);         // byte offset of the K range in a weight row
+    const uint32_t k0 = (uint32_t)st0 * 4096u;               // byte offset of the K range in a unit of weights
     const uint32_t xk0 = (uint32_t)st0 * 4096u;              // and in a fragment-major token block (4 k-steps of 1 KB)
 
     // ---- token fragments go global -> registers.  X is stored fragment-major (see frag_offset_bytes): the 16 bytes lane
@@ -367,13 +409,13 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
         }
     };
 
-    // ---- weight rows go global -> LDS by DMA: load instruction k of this wavefront fills rows [(wave + 4k)*8, +8) of the
-    //      step's slot, each lane fetching the 16-byte chunk that belongs in its (swizzled) place
+    // ---- weights go global -> LDS by DMA.  They are stored fragment-major too (frag_offset_bytes with the row in place of the
+    //      token): a unit's step of 64 k is 4 contiguous KB, one per k-step, in the order of the MFMA operand's lanes.  Load
+    //      instruction k of this wavefront fetches k-step `wave` of the tile's unit k
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.W, 0, a.N * a.K * 2, 0x00020000);
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
-    const uint32_t ld_c = (uint32_t)((lane & 7) ^ ((((wave & 1) << 2) + (lane >> 4)) & 7));
-    const uint32_t vw0 = (uint32_t)(wave * 8 + (lane >> 3)) * (uint32_t)a.K * 2u + ld_c * 16u;
-    const uint32_t w_step = 32u * (uint32_t)a.K * 2u;  // instruction k + 1 is 32 rows further
+    const uint32_t vw0 = (uint32_t)(wave * 1024 + lane * 16);
+    const uint32_t w_step = 32u * (uint32_t)a.K * 2u;  // a unit
     constexpr uint32_t DEAD = 0x80000000u;  // beyond any buffer this kernel is given: reads as zeros, moves no data
     int d_tile = 0, d_s = 0, d_nt = 0;
     uint32_t d_slot = 0;    // byte offset of the ring slot being filled
@@ -391,7 +433,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     };
     auto stream_advance = [&]() {
         d_slot = (d_slot + SLOT_BYTES) & (RING_BYTES - 1);
-        d_koff += GS_BK * 2;
+        d_koff += 4096;
         if (__builtin_expect(++d_s == ns, 0)) {
             d_s = 0;
             d_koff = k0;
@@ -412,11 +454,11 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     //      SwiGLU epilogue, the running sum of squares of the stored row for the residual epilogue (see gemm_epilogue)
     float row_val[2] = {0.0f, 0.0f};
 
-    // ---- weight fragment addresses inside a slot: row l32 of unit i at i*4096 + l32*128, chunk (2 kk + half) swizzled
+    // ---- weight fragment addresses inside a slot: k-step kk of unit i at i*4096 + kk*1024
     uint32_t aw[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
-        aw[kk] = lds0 + (uint32_t)uw * 4096u + (uint32_t)l32 * 128u + (((uint32_t)(kk * 2 + half) ^ (uint32_t)((l32 >> 1) & 7)) * 16u);
+        aw[kk] = lds0 + (uint32_t)uw * 4096u + (uint32_t)kk * 1024u + (uint32_t)lane * 16u;
     uint32_t c_slot = 0;  // ring slot of the step being multiplied
 
     // ---- fill the pipeline: W(0) .. W(AHEAD - 2), X(0) .. X(XD - 1), W(AHEAD - 1)
@@ -434,44 +476,14 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     });
     prologue_w();
     if constexpr (EPI == EPI_SWIGLU) {
-        // The row factors, behind the pipeline's first loads (and waited for with them).  With rowss the residual GEMM in
-        // front left rowss_parts partial sums of squares per row, [part][M]: half 0 of the wavefront adds the even parts,
-        // half 1 the odd ones, in ascending order (one fixed order: the result does not depend on anything else).
+        // the row factors, behind the pipeline's first loads (and waited for with them)
         int mj[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) mj[j] = min(m0 + tw * 64 + j * 32 + l32, a.M - 1);   // (rows past M: any valid row, nothing is stored)
-        if (a.rowss != nullptr) {
-            constexpr int B = 16;   // loads in flight per row: a pass covers 2 B parts (32 strips at 2048 rows: one pass)
-            for (int p0 = half; p0 < a.rowss_parts; p0 += 2 * B) {
-                float v[2][B];
-#pragma unroll
-                for (int u = 0; u < B; ++u)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        const int p = p0 + 2 * u;
-                        v[j][u] = a.rowss[(size_t)min(p, a.rowss_parts - 1) * a.M + mj[j]];
-                        if (p >= a.rowss_parts) v[j][u] = 0.0f;
-                    }
-#pragma unroll
-                for (int u = 0; u < B; ++u)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) row_val[j] += v[j][u];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) row_val[j] = a.row_scale[mj[j]];
-        }
+        load_row_factors<2>(a, mj, half, row_val);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if constexpr (EPI == EPI_SWIGLU) {
-        if (a.rowss != nullptr) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const float ss = row_val[j] + __shfl_xor(row_val[j], 32, WAVE);
-                row_val[j] = rsqrtf(ss / (float)a.K + a.rms_eps);
-            }
-        }
-    }
+    if constexpr (EPI == EPI_SWIGLU) close_row_factors<2>(a, row_val);
 
     auto run_tile = [&](auto ntc, const int unit0) {
         constexpr int NT = decltype(ntc)::value;   // units of the tile (= weight DMA instructions per step and wavefront)

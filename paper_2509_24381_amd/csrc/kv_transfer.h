@@ -20,32 +20,6 @@
 #include "elementwise.h"
 #include "kv_fp8.h"
 
-template <class T> struct Pack8;   // 8 elements
-template <> struct Pack8<bf16> { typedef uint4 type; };
-template <> struct Pack8<uint8_t> { typedef uint2 type; };
-
-template <class T>
-RS_DEVICE typename Pack8<T>::type load8(const T* p, bool wide) {
-    typedef typename Pack8<T>::type P;
-    if (wide) return *reinterpret_cast<const P*>(p);
-    union { T e[8]; P v; } u;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) u.e[i] = p[i];
-    return u.v;
-}
-template <class T>
-RS_DEVICE void store8(T* p, typename Pack8<T>::type v, bool wide) {
-    typedef typename Pack8<T>::type P;
-    if (wide) {
-        *reinterpret_cast<P*>(p) = v;
-        return;
-    }
-    union { T e[8]; P v; } u;
-    u.v = v;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) p[i] = u.e[i];
-}
-
 // 8 stored elements <-> 8 canonical ones
 RS_DEVICE uint4 convert8(uint4 v, float, bf16*) { return v; }
 RS_DEVICE uint2 convert8(uint2 v, float, uint8_t*) { return v; }

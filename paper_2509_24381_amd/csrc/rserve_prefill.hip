@@ -20,6 +20,7 @@
 #include "kv_fp8.h"
 #include "kv_transfer.h"
 #include "gemm_strip.h"
+#include "gemm_skinny.h"
 #include "last_error.h"
 
 namespace {
@@ -454,6 +455,48 @@ rs_status launch_gemm(const rs_ctx* c, GemmArgs a, int splits, hipStream_t st, i
     return RS_OK;
 }
 
+// Which projections of a call of M rows run in gemm_skinny.h.  Its wavefronts each fetch their own copy of the token
+// fragments, M K 2 bytes per workgroup: it wins while that is small beside what the strip kernel loses to its ring and its
+// reduction.  Measured us per step, strip -> skinny: QKV 7B 1 row 22.0 -> 14.2, 64 rows (M K = 229k) 22.1 -> 18.7, 100 rows
+// (358k) 26.2 -> 26.6, 72B 16 rows (131k) 47 -> 42, 64 rows (524k) 54 -> 70;  O 20 rows 19.1 -> 14.9, 64 rows 20.2 -> 18.3 but
+// the gate/up kernel then closes 112 parts of its row sums, 2 us;  down 20 rows 37.3 -> 35.6, 64 rows 41 -> 46;  layers as
+// narrow as the tiny shape gain up to 128 rows, and in the gate/up projection too (elsewhere that streams 272 MB: 5 TB/s).
+constexpr int SKINNY_ROWS = 128;
+bool skinny_qkv(const rs_ctx* c, int M, int K) { return c->gemm_narrow && M <= SKINNY_ROWS && (long)M * K <= 256 * 1024; }
+bool skinny_residual(const rs_ctx* c, int M, int K) { return c->gemm_narrow && (M <= 32 || (M <= SKINNY_ROWS && K <= 1024)); }
+bool skinny_swiglu(const rs_ctx* c, int M, int K) { return c->gemm_narrow && M <= SKINNY_ROWS && K <= 1024; }
+
+// EPI_QKV_ROPE or EPI_SWIGLU: a wavefront per 32 tokens.
+template <int EPI>
+rs_status launch_skinny_rows(GemmArgs a, hipStream_t st) {
+    a.steps_per_split = a.K / GS_BK;
+    const dim3 grid(a.N / 32);
+    const int blocks = (a.M + 31) / 32;
+    if (blocks == 1) hipLaunchKernelGGL((gemm_skinny_kernel<EPI, 1, 1, 1, 24>), grid, dim3(64), 0, st, a);
+    else if (blocks == 2) hipLaunchKernelGGL((gemm_skinny_kernel<EPI, 1, 2, 1, 24>), grid, dim3(128), 0, st, a);
+    else hipLaunchKernelGGL((gemm_skinny_kernel<EPI, 1, 4, 1, 16>), grid, dim3(256), 0, st, a);
+    RS_HIP(hipGetLastError());
+    return RS_OK;
+}
+
+// A residual projection (EPI_RESIDUAL, one K range) or its partial planes (EPI_PARTIAL).
+template <int EPI>
+rs_status launch_skinny(const rs_ctx* c, GemmArgs a, int splits, hipStream_t st, int* columns_out = nullptr) {
+    const int steps = a.K / GS_BK, units = a.N / 32;
+    a.steps_per_split = (steps + splits - 1) / splits;
+    splits = (steps + a.steps_per_split - 1) / a.steps_per_split;
+    if (columns_out) *columns_out = units;
+    const dim3 grid(units, splits);
+    const int blocks = (a.M + 31) / 32;
+    // eight wavefronts where each still has a few dozen k-steps, four otherwise
+    if (blocks > 2) hipLaunchKernelGGL((gemm_skinny_kernel<EPI, 4, 1, 4, 8>), grid, dim3(256), 4 * 4 * 4096, st, a);
+    else if (blocks == 2) hipLaunchKernelGGL((gemm_skinny_kernel<EPI, 2, 1, 4, 16>), grid, dim3(256), 4 * 2 * 4096, st, a);
+    else if (a.steps_per_split * 4 >= 8 * 32) hipLaunchKernelGGL((gemm_skinny_kernel<EPI, 1, 1, 8, 16>), grid, dim3(512), 8 * 4096, st, a);
+    else hipLaunchKernelGGL((gemm_skinny_kernel<EPI, 1, 1, 4, 24>), grid, dim3(256), 4 * 4096, st, a);
+    RS_HIP(hipGetLastError());
+    return RS_OK;
+}
+
 // out = resid + X W^T, through split-K partials when the unsplit launch would leave compute units idle.  X is fragment-
 // major; resid and out are row-major or fragment-major as flagged.  When inv_rms_out is given, the RMSNorm factor of the
 // next GEMM's input, rsqrt(mean(out[m,:]^2) + eps) per row, is prepared in one of two forms: the split-K reduction writes
@@ -475,7 +518,10 @@ rs_status gemm_residual(const rs_ctx* c, const bf16* X, const bf16* W, const bf1
     a.partial = partial;
     a.M = M; a.N = N; a.K = K;
     const float eps = c->cfg.rms_eps;
+    const bool skinny = skinny_residual(c, M, K);
     int splits = choose_splitk(c, M, N / 32, K / GS_BK);
+    if (skinny && c->splitk_override == 0)   // (a K too long for one compute unit's loads, and units to spare)
+        splits = K >= 8192 && 2 * (N / 32) <= c->n_cu ? 2 : 1;
     if (splits > 1) {
         const int sps = (K / GS_BK + splits - 1) / splits;
         splits = (K / GS_BK + sps - 1) / sps;
@@ -483,9 +529,10 @@ rs_status gemm_residual(const rs_ctx* c, const bf16* X, const bf16* W, const bf1
     if (rowss_parts_out) *rowss_parts_out = 0;
     if (splits == 1) {
         a.rowss = inv_rms_out ? rowss : nullptr;
-        return launch_gemm<EPI_RESIDUAL>(c, a, 1, st, inv_rms_out ? rowss_parts_out : nullptr);
+        return skinny ? launch_skinny<EPI_RESIDUAL>(c, a, 1, st, inv_rms_out ? rowss_parts_out : nullptr)
+                      : launch_gemm<EPI_RESIDUAL>(c, a, 1, st, inv_rms_out ? rowss_parts_out : nullptr);
     }
-    rs_status s = launch_gemm<EPI_PARTIAL>(c, a, splits, st);
+    rs_status s = skinny ? launch_skinny<EPI_PARTIAL>(c, a, splits, st) : launch_gemm<EPI_PARTIAL>(c, a, splits, st);
     if (s != RS_OK) return s;
     if (defer && resid_frag && !out_frag && !inv_rms_out) {
         defer->splits = splits; defer->partial = partial; defer->resid = resid; defer->out = out;
@@ -941,7 +988,7 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         a.rope_cols = ctx->q_dim + ctx->kv_dim; a.head_dim = f.head_dim;
         a.mrope_b0 = ctx->mrope_b0; a.mrope_b1 = ctx->mrope_b1;
         a.M = T; a.N = ctx->qkv_dim; a.K = H;
-        if ((s = launch_gemm<EPI_QKV_ROPE>(ctx, a, 1, st)) != RS_OK) return s;
+        if ((s = skinny_qkv(ctx, T, H) ? launch_skinny_rows<EPI_QKV_ROPE>(a, st) : launch_gemm<EPI_QKV_ROPE>(ctx, a, 1, st)) != RS_OK) return s;
     }
     tm.end(RS_STEP_QKV_GEMM);
     // cache append, attention
@@ -967,7 +1014,7 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
             a.rowss = rowss; a.rowss_parts = rowss_parts; a.rms_eps = f.rms_eps;
         }
         a.M = T; a.N = 2 * I; a.K = H;
-        if ((s = launch_gemm<EPI_SWIGLU>(ctx, a, 1, st)) != RS_OK) return s;
+        if ((s = skinny_swiglu(ctx, T, H) ? launch_skinny_rows<EPI_SWIGLU>(a, st) : launch_gemm<EPI_SWIGLU>(ctx, a, 1, st)) != RS_OK) return s;
     }
     tm.end(RS_STEP_GATE_UP_GEMM);
     // y = r + act Wd^T
@@ -1137,25 +1184,24 @@ rs_status rs_weights_pack(rs_ctx* c, const rs_layer_weights* src, void* dst, siz
     rs_layer_weights o{};
     RS_HIP(copy(src->ln1_g, H * 2, &o.ln1_g));
     RS_HIP(copy(src->ln2_g, H * 2, &o.ln2_g));
+    auto pack = [&](const void* m, int rows, int K, const void* gain, int mode, int p0, int p1, const void** slot) -> hipError_t {
+        *slot = p;
+        hipLaunchKernelGGL(pack_rows_kernel, dim3(rows / 32), dim3(256), 0, st, (const bf16*)m, (const bf16*)gain, reinterpret_cast<bf16*>(p), K,
+                           mode, p0, p1, (int)aligned(m, 16));
+        p += align_up((size_t)rows * K * 2, 256);
+        return hipGetLastError();
+    };
     // W_qkv with the first norm's gain folded into its columns
-    o.w_qkv = p;
-    hipLaunchKernelGGL(pack_rows_kernel, dim3(c->qkv_dim), dim3(256), 0, st, (const bf16*)src->w_qkv, (const bf16*)src->ln1_g,
-                       reinterpret_cast<bf16*>(p), f.hidden, (int)PACK_QKV_ROPE, f.head_dim, c->q_dim + c->kv_dim);
-    RS_HIP(hipGetLastError());
-    p += align_up((size_t)c->qkv_dim * H * 2, 256);
+    RS_HIP(pack(src->w_qkv, c->qkv_dim, f.hidden, src->ln1_g, PACK_QKV_ROPE, f.head_dim, c->q_dim + c->kv_dim, &o.w_qkv));
     if (f.qkv_bias) {
         RS_HIP(copy(src->b_qkv, (size_t)c->qkv_dim * 2, &o.b_qkv));
     } else {
         p += align_up((size_t)c->qkv_dim * 2, 256);
     }
-    RS_HIP(copy(src->w_o, H * c->q_dim * 2, &o.w_o));
+    RS_HIP(pack(src->w_o, f.hidden, c->q_dim, nullptr, PACK_IDENTITY, 0, 0, &o.w_o));
     // W_gate / W_up interleaved in 16-row blocks (one unit = 16 gate rows + their up rows), second norm gain folded in
-    o.w_gate_up = p;
-    hipLaunchKernelGGL(pack_rows_kernel, dim3(2 * f.mlp_inter), dim3(256), 0, st, (const bf16*)src->w_gate_up,
-                       (const bf16*)src->ln2_g, reinterpret_cast<bf16*>(p), f.hidden, (int)PACK_GATE_UP, f.mlp_inter, 0);
-    RS_HIP(hipGetLastError());
-    p += align_up(2 * I * H * 2, 256);
-    RS_HIP(copy(src->w_down, H * I * 2, &o.w_down));
+    RS_HIP(pack(src->w_gate_up, 2 * f.mlp_inter, f.hidden, src->ln2_g, PACK_GATE_UP, f.mlp_inter, 0, &o.w_gate_up));
+    RS_HIP(pack(src->w_down, f.hidden, f.mlp_inter, nullptr, PACK_IDENTITY, 0, 0, &o.w_down));
     *packed = o;
     return RS_OK;
 }
