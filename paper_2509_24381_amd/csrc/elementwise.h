@@ -465,8 +465,9 @@ __global__ __launch_bounds__(256) void append_kv_kernel(const bf16* __restrict__
 //   PACK_GATE_UP (p0 = I):  unit u = 16 gate rows 16u..16u+15, then the up rows I + 16u..
 //   PACK_QKV_ROPE (p0 = head_dim, p1 = number of q and k rows): unit u of a head = features 16u..16u+15 of the head's
 //                 first half, then their rotate-half partners head_dim/2 + 16u..; v rows keep their order
-// One workgroup per unit: 8 neighbouring 16-byte chunks of its 32 rows at a time (whole cache lines read, 512 contiguous
-// bytes written per chunk).  `wide`: the source can be read 16 bytes at a time.
+// One workgroup per unit and PACK_K features (grid y): 8 neighbouring 16-byte chunks of its 32 rows at a time (whole cache
+// lines read, 512 contiguous bytes written per chunk).  `wide`: the source can be read 16 bytes at a time.
+constexpr int PACK_K = 256;
 enum PackMode { PACK_IDENTITY = 0, PACK_GATE_UP = 1, PACK_QKV_ROPE = 2 };
 __global__ __launch_bounds__(256) void pack_rows_kernel(const bf16* __restrict__ src, const bf16* __restrict__ gain,
                                                         bf16* __restrict__ dst, int K, int mode, int p0, int p1, int wide) {
@@ -481,8 +482,17 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const bf16* __restrict__
     }
     const bf16* s = src + (size_t)srow * K;
     bf16* d = dst + (size_t)u * 32 * K + t * 8;
-    for (int c = threadIdx.x >> 5; c < K / 8; c += 8) {
-        uint4 v = load8(s + c * 8, wide != 0);
+    constexpr int N = PACK_K / 64;   // chunks per thread, all loads in flight together
+    const int c0 = blockIdx.y * (PACK_K / 8) + (int)(threadIdx.x >> 5);
+    uint4 in[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (c0 + i * 8 < K / 8) in[i] = load8(s + (c0 + i * 8) * 8, wide != 0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int c = c0 + i * 8;
+        if (c >= K / 8) break;
+        uint4 v = in[i];
         if (gain != nullptr) {
             const bf16x8 h = as_bf16x8(v), g = *reinterpret_cast<const bf16x8*>(gain + c * 8);
             bf16x8 o;
