@@ -139,8 +139,8 @@ struct AttnPartial {
 // behind the MFMAs that are left.  The four buffers are separate LDS objects so that the compiler can tell that the
 // fragment reads do not touch the buffers being filled.
 //
-// There is no running maximum in the loop.  A query's reference starts as the exact maximum of its first 32 keys and
-// stays until the probabilities of a half tile sum to more than ATT_RESCALE_SUM in one of the query's two lanes - the row
+// There is no running maximum in the loop.  A query's reference starts as the exact maximum of its first 32 keys (the lowest
+// finite number if they all score minus infinity) and stays until the probabilities of a half tile sum to more than ATT_RESCALE_SUM in one of the query's two lanes - the row
 // sum is needed anyway -; then (rarely: a request's first tiles) the half's exact maximum becomes the reference, the
 // accumulated output and row sum are rescaled and the half's probabilities are taken again from its raw scores, which are
 // still in registers.  Probabilities thus stay below ATT_RESCALE_SUM, which fp32 sums and bf16's relative rounding do not
@@ -353,7 +353,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_prefill_pipelined_kernel(c
     };
     first_scores(std::integral_constant<int, 0>{}, s0);
     first_scores(std::integral_constant<int, 1>{}, s1);
-    m_ref = half_max(s0);   // finite: the first key of a part is visible to every query of the block
+    // The first key of a part is visible to every query of the block, but its score, and those of the other 31, may be minus
+    // infinity (an infinite key element, an overflow): from the lowest finite reference such keys weigh nothing, and the first
+    // finite score moves it.
+    m_ref = fmaxf(half_max(s0), -3.402823466e38f);
     l_run = all_exps(s0, pf0);
     __syncthreads();  // every wavefront is done with the first K tile: it may be overwritten
     fetch_k(k_buf0, kb0 + 2, pg_v);

@@ -82,3 +82,34 @@ def test_key_ranges_cut_for_unequal_requests(n_cu, monkeypatch):
     shape = synth.LayerShape("small128", 256, 4, 2, 128, 256)
     spec = [(3000, 40), (0, 70), (900, 33), (1500, 128), (64, 1), (2047, 129)]
     _attention_term(shape, _requests(shape, spec, 700), f"planned for {n_cu} units", 2e-2, 3200)
+
+
+@pytest.mark.parametrize("n_cu, split", [(None, None), ("1", None), (None, "2")])
+@pytest.mark.parametrize("d", [64, 128])
+def test_keys_that_score_minus_infinity(d, n_cu, split, monkeypatch):
+    """Cached keys whose score is minus infinity for every query weigh nothing, also where they are the first 32 keys of a
+    cache or of a part (those the reference starts from) and a whole later half tile."""
+    for name, value in (("RS_NCU", n_cu), ("RS_ATTN_SPLIT", split)):
+        if value:
+            monkeypatch.setenv(name, value)
+    shape = synth.LayerShape("minf", 256, 4, 2, d, 256)
+    prior, t_new = 900, 30    # 15 tiles: in two parts the second starts at tile 7
+    reqs = _requests(shape, [(prior, t_new)], 800)
+    for first in (0, 7 * 64, 600):
+        reqs[0].prior_k[first: first + 32, :, d // 2 - 1] = -np.inf
+    # q is its bias alone; its slowest rotary pair is (1, 1), which the rotation at these positions leaves positive
+    w = synth.layer_weights(shape, 41, qkv_bias=True, gains="uniform")
+    w.wq, w.wd = np.zeros_like(w.wq), np.zeros_like(w.wd)
+    bq = w.bq.reshape(shape.n_q_heads, d)
+    bq[:, [d // 2 - 1, d - 1]] = 1.0
+    y, y_ref = _run_with_bias(shape, w, reqs, 1024)
+    check(f"d={d} keys at minus infinity", y - reqs[0].rows, y_ref - reqs[0].rows, tol=2e-2)
+
+
+def _run_with_bias(shape, w, reqs, capacity):
+    from paper_2509_24381_amd import runner as r
+    stack = r.LayerStack(shape, [w], max_tokens=64, max_requests=1, max_pos=capacity, qkv_bias=True)
+    kv = stack.new_cache(capacity)
+    kv.import_(0, r.to_device_bf16(reqs[0].prior_k), r.to_device_bf16(reqs[0].prior_v))
+    y = r.to_numpy_f32(stack.prefill_batch(0, [kv], [reqs[0].rows.shape[0]], r.to_device_bf16(reqs[0].rows)))
+    return y, oracle_batch(shape, w, reqs)[0]
