@@ -267,6 +267,8 @@ __global__ __launch_bounds__(256, 1) void lm_head_mfma_kernel(const bf16* __rest
     // (rows past the share, and steps past the last one, fall outside the buffer: they read as zeros and move no data)
     const __amdgpu_buffer_rsrc_t rw =
         __builtin_amdgcn_make_buffer_rsrc((void*)(w + (size_t)row0 * H), 0, (int)((uint32_t)n_rows * (uint32_t)H * 2u), 0x00020000);
+    const uint32_t group_bytes = (uint32_t)(H >> 4) * 1024u;
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)hb, 0, (int)(NG * group_bytes), 0x00020000);
     constexpr uint32_t DEAD = 0x80000000u;
     // load instruction i fills rows [8 i, 8 i + 8) of the slot; 16-byte chunk c of row r sits at place c ^ ((r >> 1) & 7)
     const uint32_t row_bytes = (uint32_t)H * 2u;
@@ -284,10 +286,13 @@ __global__ __launch_bounds__(256, 1) void lm_head_mfma_kernel(const bf16* __rest
         constexpr int slot = decltype(slotc)::value;
         const bool live = l_tile < tiles && l_s < ns;
         const int kg = kg0 + (l_s < ns ? l_s : 0);
+        // (steps past the last one read zeros here too: an infinite value times a zero weight would be NaN)
+        const uint32_t boff = l_s < ns ? (uint32_t)lane * 16u + (uint32_t)kg * 4096u : DEAD;
 #pragma unroll
         for (int g = 0; g < NG; ++g)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[slot][g][j] = *reinterpret_cast<const bf16x8*>(hb + ((size_t)g * (H >> 4) + kg * 4 + j) * 512 + lane * 8);
+            for (int j = 0; j < 4; ++j)
+                b[slot][g][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, boff + (uint32_t)j * 1024u, (int)((uint32_t)g * group_bytes), 0));
         const uint32_t off = live ? (uint32_t)(l_tile * LM_VROWS) * row_bytes + (uint32_t)kg * 128u : DEAD;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
@@ -376,21 +381,10 @@ __global__ __launch_bounds__(256, 1) void lm_head_mfma_kernel(const bf16* __rest
                         piece[s] = (red[0][at] + red[1][at]) + (red[2][at] + red[3][at]);
                     }
                     if (v < n_rows) {
-                        float out = piece[0] + (piece[1] + piece[2]);
-                        if (__builtin_expect(!(fabsf(out) <= 3.402823466e38f), 0)) {
-                            // not finite: a weight may be infinite, and inf times the pieces is not inf times h (0 * inf,
-                            // inf - inf).  Once more in plain fp32, unless the whole row is NaN
-                            const bf16* hg = hb + (size_t)g * (H >> 4) * 512;
-                            const bf16* wv = w + (size_t)(row0 + v) * H;
-                            if (bf16_to_f32(hg[r * 8]) == bf16_to_f32(hg[r * 8])) {
-                                out = 0.0f;
-                                for (int k = 0; k < H; ++k) {
-                                    const bf16* pk = hg + (size_t)(k >> 4) * 512 + ((k >> 3) & 1) * 256 + (k & 7);
-                                    out += (bf16_to_f32(pk[r * 8]) + (bf16_to_f32(pk[(LM_GROUP + r) * 8]) + bf16_to_f32(pk[(2 * LM_GROUP + r) * 8]))) *
-                                           bf16_to_f32(wv[k]);
-                                }
-                            }
-                        }
+                        // An infinite or NaN weight or value makes the sum of the first pieces infinite or NaN as it makes the
+                        // row's own (they carry the values' signs, and a value of the row is zero where they are); of the other
+                        // two it makes anything (0 * inf, inf - inf), so then they do not count
+                        const float out = fabsf(piece[0]) <= 3.402823466e38f ? piece[0] + (piece[1] + piece[2]) : piece[0];
                         logits[(size_t)(g * LM_GROUP + r) * vocab + row0 + v] = out;
                     }
                 }

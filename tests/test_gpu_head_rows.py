@@ -1,7 +1,7 @@
 """GPU: the first-token head's matrix path (3 rows and more) at the edges of its groups, shares and K ranges, against the
 oracle, and where it must hand over to plain fp32 arithmetic.
 
-Both kernels keep the rows' fp32 values exactly and sum in fp32: the error against 64 bits is 1.0e-7 to 1.5e-7 measured on
+Both kernels keep the rows' values to fp32 or better and sum in fp32: the error against 64 bits is 1.0e-7 to 1.5e-7 measured on
 3584 and 8192 features (2-norm); 1e-6 leaves a margin for small vocabularies.
 """
 import ctypes as C
@@ -70,3 +70,45 @@ def test_infinite_weights_and_nan_rows_stay_where_they_are():
     fin = np.delete(np.arange(200), [17, 130])
     want = first_token_logits(x[rows], g, w[fin], shape.rms_eps)
     assert rel_fro(got[np.ix_(rows, fin)], want) <= 1e-6
+
+
+def test_infinite_gains_give_the_logits_of_the_fp32_path():
+    """An infinite gain makes one normalised value infinite, or NaN where x is zero: infinite logits of its sign, NaN beside a zero
+    weight, and what infinite weights make of it - in calls of six rows as in calls of one, which take the fp32 kernel."""
+    runner, ctx, shape, g, w, x = _head(256, 200, 6)
+    g[5] = np.inf
+    x[4, 5] = 0.0
+    w[3, 5] = 0.0
+    w[17, 9], w[130, 200], w[131, 5] = np.inf, -np.inf, -np.inf
+    gd, wd, xd = (runner.to_device_bf16(a) for a in (g, w, x))
+    got = ctx.lm_head(gd, wd, xd).cpu().numpy()
+    for r in range(6):
+        np.testing.assert_array_equal(got[r:r + 1], ctx.lm_head(gd, wd, xd[r:r + 1]).cpu().numpy())   # (nothing is finite)
+    assert np.all(np.isnan(got[4])) and np.all(np.isnan(got[:, 3])) and np.isinf(got[0]).sum() >= 197
+
+
+def test_an_infinite_activation_costs_no_more_than_any_other():
+    """A row of x with an infinity away from feature 0 (its normalised values are zeros and one NaN) gives NaN logits in the
+    time of an ordinary call: nothing is worked out again logit by logit.  (Factor 3 between medians of five: walking every
+    logit's row once more took well over ten times the call.)"""
+    runner, ctx, shape, g, w, x = _head(3584, 16000, 6)
+    bad = x.copy()
+    bad[2, 1000] = np.inf
+    gd, wd, xd, bd = (runner.to_device_bf16(a) for a in (g, w, x, bad))
+
+    def median_ms(rows):
+        ts = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            out = ctx.lm_head(gd, wd, rows)
+            b.record()
+            torch.cuda.synchronize()
+            ts.append(a.elapsed_time(b))
+        return sorted(ts[1:])[2], out
+    t_plain, plain = median_ms(xd)
+    t_bad, out = median_ms(bd)
+    print(f"[head] plain {t_plain * 1e3:.0f} us, with an infinite activation {t_bad * 1e3:.0f} us", flush=True)
+    keep = [0, 1, 3, 4, 5]
+    assert bool(torch.isnan(out[2]).all()) and torch.equal(out[keep], plain[keep])
+    assert t_bad <= 3 * t_plain
