@@ -170,9 +170,10 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const bf16* __restrict__ w
     }
 }
 
-// The same for 3 rows and more, on the matrix pipe.  The fp32 row is cut into three bfloat16 pieces whose sum it is exactly
-// (hi = bf16(h), mid = bf16(h - hi), lo = h - hi - mid: 8 significand bits each, signs included, cover fp32's 24); products
-// of a piece with a bfloat16 weight are exact in fp32.  The pieces of up to 10 rows are the columns of ONE 32-column B
+// The same for 3 rows and more, on the matrix pipe.  A value of the normalised row is the product of u = x / rms
+// (fp32) and the gain; it is cut into three bfloat16 pieces, hi = bf16(u g), mid = bf16(u g - hi), lo = bf16(u g - hi - mid),
+// whose sum is within 2^-26 of it (fp32: 2^-24; below 2^-110 lo runs out of exponents); products of a piece with a bfloat16
+// weight are exact in fp32.  The pieces of up to 10 rows are the columns of ONE 32-column B
 // operand (column 10 s + r = piece s of row r), so the kernel streams the vocabulary once per 10 NG rows and spends one
 // 32x32x16 MFMA per 32 vocabulary rows, 16 k and 10 rows, far below the stream's time.
 //   operand layout: [group of 10 rows][k-step of 16][half][column 32][8 bfloat16]: a wavefront's load is one contiguous KB.
@@ -227,9 +228,11 @@ __global__ __launch_bounds__(256) void final_norm_split_kernel(const bf16* __res
         bf16x8 hi, mid, lo;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float h = bf16_to_f32(v[e]) * inv * bf16_to_f32(g[e]);
-            hi[e] = f32_to_bf16(h);
-            const float r1 = h - bf16_to_f32(hi[e]);
+            constexpr float BF16_MAX = 3.38953139e38f;
+            const float u = bf16_to_f32(v[e]) * inv, gain_e = bf16_to_f32(g[e]), h = u * gain_e;
+            // (the largest finite values would round to an infinite bfloat16)
+            hi[e] = f32_to_bf16(fabsf(h) <= 3.402823466e38f ? fminf(fmaxf(h, -BF16_MAX), BF16_MAX) : h);
+            const float r1 = __builtin_fmaf(u, gain_e, -bf16_to_f32(hi[e]));   // (of the product, not of its fp32 rounding)
             mid[e] = f32_to_bf16(r1);
             lo[e] = f32_to_bf16(r1 - bf16_to_f32(mid[e]));
         }

@@ -72,6 +72,43 @@ def test_infinite_weights_and_nan_rows_stay_where_they_are():
     assert rel_fro(got[np.ix_(rows, fin)], want) <= 1e-6
 
 
+def _call_with_workspace(ctx, g, w, x):
+    """Logits and the bytes the call left in its workspace."""
+    n, vocab = int(x.shape[0]), int(w.shape[0])
+    out = torch.empty((n, vocab), dtype=torch.float32, device="cuda")
+    ws = torch.zeros(ctx.lib.rs_lm_head_workspace_bytes(ctx.handle, n), dtype=torch.uint8, device="cuda")
+    assert ctx.lib.rs_lm_head(ctx.handle, g.data_ptr(), w.data_ptr(), vocab, x.data_ptr(), n, out.data_ptr(), ws.data_ptr(),
+                              C.c_size_t(ws.numel()), torch.cuda.current_stream().cuda_stream or None) == 0
+    return out.cpu().numpy(), ws
+
+
+@pytest.mark.parametrize("hidden", [64, 3584])
+def test_the_three_pieces_sum_to_the_normalised_value(hidden):
+    """What the matrix path leaves in its workspace - three bfloat16 pieces per normalised value, columns 10 s + r of a group
+    of 10 rows - sums to u g within 2^-26, u = x / rms being the fp32 row that a call of one row with gains of one leaves
+    there.  (hi is within 2^-9 of the product, mid within 2^-9 of the difference and lo within 2^-9 of the next: 2^-27.)  One
+    gain is the largest bfloat16 number: its product rounds to an infinite bfloat16 where the fp32 value is still finite."""
+    runner, ctx, shape, g, w, x = _head(hidden, 64, 13)
+    g[7] = synth.bf16_round(np.array([3.3895314e38], dtype=np.float32))[0]
+    x[:, 7] = 1.0     # h = g / rms(x), finite where the rms is not below 1
+    x[0] = np.where(np.arange(hidden) % 2 == 0, 1.0, -1.0)
+    x[0, np.arange(hidden) % 4 != 3] *= 0.99609375     # an rms of 0.997: h lies between the two largest values
+    gd, wd, xd, ones = (runner.to_device_bf16(a) for a in (g, w, x, np.ones_like(g)))
+    _, ws = _call_with_workspace(ctx, gd, wd, xd)
+    pieces = ws[: 2 * (hidden // 16) * 512 * 2].view(torch.bfloat16).double().cpu().numpy()
+    pieces = pieces.reshape(2, hidden // 16, 2, 32, 8).transpose(0, 3, 1, 2, 4).reshape(2, 32, hidden)
+    edge = 0
+    for r in range(13):
+        _, ws1 = _call_with_workspace(ctx, ones, wd, xd[r:r + 1])
+        with np.errstate(over='ignore'):
+            want = ws1[: hidden * 4].view(torch.float32).double().cpu().numpy() * g.astype(np.float64)
+        keep = np.abs(want) <= np.finfo(np.float32).max
+        edge += int(np.sum(keep & (np.abs(want) > 3.3961e38)))
+        got = sum(pieces[r // 10, 10 * s + r % 10] for s in range(3))
+        assert np.all(np.abs(got - want)[keep] <= 2.0 ** -26 * np.abs(want)[keep])
+    assert edge > 0, "no value between the largest bfloat16 and the largest fp32 number"
+
+
 def test_infinite_gains_give_the_logits_of_the_fp32_path():
     """An infinite gain makes one normalised value infinite, or NaN where x is zero: infinite logits of its sign, NaN beside a zero
     weight, and what infinite weights make of it - in calls of six rows as in calls of one, which take the fp32 kernel."""
