@@ -22,6 +22,7 @@
 #pragma once
 #include <type_traits>
 
+#include "attention_plan.h"
 #include "common.h"
 
 struct ReqDesc {
@@ -89,32 +90,14 @@ RS_DEVICE KVHeadTiles kv_head_tiles(const ReqDesc& rq, int kvh) {
     return t;
 }
 
-// Wavefronts per workgroup, 32 stacked query rows each.  Eight (two per SIMD) are faster when they fill the chip; calls too
-// small for that, even with every key range cut as finely as it may be, run four: twice the workgroups, and a wavefront
-// that has its SIMD to itself (attention step with eight and with four, 64 rows on 2048 cached tokens, 7B shape: 24.4 and
-// 20.5 us; tiny shape, 128 rows on 384: 14.0 and 11.4).
-constexpr int ATT_WAVES = 8, ATT_WAVES_SMALL = 4;
-constexpr int ATT_KEYS = 64;   // keys per tile
-
-struct AttnItem {
-    int req;
-    int kvh;
-    int qblock;  // block of 32 WAVES stacked query rows
-    int nkb;     // number of 64-key tiles this block must visit (tiles [0, nkb), or [kb0, nkb) for a part of a split block)
-    int kb0;     // first tile of this part (0 unless the block's key range is split)
-    int slot;    // -1: the workgroup finishes the block and writes the output; >= 0: it leaves an unnormalised partial
-                 // result in this slot of the split buffer (see AttnPartial) for attn_merge_kernel
-    int pad0_, pad1_;
-};
-
 // Split key ranges.  With few query rows and a long cache there are fewer blocks than compute units (a 256-token chunk
 // at the 7B shape gives 28), each walking the whole cache, and requests of one call may have caches of very different
-// lengths.  The host then cuts blocks' tiles into up to ATT_MAX_PARTS consecutive parts (plan_attention), one workgroup each; a part leaves  O~ = sum_k 2^((s_k - m) c) v_k  (fp32, unnormalised), its reference maximum m
+// lengths.  The host then cuts blocks' tiles into up to ATT_MAX_PARTS consecutive parts (attention_plan.h), one workgroup
+// each; a part leaves  O~ = sum_k 2^((s_k - m) c) v_k  (fp32, unnormalised), its reference maximum m
 // and its row sums l in a slot of the split buffer, and attn_merge_kernel combines the parts of a block:
 //   M = max_p m_p,  w_p = 2^((m_p - M) c),  out = sum_p w_p O~_p / sum_p w_p l_p.
 // A slot holds the block's rows: O~ as [D/4 chunks of 4 floats][rows] (the 32 lanes of a store cover 512 contiguous bytes),
 // then m, then l.
-constexpr int ATT_MAX_PARTS = 16;
 template <int D>
 struct AttnPartial {
     static constexpr int CHUNKS = D / 4;
@@ -484,14 +467,6 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_prefill_pipelined_kernel(c
 // chunks, so all of a thread's loads are in flight together (one workgroup per block walking all its chunks one after the
 // other took 13 us, more than a short key range saves).  Every workgroup computes the rows' weights.
 constexpr int ATT_MERGE_Y = 16;
-struct AttnMergeItem {
-    int req;
-    int kvh;
-    int qblock;
-    int n_parts;
-    int slot0;  // the parts' slots are slot0 .. slot0 + n_parts - 1
-    int pad0_, pad1_, pad2_;
-};
 template <int D, int WAVES>
 __global__ __launch_bounds__(32 * WAVES) void attn_merge_kernel(const ReqDesc* __restrict__ reqs, const AttnMergeItem* __restrict__ items,
                                                          const float* __restrict__ split_buf, bf16* __restrict__ out, int ld_out,

@@ -1,0 +1,236 @@
+// Host side of the attention launch: which work items a call's queries and caches become, in which order.  No device code
+// (a test compiles this file on its own).
+#pragma once
+#include <algorithm>
+#include <utility>
+#include <vector>
+
+// Wavefronts per workgroup, 32 stacked query rows each.  Eight (two per SIMD) share each K / V tile, which halves the DMA into
+// LDS; four leave twice the blocks (see plan_attention for when).
+constexpr int ATT_WAVES = 8, ATT_WAVES_SMALL = 4;
+constexpr int ATT_KEYS = 64;   // keys per tile
+constexpr int ATT_MAX_PARTS = 16;
+constexpr int ATT_SPLIT_SLOTS = 384;       // slots of the split buffer (a block that finds no free slots stays whole)
+constexpr int ATT_MIN_PART_TILES = 6;      // a part is worth a workgroup and its share of the merge from about 400 keys; every row of a
+                                           // block must see keys of each part: its rows span at most 256 positions, 5 tiles
+constexpr int ATT_MIN_SPLIT_TILES = 16;    // no block of the call is split unless the longest walks at least 1024 keys
+
+struct AttnItem {
+    int req;
+    int kvh;
+    int qblock;  // block of 32 WAVES stacked query rows
+    int nkb;     // number of 64-key tiles this block must visit (tiles [0, nkb), or [kb0, nkb) for a part of a split block)
+    int kb0;     // first tile of this part (0 unless the block's key range is split)
+    int slot;    // -1: the workgroup finishes the block and writes the output; >= 0: it leaves an unnormalised partial
+                 // result in this slot of the split buffer (see AttnPartial) for attn_merge_kernel
+    int pad0_, pad1_;
+};
+struct AttnMergeItem {
+    int req;
+    int kvh;
+    int qblock;
+    int n_parts;
+    int slot0;  // the parts' slots are slot0 .. slot0 + n_parts - 1
+    int pad0_, pad1_, pad2_;
+};
+
+struct AttnRequest {
+    int T, P;   // rows of the call, tokens cached before it
+    bool operator==(const AttnRequest& o) const { return T == o.T && P == o.P; }
+};
+struct AttnPlanSettings {
+    int n_cu;           // compute units
+    int split;          // RS_ATTN_SPLIT: 0 decided here, 1 nothing is cut, n > 1 parts of every block
+};
+struct AttnPlan {
+    int waves = ATT_WAVES;
+    int cost = 0;   // estimated duration, in tiles (0: nothing was weighed)
+    std::vector<AttnItem> items;
+    std::vector<AttnMergeItem> merges;
+};
+
+// Where a block of n tiles is cut: in equal parts of at most `cap` tiles, in parts of exactly `cap` and a rest (!even), or (cap 0)
+// not at all.
+struct AttnCut {
+    int cap = 0;
+    bool even = true;
+    int parts = 0;   // > 0: this many parts (RS_ATTN_SPLIT)
+    // number of parts (1: whole) and the tiles of every part but the last (0: equal parts)
+    std::pair<int, int> of(int n) const {
+        int p = 1, step = 0;
+        if (parts > 0) {
+            p = std::min(parts, n / ATT_MIN_PART_TILES);
+        } else if (cap > 0 && even) {
+            p = std::min(std::min((n + cap - 1) / cap, n / ATT_MIN_PART_TILES), ATT_MAX_PARTS);
+        } else if (cap > 0) {
+            const int full = n / cap, rest = n - full * cap;
+            p = rest < ATT_MIN_PART_TILES ? full : full + 1;
+            step = rest < ATT_MIN_PART_TILES ? 0 : cap;
+        }
+        return p < 2 || p > ATT_MAX_PARTS ? std::make_pair(1, 0) : std::make_pair(p, step);
+    }
+};
+
+// The blocks under a cut, in their order: whole(block) or part(block, index, of, first tile, end tile, slot).
+template <class Whole, class Part>
+void attn_walk_parts(const std::vector<AttnItem>& blocks, const AttnCut& cut, Whole&& whole, Part&& part) {
+    int slots = 0;
+    for (const AttnItem& b : blocks) {
+        const auto [p, step] = cut.of(b.nkb);
+        if (p < 2 || slots + p > ATT_SPLIT_SLOTS) {
+            whole(b);
+            continue;
+        }
+        for (int i = 0; i < p; ++i)
+            part(b, i, p, step ? i * step : (int)((long)i * b.nkb / p), step ? std::min((i + 1) * step, b.nkb) : (int)((long)(i + 1) * b.nkb / p),
+                 slots + i);
+        slots += p;
+    }
+}
+
+// Heaviest first, equals in their order.
+inline void attn_sort_items(std::vector<AttnItem>& items) {
+    int longest = 0;
+    for (const AttnItem& it : items) longest = std::max(longest, it.nkb - it.kb0);
+    std::vector<int> at(longest + 2, 0);
+    for (const AttnItem& it : items) ++at[it.nkb - it.kb0];
+    for (int n = longest, first = 0; n >= 0; --n) {
+        const int count = at[n];
+        at[n] = first;
+        first += count;
+    }
+    std::vector<AttnItem> sorted(items.size());
+    for (const AttnItem& it : items) sorted[at[it.nkb - it.kb0]++] = it;
+    items.swap(sorted);
+}
+
+// End of a launch in which items of the given costs (longest first) are handed to n_cu compute units as these fall free.
+inline int attn_makespan(const std::vector<int>& costs, int n_cu) {
+    if (costs.empty()) return 0;
+    if ((int)costs.size() <= n_cu) return costs[0];
+    long sum = 0;
+    for (int c : costs) sum += c;
+    std::vector<int> units((size_t)(sum / n_cu) + costs[0] + 2, 0);   // compute units by load; the least load only grows
+    units[0] = n_cu;
+    int least = 0, end = 0;
+    for (int c : costs) {
+        while (units[least] == 0) ++least;
+        --units[least];
+        ++units[least + c];
+        end = std::max(end, least + c);
+    }
+    return end;
+}
+
+// The estimates are in units of one key tile's time on a full chip (1.6 to 1.8 us at d = 128); the constants are fitted to kernel
+// traces (the merge 6 us, and 14 us for 392 parts; a part's partial result 133 KB at d = 128).
+constexpr int ATT_COST_ITEM = 2, ATT_COST_PART = 4, ATT_COST_MERGE = 4, ATT_COST_MERGE_PARTS = 36;   // per whole item, part, merge; parts per further one
+
+// Estimated duration of a launch of these blocks (heaviest first, one to a compute unit at a time) under a cut.
+inline int attn_cost(const std::vector<AttnItem>& blocks, const AttnCut& cut, int n_cu) {
+    std::vector<int> costs;
+    costs.reserve(blocks.size() + ATT_SPLIT_SLOTS);
+    int slots = 0;
+    bool sorted = true;
+    const auto add = [&](int c) {
+        sorted = sorted && (costs.empty() || costs.back() >= c);
+        costs.push_back(c);
+    };
+    attn_walk_parts(blocks, cut, [&](const AttnItem& b) { add(b.nkb + ATT_COST_ITEM); },
+                    [&](const AttnItem&, int, int, int first, int end, int) {
+                        add(end - first + ATT_COST_PART);
+                        ++slots;
+                    });
+    if (!sorted) std::sort(costs.begin(), costs.end(), [](int a, int b) { return a > b; });
+    return attn_makespan(costs, n_cu) + (slots ? ATT_COST_MERGE + slots / ATT_COST_MERGE_PARTS : 0);
+}
+
+// A call's blocks of 32 `waves` stacked rows, heaviest first, whole key ranges.
+inline std::vector<AttnItem> attn_blocks(const std::vector<AttnRequest>& reqs, int group, int kv_heads, int waves) {
+    std::vector<AttnItem> blocks;
+    const int rows = 32 * waves;
+    for (int r = 0; r < (int)reqs.size(); ++r) {
+        const int n = (int)(((long)reqs[r].T * group + rows - 1) / rows);
+        for (int qb = 0; qb < n; ++qb) {
+            const int t_max = std::min(reqs[r].T - 1, (qb * rows + rows - 1) / group);   // the block's last token
+            const int nkb = (reqs[r].P + t_max + 1 + ATT_KEYS - 1) / ATT_KEYS;
+            for (int c = 0; c < kv_heads; ++c) blocks.push_back(AttnItem{r, c, qb, nkb, 0, -1, 0, 0});
+        }
+    }
+    attn_sort_items(blocks);
+    return blocks;
+}
+
+// The call's work items.  One workgroup of eight wavefronts fills a compute unit, so a launch lasts as long as the fullest unit:
+// key ranges are cut where that ends the launch sooner, and the parts of a cut block are combined by attn_merge_kernel.
+// Measured at the 7B shape, attention step, nothing cut -> planned: 16 requests, 2048 rows, caches of 0 to 12288 tokens 256 -> 178
+// us; 1000 rows on 12000 tokens 181 -> 161; 250 on 8192: 69 -> 48; 64 on 2048: 28 -> 24; 2048 on 6144: 210 -> 200 (97 to 128 tiles
+// per block, at most 105 per unit after: the board's power limit gives back little of a better balance).  4096 rows on 28672 (1024
+// blocks) stay whole.
+// Calls too small to fill the chip even with every key range cut as finely as it may be take blocks of four wavefronts: twice the
+// workgroups, and a wavefront that has its SIMD to itself (attention step with eight and with four, 64 rows on 2048 cached tokens,
+// 7B shape: 24.4 and 20.5 us; tiny shape, 128 rows on 384: 14.0 and 11.4).
+inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<AttnRequest>& reqs, int group, int kv_heads) {
+    AttnPlan plan;
+    long most = 0;   // parts the small blocks could be cut into
+    for (const AttnRequest& r : reqs) {
+        const long blocks = ((long)r.T * group + 32 * ATT_WAVES_SMALL - 1) / (32 * ATT_WAVES_SMALL) * kv_heads;
+        const long tiles = ((long)r.P + r.T + ATT_KEYS - 1) / ATT_KEYS;
+        most += blocks * (tiles < ATT_MIN_SPLIT_TILES ? 1 : std::min<long>(tiles / ATT_MIN_PART_TILES, ATT_MAX_PARTS));
+    }
+    if (most <= s.n_cu) plan.waves = ATT_WAVES_SMALL;
+    const std::vector<AttnItem> blocks = attn_blocks(reqs, group, kv_heads, plan.waves);
+    if (blocks.empty()) return plan;
+
+    AttnCut cut;
+    const int longest = blocks[0].nkb, n = (int)blocks.size();
+    if (s.split > 1) {
+        cut.parts = s.split;
+    } else if (s.split == 0 && longest >= ATT_MIN_SPLIT_TILES) {
+        plan.cost = attn_cost(blocks, cut, s.n_cu);
+        const auto consider = [&](AttnCut c) {
+            const int cost = attn_cost(blocks, c, s.n_cu);
+            if (cost < plan.cost) {
+                plan.cost = cost;
+                cut = c;
+            }
+        };
+        // (1) equal parts, as long as every part has a compute unit of its own: the smallest cap with at most n_cu parts
+        if (n < s.n_cu) {
+            AttnCut c;
+            int lo = ATT_MIN_PART_TILES, hi = longest;
+            while (lo < hi) {
+                c.cap = (lo + hi) / 2;
+                long parts = 0;
+                for (int i = 0; i < n;) {   // (blocks of equal length are neighbours)
+                    int j = i;
+                    while (j < n && blocks[j].nkb == blocks[i].nkb) ++j;
+                    parts += (long)(j - i) * c.of(blocks[i].nkb).first;
+                    i = j;
+                }
+                if (parts <= s.n_cu) hi = c.cap; else lo = c.cap + 1;
+            }
+            c.cap = lo;
+            consider(c);
+        }
+        // (2) an even share for every compute unit: blocks longer than the share are cut there, the rests fill the gaps
+        long work = 0;
+        for (const AttnItem& b : blocks) work += b.nkb;
+        AttnCut c;
+        c.even = false;
+        c.cap = (int)((work + (long)n * ATT_COST_PART) * 102 / 100 / s.n_cu) + 1;
+        if (c.cap >= ATT_MIN_PART_TILES && c.cap + ATT_MIN_PART_TILES <= longest) consider(c);
+    }
+    plan.items.reserve(blocks.size() + ATT_SPLIT_SLOTS);
+    attn_walk_parts(blocks, cut, [&](const AttnItem& b) { plan.items.push_back(b); },
+                    [&](const AttnItem& b, int i, int of, int first, int end, int slot) {
+                        if (i == 0) plan.merges.push_back(AttnMergeItem{b.req, b.kvh, b.qblock, of, slot, 0, 0, 0});
+                        AttnItem part = b;
+                        part.kb0 = first;
+                        part.nkb = end;
+                        part.slot = slot;
+                        plan.items.push_back(part);
+                    });
+    if (!plan.merges.empty()) attn_sort_items(plan.items);
+    return plan;
+}

@@ -189,16 +189,10 @@ struct DescSizes {
     size_t reqs, items, vblocks, rowpos, pagetab, mitems, fp8, total;
 };
 
-constexpr int ATT_MIN_PART_TILES = 6;      // a part is worth a workgroup and its share of the merge from about 400 keys; every row of a
-                                           // block must see keys of each part: its rows span at most 256 positions, 5 tiles
-constexpr int ATT_MIN_SPLIT_TILES = 16;    // no block of the call is split unless the longest walks at least 1024 keys
-// slots of the split buffer (a block that finds no free slots stays whole)
-size_t attn_split_slots(const rs_ctx*) { return 384; }
-
 DescSizes desc_sizes(const rs_ctx* c, int max_tokens, int max_requests) {
     DescSizes d;
     const size_t n_items = ((size_t)(max_tokens * (size_t)c->group + 32 * ATT_WAVES_SMALL - 1) / (32 * ATT_WAVES_SMALL) + max_requests) * c->cfg.n_kv_heads +
-                           attn_split_slots(c);
+                           ATT_SPLIT_SLOTS;
     const size_t n_vb = (size_t)max_tokens / 64 + 2 * (size_t)max_requests + 1;
     d.reqs = align_up(sizeof(ReqDesc) * std::max(max_requests, 1), 256);
     d.items = align_up(sizeof(AttnItem) * n_items, 256);
@@ -206,7 +200,7 @@ DescSizes desc_sizes(const rs_ctx* c, int max_tokens, int max_requests) {
     d.rowpos = align_up(3 * sizeof(int) * (size_t)std::max(max_tokens, 1), 256);  // (temporal, height, width) per row
     // block -> page numbers of the paged caches in the call: at most max_pos / 64 + 1 blocks per request
     d.pagetab = align_up(sizeof(int) * (size_t)std::max(max_requests, 1) * ((size_t)c->cfg.max_pos / 64 + 2), 256);
-    d.mitems = align_up(sizeof(AttnMergeItem) * attn_split_slots(c), 256);
+    d.mitems = align_up(sizeof(AttnMergeItem) * ATT_SPLIT_SLOTS, 256);
     d.fp8 = align_up(sizeof(Fp8CacheDesc) * std::max(max_requests, 1), 256);
     d.total = d.reqs + d.items + d.vblocks + d.rowpos + d.pagetab + d.mitems + d.fp8;
     return d;
@@ -285,134 +279,13 @@ WorkspaceLayout ws_layout(const rs_ctx* c, int T, int R) {
     w.r = take(tp * f.hidden * 2);
     w.act = take(tp * f.mlp_inter * 2);
     w.partial = take(4 * t * f.hidden * 4);  // up to 4 split-K partial planes of [T, H] fp32
-    w.attn_split = take(attn_split_slots(c) * (size_t)(32 * ATT_WAVES) * (f.head_dim + 2) * 4);  // partial results of split key ranges
+    w.attn_split = take((size_t)ATT_SPLIT_SLOTS * (32 * ATT_WAVES) * (f.head_dim + 2) * 4);  // partial results of split key ranges
     w.inv_rms1 = take(tp * 4);
     w.inv_rms2 = take(tp * 4);
     w.rowss = take(tp * (f.hidden / 32) * 4);
     w.desc = take(desc_sizes(c, T, R).total);
     w.total = off;
     return w;
-}
-
-// Estimated end of a launch in which `lens` (longest first) are handed to n_cu compute units as these fall free.
-int attn_makespan(const std::vector<int>& lens, int n_cu, int per_item) {
-    if ((int)lens.size() <= n_cu) return lens.empty() ? 0 : lens[0] + per_item;
-    std::vector<int> heap(n_cu, 0);   // min-heap of the units' loads
-    const auto later = [](int a, int b) { return a > b; };
-    int end = 0;
-    for (int n : lens) {
-        std::pop_heap(heap.begin(), heap.end(), later);
-        heap.back() += n + per_item;
-        end = std::max(end, heap.back());
-        std::push_heap(heap.begin(), heap.end(), later);
-    }
-    return end;
-}
-
-// Turns the call's attention blocks (whole key ranges) into the launch's work items, heaviest first, cutting key ranges
-// where that ends the launch sooner; the parts of a cut block are combined by attn_merge_kernel.  One workgroup fills a
-// compute unit, so a launch lasts as long as the fullest unit.  The estimates are in units of one key tile's time (1.6 to
-// 1.8 us on a full chip); the constants are fitted to kernel traces (the merge 6 us, and 14 us for 392 parts; a part's
-// partial result 133 KB at d = 128).  Measured at the 7B shape, attention step, nothing cut -> planned: 16 requests, 2048
-// rows, caches of 0 to 12288 tokens 256 -> 178 us; 1000 rows on 12000 tokens 181 -> 161; 250 on 8192: 69 -> 48; 64 on 2048:
-// 28 -> 24; 2048 on 6144: 210 -> 200 (97 to 128 tiles per block, at most 105 per unit after: the board's power limit gives
-// back little of a better balance).  4096 rows on 28672 (1024 blocks) stay whole.
-void plan_attention(const rs_ctx* c, std::vector<AttnItem>& items, std::vector<AttnMergeItem>& mitems) {
-    if (items.empty()) return;
-    std::stable_sort(items.begin(), items.end(), [](const AttnItem& a, const AttnItem& b) { return a.nkb > b.nkb; });
-    constexpr int ITEM = 2, PART = 4, MERGE = 4, MERGE_PARTS = 36;   // tile times: per whole item, per part, per merge, parts per further one
-    const int longest = items[0].nkb, blocks = (int)items.size();
-    const int slot_cap = (int)attn_split_slots(c);
-    // parts of a block of n tiles when none may exceed `cap`
-    const auto parts_of = [&](int n, int cap) { return std::min(std::min((n + cap - 1) / cap, n / ATT_MIN_PART_TILES), ATT_MAX_PARTS); };
-    int cap = 0;          // 0: nothing is cut
-    bool even = true;     // equal parts, or parts of `cap` tiles and a rest
-    if (c->attn_split > 1) {
-        cap = 1;          // (test hook: handled below)
-    } else if (c->attn_split == 0 && longest >= ATT_MIN_SPLIT_TILES) {
-        std::vector<int> lens(blocks);
-        long work = 0;
-        for (int i = 0; i < blocks; ++i) work += lens[i] = items[i].nkb;
-        int best = attn_makespan(lens, c->n_cu, ITEM);
-        // (1) equal parts, as long as every part has a compute unit of its own
-        if (blocks < c->n_cu) {
-            int lo = ATT_MIN_PART_TILES, hi = longest;   // smallest cap with at most n_cu parts
-            while (lo < hi) {
-                const int mid = (lo + hi) / 2;
-                long n = 0;
-                for (int len : lens) n += std::max(1, parts_of(len, mid));
-                if (n <= c->n_cu) hi = mid; else lo = mid + 1;
-            }
-            int end = 0, slots = 0;
-            for (int len : lens) {
-                const int p = std::max(1, parts_of(len, lo));
-                end = std::max(end, (len + p - 1) / p);
-                if (p > 1) slots += p;
-            }
-            const int cost = end + PART + MERGE + slots / MERGE_PARTS;
-            if (slots > 0 && slots <= slot_cap && cost < best) {
-                best = cost;
-                cap = lo;
-            }
-        }
-        // (2) an even share for every compute unit: blocks longer than the share are cut there, the rests fill the gaps
-        const int share = (int)((work + (long)blocks * PART) * 102 / 100 / c->n_cu) + 1;
-        if (share >= ATT_MIN_PART_TILES && share + ATT_MIN_PART_TILES <= longest) {
-            std::vector<int> cut;
-            int slots = 0;
-            for (int len : lens) {
-                const int full = len / share, rest = len - full * share;
-                if (full == 0 || (full == 1 && rest < ATT_MIN_PART_TILES) || slots + full + 1 > slot_cap || full + 1 > ATT_MAX_PARTS) {
-                    cut.push_back(len);
-                    continue;
-                }
-                if (rest < ATT_MIN_PART_TILES) {
-                    for (int p = 0; p < full; ++p) cut.push_back((len + full - 1) / full + PART - ITEM);
-                    slots += full;
-                } else {
-                    for (int p = 0; p < full; ++p) cut.push_back(share + PART - ITEM);
-                    cut.push_back(rest + PART - ITEM);
-                    slots += full + 1;
-                }
-            }
-            std::sort(cut.begin(), cut.end(), [](int a, int b) { return a > b; });
-            const int cost = attn_makespan(cut, c->n_cu, ITEM) + MERGE + slots / MERGE_PARTS;
-            if (slots > 0 && cost < best) {
-                best = cost;
-                cap = share;
-                even = false;
-            }
-        }
-    }
-    if (cap > 0) {
-        std::vector<AttnItem> cut;
-        int slots = 0;
-        for (const AttnItem& it : items) {
-            int parts = c->attn_split > 1 ? std::min(c->attn_split, it.nkb / ATT_MIN_PART_TILES) : parts_of(it.nkb, cap);
-            int step = 0;   // tiles of every part but the last (0: equal parts)
-            if (!even) {
-                const int full = it.nkb / cap, rest = it.nkb - full * cap;
-                parts = rest < ATT_MIN_PART_TILES ? full : full + 1;
-                step = rest < ATT_MIN_PART_TILES ? 0 : cap;
-                if (parts > ATT_MAX_PARTS) parts = 1;
-            }
-            if (parts < 2 || slots + parts > slot_cap) {
-                cut.push_back(it);
-                continue;
-            }
-            mitems.push_back(AttnMergeItem{it.req, it.kvh, it.qblock, parts, slots, 0, 0, 0});
-            for (int p = 0; p < parts; ++p) {
-                AttnItem part = it;
-                part.kb0 = step ? p * step : (int)((long)p * it.nkb / parts);
-                part.nkb = step ? std::min((p + 1) * step, it.nkb) : (int)((long)(p + 1) * it.nkb / parts);
-                part.slot = slots++;
-                cut.push_back(part);
-            }
-        }
-        items.swap(cut);
-        std::stable_sort(items.begin(), items.end(),
-                         [](const AttnItem& a, const AttnItem& b) { return a.nkb - a.kb0 > b.nkb - b.kb0; });
-    }
 }
 
 // bytes of the bfloat16 copy of an 8-bit cache's first n_tokens (whole 64-token blocks, K and V^T of all KV heads)
@@ -821,7 +694,6 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
 
     // ---- host descriptors
     std::vector<ReqDesc> reqs;
-    std::vector<AttnItem> items;
     std::vector<KVBlockItem> vbs;
     std::vector<int> rowpos;
     std::vector<int> pagetab;
@@ -832,18 +704,7 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     const DescSizes ds = desc_sizes(ctx, T, R);
     char* wsb = reinterpret_cast<char*>(ws);
     const int* d_pagetab = reinterpret_cast<const int*>(wsb + L.desc + ds.reqs + ds.items + ds.vblocks + ds.rowpos);
-    const int g = ctx->group;
-    int att_waves = ATT_WAVES;
-    {   // (see ATT_WAVES; the most parts the small blocks could be cut into)
-        long most = 0;
-        for (int i = 0; i < R; ++i) {
-            const long blocks = ((long)lens[i] * g + 32 * ATT_WAVES_SMALL - 1) / (32 * ATT_WAVES_SMALL) * f.n_kv_heads;
-            const long tiles = ((long)kvs[i]->len[layer] + lens[i] + ATT_KEYS - 1) / ATT_KEYS;
-            most += blocks * (tiles < ATT_MIN_SPLIT_TILES ? 1 : std::min<long>(tiles / ATT_MIN_PART_TILES, ATT_MAX_PARTS));
-        }
-        if (most <= ctx->n_cu) att_waves = ATT_WAVES_SMALL;
-    }
-    const int att_rows = 32 * att_waves;
+    std::vector<AttnRequest> att_reqs;
     int row0 = 0;
     for (int i = 0; i < R; ++i) {
         const int Ti = lens[i];
@@ -877,19 +738,15 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         if (kv->paged()) pagetab.insert(pagetab.end(), kv->pages[layer].begin(), kv->pages[layer].end());
         const int ri = (int)reqs.size();
         reqs.push_back(d);
-        const int nqb = (Ti * g + att_rows - 1) / att_rows;
-        for (int qb = 0; qb < nqb; ++qb) {
-            const int t_max = std::min(Ti - 1, (qb * att_rows + att_rows - 1) / g);
-            const int nkb = (P + t_max + 1 + ATT_KEYS - 1) / ATT_KEYS;
-            for (int c = 0; c < f.n_kv_heads; ++c) items.push_back(AttnItem{ri, c, qb, nkb, 0, -1, 0, 0});
-        }
+        att_reqs.push_back(AttnRequest{Ti, P});
         for (int b = P / 64; b <= (P + Ti - 1) / 64; ++b) vbs.push_back(KVBlockItem{ri, b});
         for (int t = 0; t < Ti; ++t)
             for (int ax = 0; ax < 3; ++ax) rowpos.push_back(positions3 ? positions3[3 * (size_t)(row0 + t) + ax] : P + t);
         row0 += Ti;
     }
-    std::vector<AttnMergeItem> mitems;
-    plan_attention(ctx, items, mitems);
+    const AttnPlan plan = plan_attention(AttnPlanSettings{ctx->n_cu, ctx->attn_split}, att_reqs, ctx->group, f.n_kv_heads);
+    const std::vector<AttnItem>& items = plan.items;
+    const std::vector<AttnMergeItem>& mitems = plan.merges;
 
     if (sizeof(ReqDesc) * reqs.size() > ds.reqs || sizeof(AttnItem) * items.size() > ds.items ||
         sizeof(KVBlockItem) * vbs.size() > ds.vblocks || sizeof(int) * rowpos.size() > ds.rowpos ||
@@ -997,10 +854,10 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     tm.end(RS_STEP_QKV_GEMM);
     // cache append, attention
     if (f.head_dim == 128)
-        s = launch_attention_path<128>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), att_waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
+        s = launch_attention_path<128>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), plan.waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
                                        attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, st, tm);
     else
-        s = launch_attention_path<64>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), att_waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
+        s = launch_attention_path<64>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), plan.waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
                                       attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, st, tm);
     if (s != RS_OK) return s;
     // r = x + attn Wo^T, and 1/rms of every row of r (the second RMSNorm; its gain lives in the packed W_gate_up)
