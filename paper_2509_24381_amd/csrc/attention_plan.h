@@ -49,6 +49,12 @@ struct AttnPlan {
     std::vector<AttnMergeItem> merges;
 };
 
+// The plan of the layer before, in a call of several layers: good for the next one if its caches have the same lengths.
+struct AttnPlanCache {
+    std::vector<AttnRequest> reqs;   // empty: no plan yet
+    AttnPlan plan;
+};
+
 // Where a block of n tiles is cut: in equal parts of at most `cap` tiles, in parts of exactly `cap` and a rest (!even), or (cap 0)
 // not at all.
 struct AttnCut {
@@ -71,22 +77,14 @@ struct AttnCut {
     }
 };
 
-// The blocks under a cut, in their order: whole(block) or part(block, index, of, first tile, end tile, slot).
-template <class Whole, class Part>
-void attn_walk_parts(const std::vector<AttnItem>& blocks, const AttnCut& cut, Whole&& whole, Part&& part) {
-    int slots = 0;
-    for (const AttnItem& b : blocks) {
-        const auto [p, step] = cut.of(b.nkb);
-        if (p < 2 || slots + p > ATT_SPLIT_SLOTS) {
-            whole(b);
-            continue;
-        }
-        for (int i = 0; i < p; ++i)
-            part(b, i, p, step ? i * step : (int)((long)i * b.nkb / p), step ? std::min((i + 1) * step, b.nkb) : (int)((long)(i + 1) * b.nkb / p),
-                 slots + i);
-        slots += p;
-    }
+// How many of `count` such blocks of n tiles are cut when `slots` of the split buffer are taken: a block that finds no free slots
+// stays whole.
+inline int attn_blocks_cut(const AttnCut& cut, int n, int count, int slots) {
+    const int p = cut.of(n).first;
+    return p < 2 ? 0 : std::min(count, (ATT_SPLIT_SLOTS - slots) / p);
 }
+// End of part i of p of a block of n tiles (`step`: see AttnCut::of).
+inline int attn_part_end(int n, int p, int step, int i) { return step ? std::min((i + 1) * step, n) : (int)((long)(i + 1) * n / p); }
 
 // Heaviest first, equals in their order.
 inline void attn_sort_items(std::vector<AttnItem>& items) {
@@ -104,45 +102,59 @@ inline void attn_sort_items(std::vector<AttnItem>& items) {
     items.swap(sorted);
 }
 
-// End of a launch in which items of the given costs (longest first) are handed to n_cu compute units as these fall free.
-inline int attn_makespan(const std::vector<int>& costs, int n_cu) {
-    if (costs.empty()) return 0;
-    if ((int)costs.size() <= n_cu) return costs[0];
-    long sum = 0;
-    for (int c : costs) sum += c;
-    std::vector<int> units((size_t)(sum / n_cu) + costs[0] + 2, 0);   // compute units by load; the least load only grows
-    units[0] = n_cu;
-    int least = 0, end = 0;
-    for (int c : costs) {
-        while (units[least] == 0) ++least;
-        --units[least];
-        ++units[least + c];
-        end = std::max(end, least + c);
-    }
-    return end;
-}
-
 // The estimates are in units of one key tile's time on a full chip (1.6 to 1.8 us at d = 128); the constants are fitted to kernel
 // traces (the merge 6 us, and 14 us for 392 parts; a part's partial result 133 KB at d = 128).
 constexpr int ATT_COST_ITEM = 2, ATT_COST_PART = 4, ATT_COST_MERGE = 4, ATT_COST_MERGE_PARTS = 36;   // per whole item, part, merge; parts per further one
 
-// Estimated duration of a launch of these blocks (heaviest first, one to a compute unit at a time) under a cut.
-inline int attn_cost(const std::vector<AttnItem>& blocks, const AttnCut& cut, int n_cu) {
-    std::vector<int> costs;
-    costs.reserve(blocks.size() + ATT_SPLIT_SLOTS);
+// Equally long blocks (KV heads and requests repeat lengths: a few dozen groups stand for hundreds of blocks).
+struct AttnGroup {
+    int n, count;   // tiles of a block, blocks
+};
+inline std::vector<AttnGroup> attn_groups(const std::vector<AttnItem>& blocks) {   // (heaviest first)
+    std::vector<AttnGroup> groups;
+    for (const AttnItem& b : blocks) {
+        if (groups.empty() || groups.back().n != b.nkb) groups.push_back(AttnGroup{b.nkb, 0});
+        ++groups.back().count;
+    }
+    return groups;
+}
+
+// Estimated duration of a launch of these blocks under a cut, the items handed out longest first, one to a compute unit at a time
+// and to the next as units fall free.
+inline int attn_cost(const std::vector<AttnGroup>& groups, const AttnCut& cut, int n_cu) {
+    if (groups.empty()) return 0;
+    std::vector<int> items((size_t)groups[0].n + ATT_COST_PART + 1, 0);   // items by cost
     int slots = 0;
-    bool sorted = true;
-    const auto add = [&](int c) {
-        sorted = sorted && (costs.empty() || costs.back() >= c);
-        costs.push_back(c);
+    long sum = 0;
+    const auto add = [&](int cost, int count) {
+        items[cost] += count;
+        sum += (long)cost * count;
     };
-    attn_walk_parts(blocks, cut, [&](const AttnItem& b) { add(b.nkb + ATT_COST_ITEM); },
-                    [&](const AttnItem&, int, int, int first, int end, int) {
-                        add(end - first + ATT_COST_PART);
-                        ++slots;
-                    });
-    if (!sorted) std::sort(costs.begin(), costs.end(), [](int a, int b) { return a > b; });
-    return attn_makespan(costs, n_cu) + (slots ? ATT_COST_MERGE + slots / ATT_COST_MERGE_PARTS : 0);
+    for (const AttnGroup& g : groups) {
+        const auto [p, step] = cut.of(g.n);
+        const int k = attn_blocks_cut(cut, g.n, g.count, slots);
+        if (k < g.count) add(g.n + ATT_COST_ITEM, g.count - k);
+        if (k == 0) continue;
+        for (int i = 0, first = 0; i < p; ++i) {
+            const int end = attn_part_end(g.n, p, step, i);
+            add(end - first + ATT_COST_PART, k);
+            first = end;
+        }
+        slots += k * p;
+    }
+    std::vector<int> units((size_t)(sum / n_cu) + items.size() + 1, 0);   // compute units by load; the least load only grows
+    units[0] = n_cu;
+    int least = 0, end = 0;
+    for (int cost = (int)items.size() - 1; cost > 0; --cost)
+        for (int left = items[cost]; left > 0;) {
+            while (units[least] == 0) ++least;
+            const int k = std::min(left, units[least]);
+            units[least] -= k;
+            units[least + cost] += k;
+            end = std::max(end, least + cost);
+            left -= k;
+        }
+    return end + (slots ? ATT_COST_MERGE + slots / ATT_COST_MERGE_PARTS : 0);
 }
 
 // A call's blocks of 32 `waves` stacked rows, heaviest first, whole key ranges.
@@ -183,13 +195,14 @@ inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<Attn
     if (blocks.empty()) return plan;
 
     AttnCut cut;
+    const std::vector<AttnGroup> groups = attn_groups(blocks);
     const int longest = blocks[0].nkb, n = (int)blocks.size();
     if (s.split > 1) {
         cut.parts = s.split;
     } else if (s.split == 0 && longest >= ATT_MIN_SPLIT_TILES) {
-        plan.cost = attn_cost(blocks, cut, s.n_cu);
+        plan.cost = attn_cost(groups, cut, s.n_cu);
         const auto consider = [&](AttnCut c) {
-            const int cost = attn_cost(blocks, c, s.n_cu);
+            const int cost = attn_cost(groups, c, s.n_cu);
             if (cost < plan.cost) {
                 plan.cost = cost;
                 cut = c;
@@ -202,12 +215,7 @@ inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<Attn
             while (lo < hi) {
                 c.cap = (lo + hi) / 2;
                 long parts = 0;
-                for (int i = 0; i < n;) {   // (blocks of equal length are neighbours)
-                    int j = i;
-                    while (j < n && blocks[j].nkb == blocks[i].nkb) ++j;
-                    parts += (long)(j - i) * c.of(blocks[i].nkb).first;
-                    i = j;
-                }
+                for (const AttnGroup& g : groups) parts += (long)g.count * c.of(g.n).first;
                 if (parts <= s.n_cu) hi = c.cap; else lo = c.cap + 1;
             }
             c.cap = lo;
@@ -215,22 +223,30 @@ inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<Attn
         }
         // (2) an even share for every compute unit: blocks longer than the share are cut there, the rests fill the gaps
         long work = 0;
-        for (const AttnItem& b : blocks) work += b.nkb;
+        for (const AttnGroup& g : groups) work += (long)g.n * g.count;
         AttnCut c;
         c.even = false;
         c.cap = (int)((work + (long)n * ATT_COST_PART) * 102 / 100 / s.n_cu) + 1;
         if (c.cap >= ATT_MIN_PART_TILES && c.cap + ATT_MIN_PART_TILES <= longest) consider(c);
     }
     plan.items.reserve(blocks.size() + ATT_SPLIT_SLOTS);
-    attn_walk_parts(blocks, cut, [&](const AttnItem& b) { plan.items.push_back(b); },
-                    [&](const AttnItem& b, int i, int of, int first, int end, int slot) {
-                        if (i == 0) plan.merges.push_back(AttnMergeItem{b.req, b.kvh, b.qblock, of, slot, 0, 0, 0});
-                        AttnItem part = b;
-                        part.kb0 = first;
-                        part.nkb = end;
-                        part.slot = slot;
-                        plan.items.push_back(part);
-                    });
+    int slots = 0;
+    for (const AttnItem& b : blocks) {
+        if (attn_blocks_cut(cut, b.nkb, 1, slots) == 0) {
+            plan.items.push_back(b);
+            continue;
+        }
+        const auto [p, step] = cut.of(b.nkb);
+        plan.merges.push_back(AttnMergeItem{b.req, b.kvh, b.qblock, p, slots, 0, 0, 0});
+        AttnItem part = b;
+        part.nkb = 0;
+        for (int i = 0; i < p; ++i) {
+            part.kb0 = part.nkb;
+            part.nkb = attn_part_end(b.nkb, p, step, i);
+            part.slot = slots++;
+            plan.items.push_back(part);
+        }
+    }
     if (!plan.merges.empty()) attn_sort_items(plan.items);
     return plan;
 }

@@ -669,8 +669,9 @@ rs_status prefill_check(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_kv
 // `pending_in` (layers after the first of rs_prefill_model_batch): the previous layer's down projection left its split-K
 // sum pending; x is then that layer's output buffer, not yet written, and this layer's first kernel produces it.
 // `pending_out`: this layer may leave its own down projection pending in the same way (the next layer follows at once).
+// `plans`: the attention plan of the call's previous layer, if any; replaced where it does not fit.
 rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_kv* const* kvs, const int* lens, int R, int T,
-                          const void* x, void* y, void* ws, void* stream, const int* positions3 = nullptr,
+                          const void* x, void* y, void* ws, void* stream, AttnPlanCache& plans, const int* positions3 = nullptr,
                           const PendingReduce* pending_in = nullptr, PendingReduce* pending_out = nullptr) {
     const rs_layer_cfg& f = ctx->cfg;
     const WorkspaceLayout L = ws_layout(ctx, T, R);
@@ -744,7 +745,11 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
             for (int ax = 0; ax < 3; ++ax) rowpos.push_back(positions3 ? positions3[3 * (size_t)(row0 + t) + ax] : P + t);
         row0 += Ti;
     }
-    const AttnPlan plan = plan_attention(AttnPlanSettings{ctx->n_cu, ctx->attn_split}, att_reqs, ctx->group, f.n_kv_heads);
+    if (plans.reqs != att_reqs) {
+        plans.plan = plan_attention(AttnPlanSettings{ctx->n_cu, ctx->attn_split}, att_reqs, ctx->group, f.n_kv_heads);
+        plans.reqs.swap(att_reqs);
+    }
+    const AttnPlan& plan = plans.plan;
     const std::vector<AttnItem>& items = plan.items;
     const std::vector<AttnMergeItem>& mitems = plan.merges;
 
@@ -892,7 +897,8 @@ rs_status prefill_impl(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_kv*
     int T = 0;
     const rs_status s = prefill_check(ctx, w, layer, kvs, lens, R, x, y, ws, ws_bytes, &T, positions3);
     if (s != RS_OK || T == 0) return s;
-    return prefill_enqueue(ctx, w, layer, kvs, lens, R, T, x, y, ws, stream, positions3);
+    AttnPlanCache plans;
+    return prefill_enqueue(ctx, w, layer, kvs, lens, R, T, x, y, ws, stream, plans, positions3);
 }
 
 }  // namespace
@@ -1456,11 +1462,14 @@ static rs_status model_batch(rs_ctx* ctx, const rs_layer_weights* packed_layers,
     // Layer 0 reads x; later layers work on y in place.  Between two layers the split-K sum of the down projection, the
     // pass that takes the next layer's norm factors and the copy into its GEMMs' operand layout are one kernel (see
     // rms_and_fragment_major_kernel<true>): the bits are those of the layers called one by one.
+    // The attention plan of one layer serves the next while their caches are equally long (planning takes 2 to 15 us of host
+    // time, of about 30 per layer).
     PendingReduce pending;
+    AttnPlanCache plans;
     for (int l = 0; l < n_layers; ++l) {
         PendingReduce next;
         const rs_status s = prefill_enqueue(ctx, &packed_layers[l], l, kvs, chunk_lens, R, T, l == 0 ? x : y, y, workspace, stream,
-                                            positions3, l > 0 ? &pending : nullptr, l + 1 < n_layers ? &next : nullptr);
+                                            plans, positions3, l > 0 ? &pending : nullptr, l + 1 < n_layers ? &next : nullptr);
         if (s != RS_OK) return s;
         pending = next;
     }

@@ -26,7 +26,7 @@ int main() {
         s.n_cu = n_cu;
         s.split = split;
         const AttnPlan p = plan_attention(s, reqs, group, heads);
-        printf("plan %d %zu %zu %d %d\n", p.waves, p.items.size(), p.merges.size(), p.cost, attn_cost(attn_blocks(reqs, group, heads, p.waves), AttnCut{}, n_cu));
+        printf("plan %d %zu %zu %d %d\n", p.waves, p.items.size(), p.merges.size(), p.cost, attn_cost(attn_groups(attn_blocks(reqs, group, heads, p.waves)), AttnCut{}, n_cu));
         for (auto& i : p.items) printf("%d %d %d %d %d %d\n", i.req, i.kvh, i.qblock, i.kb0, i.nkb, i.slot);
         for (auto& m : p.merges) printf("%d %d %d %d %d\n", m.req, m.kvh, m.qblock, m.n_parts, m.slot0);
     }

@@ -113,3 +113,34 @@ def _run_with_bias(shape, w, reqs, capacity):
     kv.import_(0, r.to_device_bf16(reqs[0].prior_k), r.to_device_bf16(reqs[0].prior_v))
     y = r.to_numpy_f32(stack.prefill_batch(0, [kv], [reqs[0].rows.shape[0]], r.to_device_bf16(reqs[0].rows)))
     return y, oracle_batch(shape, w, reqs)[0]
+
+
+def test_layers_of_different_lengths_in_one_call():
+    """The layers of one call whose caches are equally long share one plan; where the lengths change, so must the plan: the same
+    bits as layer by layer, with caches cut into parts, too short for that, and long again."""
+    import torch
+    from paper_2509_24381_amd import runner as r
+    shape = synth.LayerShape("lens", 256, 4, 2, 128, 256)
+    w = synth.layer_weights(shape, 42, gains="uniform")
+    stack = r.LayerStack(shape, [w] * 4, max_tokens=80, max_requests=2, max_pos=3200)
+    lens, priors = [50, 30], [[2000, 2000, 300, 2500], [100, 100, 100, 900]]
+    rng = np.random.default_rng(43)
+    x = r.to_device_bf16(synth.prompt_rows([("text", sum(lens))], shape.hidden, 44))
+    made = [[[r.to_device_bf16(rng.standard_normal((p, 2, 128), dtype=np.float32)) for _ in range(2)] for p in ps] for ps in priors]
+
+    def caches():
+        kvs = [stack.new_cache(2600) for _ in lens]
+        for kv, layers in zip(kvs, made):
+            for l, (k, v) in enumerate(layers):
+                kv.import_(l, k, v)
+        return kvs
+    a, b = caches(), caches()
+    y = torch.empty_like(x)
+    stack.ctx.prefill_model_batch(stack.layers, a, lens, x, y, stack.ws)
+    z = x
+    for l in range(4):
+        z = stack.prefill_batch(l, b, lens, z)
+    assert torch.equal(y.view(torch.int16), z.view(torch.int16))
+    for kv_a, kv_b in zip(a, b):
+        for l in range(4):
+            assert all(torch.equal(s.view(torch.int16), t.view(torch.int16)) for s, t in zip(kv_a.export(l), kv_b.export(l)))
