@@ -41,10 +41,11 @@ struct AttnRequest {
 struct AttnPlanSettings {
     int n_cu;           // compute units
     int split;          // RS_ATTN_SPLIT: 0 decided here, 1 nothing is cut, n > 1 parts of every block
+    bool plain_order;   // RS_ATTN_ORDER=plain: blocks that share a compute unit stay in heaviest-first order
 };
 struct AttnPlan {
     int waves = ATT_WAVES;
-    int cost = 0;   // estimated duration, in tiles (0: nothing was weighed)
+    int cost = 0;   // estimated duration, in tiles (0 under RS_ATTN_SPLIT > 1)
     std::vector<AttnItem> items;
     std::vector<AttnMergeItem> merges;
 };
@@ -173,6 +174,36 @@ inline std::vector<AttnItem> attn_blocks(const std::vector<AttnRequest>& reqs, i
     return blocks;
 }
 
+// Two blocks of four wavefronts to a compute unit (between n_cu and 2 n_cu of them, heaviest first, nothing cut): the heaviest run
+// alone, the others in pairs, heavy with light, and all are there from the first clock.  A pair shares the unit until the light one
+// ends, at the rate of a block of eight (289.8 us against 287.1 at d = 128, 179.4 against 183.2 at d = 64, 512 blocks of 128 rows on
+// 8192 tokens); a block alone takes 0.65 (d = 128) to 0.70 (d = 64) of that per tile: ATT_COST_ALONE / 16.
+constexpr int ATT_COST_ALONE = 11;
+inline int attn_pairs_cost(const std::vector<AttnItem>& blocks, int n_cu) {
+    const int n = (int)blocks.size(), lone = 2 * n_cu - n;
+    int end = blocks[0].nkb * ATT_COST_ALONE;
+    for (int k = 0; k < n - n_cu; ++k) {
+        const int heavy = blocks[lone + k].nkb, light = blocks[n - 1 - k].nkb;
+        end = std::max(end, 16 * light + (heavy - light) * ATT_COST_ALONE);
+    }
+    return (end + 15) / 16 + ATT_COST_ITEM;
+}
+// Their order.  On an empty chip the dispatcher hands workgroup k and workgroup k + n_cu to the same compute unit (measured: 448
+// workgroups that fit two to a unit leave exactly workgroups 192 .. 255 alone on theirs).
+inline void attn_place_pairs(std::vector<AttnItem>& blocks, int n_cu, int kv_heads) {
+    const int n = (int)blocks.size(), paired = n - n_cu, lone = n_cu - paired;
+    std::vector<AttnItem> placed(n);
+    for (int k = 0; k < lone; ++k) placed[paired + k] = blocks[k];
+    // (the light partners are taken from the tail in runs of one block per KV head, in the head order of the front: the blocks of a
+    //  head then stay on the XCDs, workgroup index mod 8, whose L2 already holds that head's K and V)
+    const bool by_head = n % kv_heads == 0 && paired % kv_heads == 0;
+    for (int k = 0; k < paired; ++k) {
+        placed[k] = blocks[lone + k];
+        placed[n_cu + k] = by_head ? blocks[n - kv_heads * (k / kv_heads + 1) + k % kv_heads] : blocks[n - 1 - k];
+    }
+    blocks.swap(placed);
+}
+
 // The call's work items.  One workgroup of eight wavefronts fills a compute unit, so a launch lasts as long as the fullest unit:
 // key ranges are cut where that ends the launch sooner, and the parts of a cut block are combined by attn_merge_kernel.
 // Measured at the 7B shape, attention step, nothing cut -> planned: 16 requests, 2048 rows, caches of 0 to 12288 tokens 256 -> 178
@@ -182,12 +213,17 @@ inline std::vector<AttnItem> attn_blocks(const std::vector<AttnRequest>& reqs, i
 // Calls too small to fill the chip even with every key range cut as finely as it may be take blocks of four wavefronts: twice the
 // workgroups, and a wavefront that has its SIMD to itself (attention step with eight and with four, 64 rows on 2048 cached tokens,
 // 7B shape: 24.4 and 20.5 us; tiny shape, 128 rows on 384: 14.0 and 11.4).
+// So do calls of more small blocks than compute units, but no more than two to each, where the pairs of attn_pairs_cost end sooner:
+// the blocks of a prompt's first chunks differ in length, and cutting them costs more than pairing.  Attention step, us, blocks of
+// eight planned as above -> pairs: 7B, 2048 rows on 0 tokens 60.8 -> 52.0 (in heaviest-first order 55.1), on 2000 109 -> 99, on 6144
+// 207 -> 202; 32 / 8 heads of 64, 2048 rows on 0: 42.6 -> 35.0, on 2000: 77.4 -> 66.1.
 inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<AttnRequest>& reqs, int group, int kv_heads) {
     AttnPlan plan;
-    long most = 0;   // parts the small blocks could be cut into
+    long n_small = 0, most = 0;   // small blocks, parts they could be cut into
     for (const AttnRequest& r : reqs) {
         const long blocks = ((long)r.T * group + 32 * ATT_WAVES_SMALL - 1) / (32 * ATT_WAVES_SMALL) * kv_heads;
         const long tiles = ((long)r.P + r.T + ATT_KEYS - 1) / ATT_KEYS;
+        n_small += blocks;
         most += blocks * (tiles < ATT_MIN_SPLIT_TILES ? 1 : std::min<long>(tiles / ATT_MIN_PART_TILES, ATT_MAX_PARTS));
     }
     if (most <= s.n_cu) plan.waves = ATT_WAVES_SMALL;
@@ -197,10 +233,10 @@ inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<Attn
     AttnCut cut;
     const std::vector<AttnGroup> groups = attn_groups(blocks);
     const int longest = blocks[0].nkb, n = (int)blocks.size();
+    if (s.split <= 1) plan.cost = attn_cost(groups, cut, s.n_cu);
     if (s.split > 1) {
         cut.parts = s.split;
     } else if (s.split == 0 && longest >= ATT_MIN_SPLIT_TILES) {
-        plan.cost = attn_cost(groups, cut, s.n_cu);
         const auto consider = [&](AttnCut c) {
             const int cost = attn_cost(groups, c, s.n_cu);
             if (cost < plan.cost) {
@@ -228,6 +264,17 @@ inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<Attn
         c.even = false;
         c.cap = (int)((work + (long)n * ATT_COST_PART) * 102 / 100 / s.n_cu) + 1;
         if (c.cap >= ATT_MIN_PART_TILES && c.cap + ATT_MIN_PART_TILES <= longest) consider(c);
+    }
+    if (plan.waves == ATT_WAVES && s.split <= 1 && n_small > s.n_cu && n_small <= 2 * s.n_cu) {
+        std::vector<AttnItem> pairs = attn_blocks(reqs, group, kv_heads, ATT_WAVES_SMALL);
+        const int cost = attn_pairs_cost(pairs, s.n_cu);
+        if (cost < plan.cost) {
+            if (!s.plain_order) attn_place_pairs(pairs, s.n_cu, kv_heads);
+            plan.waves = ATT_WAVES_SMALL;
+            plan.cost = cost;
+            plan.items.swap(pairs);
+            return plan;
+        }
     }
     plan.items.reserve(blocks.size() + ATT_SPLIT_SLOTS);
     int slots = 0;

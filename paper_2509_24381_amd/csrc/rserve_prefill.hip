@@ -103,6 +103,7 @@ struct rs_ctx {
     hipStream_t last_stream = nullptr;
     int splitk_override = 0;  // RS_SPLITK environment variable (0 = heuristic)
     int mrope_b0 = 0, mrope_b1 = 0;  // rotary pair j turns with axis 0 below b0, axis 1 below b1, axis 2 above (set in rs_ctx_create)
+    bool attn_plain_order = false;  // RS_ATTN_ORDER=plain: attention blocks that share a compute unit stay heaviest-first (no pairing)
     int attn_split = 0;       // RS_ATTN_SPLIT environment variable: parts a block's key range is cut into (0: decided per call)
     int gemm_pairs = 1;       // RS_PAIRS environment variable: 0 never lets two wavefronts of a GEMM workgroup split a pair of units
     int gemm_narrow = 1;      // RS_NARROW environment variable: 0 never uses the narrow GEMM geometry; otherwise launches of at most
@@ -746,7 +747,7 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         row0 += Ti;
     }
     if (plans.reqs != att_reqs) {
-        plans.plan = plan_attention(AttnPlanSettings{ctx->n_cu, ctx->attn_split}, att_reqs, ctx->group, f.n_kv_heads);
+        plans.plan = plan_attention(AttnPlanSettings{ctx->n_cu, ctx->attn_split, ctx->attn_plain_order}, att_reqs, ctx->group, f.n_kv_heads);
         plans.reqs.swap(att_reqs);
     }
     const AttnPlan& plan = plans.plan;
@@ -938,6 +939,7 @@ rs_status rs_ctx_create(const rs_layer_cfg* cfg, rs_ctx** out) {
     if (const char* e = getenv("RS_PAIRS")) c->gemm_pairs = atoi(e);
     if (const char* e = getenv("RS_NARROW")) c->gemm_narrow = atoi(e);
     if (const char* e = getenv("RS_NARROW_TM")) c->narrow_max_tiles_m = atoi(e);
+    if (const char* e = getenv("RS_ATTN_ORDER")) c->attn_plain_order = strcmp(e, "plain") == 0;
     if (const char* e = getenv("RS_ATTN_SPLIT")) c->attn_split = std::max(0, std::min(atoi(e), ATT_MAX_PARTS));
     auto cleanup = [&](rs_status s) { rs_ctx_destroy(c); return s; };
 

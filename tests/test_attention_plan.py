@@ -3,8 +3,8 @@ compute-unit counts and request mixes, up to 16 parts a block and an exhausted s
 
 Checked for every plan: each (request, KV head, block of rows) is covered exactly once, by one whole item or by consecutive
 parts; a part has at least 6 tiles (every row of a block must see keys of each part) and a block at most 16; slots are numbered
-without gaps, stay inside the buffer and belong to one block; items come heaviest first; and what was built costs what was
-estimated, never more than leaving every block whole.
+without gaps, stay inside the buffer and belong to one block; items come heaviest first, or the heaviest alone and the others in
+pairs; and what was built costs what was estimated, never more than leaving every block whole.
 """
 import os
 import random
@@ -18,15 +18,16 @@ HARNESS = r"""
 #include <cstdio>
 #include "attention_plan.h"
 int main() {
-    int n_cu, split, group, heads, n;
-    while (scanf("%d %d %d %d %d", &n_cu, &split, &group, &heads, &n) == 5) {
+    int n_cu, split, plain, group, heads, n;
+    while (scanf("%d %d %d %d %d %d", &n_cu, &split, &plain, &group, &heads, &n) == 6) {
         std::vector<AttnRequest> reqs(n);
         for (auto& r : reqs) if (scanf("%d %d", &r.T, &r.P) != 2) return 1;
         AttnPlanSettings s{};
         s.n_cu = n_cu;
         s.split = split;
+        s.plain_order = plain != 0;
         const AttnPlan p = plan_attention(s, reqs, group, heads);
-        printf("plan %d %zu %zu %d %d\n", p.waves, p.items.size(), p.merges.size(), p.cost, attn_cost(attn_groups(attn_blocks(reqs, group, heads, p.waves)), AttnCut{}, n_cu));
+        printf("plan %d %zu %zu %d %d\n", p.waves, p.items.size(), p.merges.size(), p.cost, attn_cost(attn_groups(attn_blocks(reqs, group, heads, n_cu > 0 && p.waves == ATT_WAVES_SMALL && (int)p.items.size() <= n_cu ? ATT_WAVES_SMALL : ATT_WAVES)), AttnCut{}, n_cu));
         for (auto& i : p.items) printf("%d %d %d %d %d %d\n", i.req, i.kvh, i.qblock, i.kb0, i.nkb, i.slot);
         for (auto& m : p.merges) printf("%d %d %d %d %d\n", m.req, m.kvh, m.qblock, m.n_parts, m.slot0);
     }
@@ -42,8 +43,8 @@ def planner(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-Wall",
                     "-I", os.path.join(ROOT, "paper_2509_24381_amd", "csrc"), str(src), "-o", str(exe)], check=True)
 
-    def run(cases):
-        text = "\n".join(" ".join(map(str, [n_cu, split, g, h, len(reqs), *[v for r in reqs for v in r]]))
+    def run(cases, plain=0):
+        text = "\n".join(" ".join(map(str, [n_cu, split, plain, g, h, len(reqs), *[v for r in reqs for v in r]]))
                          for n_cu, split, g, h, reqs in cases)
         env = dict(os.environ, LD_PRELOAD="", ASAN_OPTIONS="detect_leaks=0")
         out = iter(subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True, env=env).stdout.splitlines())
@@ -91,10 +92,18 @@ def _check(case, plan):
         n_slots += n_parts
     assert n_slots <= 384 and sorted(s for *_, s in items if s >= 0) == list(range(n_slots))
     lens = [nkb - kb0 for *_, kb0, nkb, _ in items]
+    if waves == 4 and len(items) > n_cu:   # item k and item k + n_cu share a compute unit: ranks lone + k and n - 1 - k
+        n, paired = len(items), len(items) - n_cu
+        ranks = sorted(lens, reverse=True)
+        assert n <= 2 * n_cu and not merges and split <= 1
+        assert lens == ranks[n_cu - paired: n_cu] + ranks[:n_cu - paired] + ranks[n_cu:][::-1]
+        ends = [16 * b + 11 * (a - b) for a, b in zip(lens, lens[n_cu:])] + [11 * a for a in lens[paired:n_cu]]
+        assert -(-max(ends) // 16) + 2 == estimate <= whole_cost
+        return
     assert lens == sorted(lens, reverse=True)
     if split == 1 or max(tiles.values()) < 16:
         assert split > 1 or not merges
-    if split == 0 and max(tiles.values()) >= 16:   # (tiles + 2 per whole item, + 4 per part, 4 and 1 per 36 parts for the merge)
+    if split <= 1:   # (tiles + 2 per whole item, + 4 per part, 4 and 1 per 36 parts for the merge)
         cost = _list_schedule([nkb - kb0 + (4 if s >= 0 else 2) for *_, kb0, nkb, s in items], n_cu)
         assert cost + (4 + n_slots // 36 if merges else 0) == estimate <= whole_cost
 
@@ -132,11 +141,17 @@ def test_swept_plans(planner):
 
 
 def test_the_forms_are_reached(planner):
-    """Whole blocks, equal parts, an even share with a rest, and blocks of four wavefronts each occur where the rules put them."""
-    whole, equal, share, small = planner([(256, 0, 8, 8, [(4096, 28672)]), (256, 0, 7, 4, [(250, 8192)]), (256, 0, 7, 4, [(2048, 6144)]),
+    """Whole blocks, equal parts, an even share with a rest, blocks of four wavefronts, and pairs of them occur where the rules
+    put them; RS_ATTN_ORDER=plain gives the same blocks in another order."""
+    whole, equal, share, small = planner([(256, 0, 8, 8, [(4096, 28672)]), (256, 0, 7, 4, [(250, 8192)]), (256, 0, 7, 4, [(1000, 12000)]),
                                           (256, 0, 2, 2, [(128, 384)])])
     assert not whole[2] and whole[0] == 8
     assert equal[2] and len(equal[1]) <= 256
     lens = {m[:3]: sorted(i[4] - i[3] for i in share[1] if i[:3] == m[:3]) for m in share[2]}
     assert any(v[-1] - v[0] > 1 for v in lens.values()) and len(share[1]) > 256
-    assert small[0] == 4 and equal[0] == 8
+    assert small[0] == 4 and len(small[1]) <= 256 and equal[0] == 8
+    for case in ((256, 0, 7, 4, [(2048, 0)]), (256, 0, 4, 8, [(2048, 2000)]), (7, 0, 2, 2, [(384, 0)]), (7, 0, 2, 2, [(384, 384)])):
+        paired, plain = planner([case])[0], planner([case], plain=1)[0]
+        assert paired[0] == plain[0] == 4 and case[0] < len(paired[1]) <= 2 * case[0]
+        assert paired[1] != plain[1] and sorted(paired[1]) == sorted(plain[1])
+        assert [i[4] for i in plain[1]] == sorted((i[4] for i in plain[1]), reverse=True)
