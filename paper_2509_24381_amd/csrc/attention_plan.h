@@ -174,6 +174,20 @@ inline std::vector<AttnItem> attn_blocks(const std::vector<AttnRequest>& reqs, i
     return blocks;
 }
 
+// Equal parts as long as every part has a compute unit of its own: the smallest cap with at most n_cu parts.
+inline AttnCut attn_even_cut(const std::vector<AttnGroup>& groups, int n_cu) {
+    AttnCut c;
+    int lo = ATT_MIN_PART_TILES, hi = std::max(lo, groups[0].n);
+    while (lo < hi) {
+        c.cap = (lo + hi) / 2;
+        long parts = 0;
+        for (const AttnGroup& g : groups) parts += (long)g.count * c.of(g.n).first;
+        if (parts <= n_cu) hi = c.cap; else lo = c.cap + 1;
+    }
+    c.cap = lo;
+    return c;
+}
+
 // Two blocks of four wavefronts to a compute unit (between n_cu and 2 n_cu of them, heaviest first, nothing cut): the heaviest run
 // alone, the others in pairs, heavy with light, and all are there from the first clock.  A pair shares the unit until the light one
 // ends, at the rate of a block of eight (289.8 us against 287.1 at d = 128, 179.4 against 183.2 at d = 64, 512 blocks of 128 rows on
@@ -204,15 +218,21 @@ inline void attn_place_pairs(std::vector<AttnItem>& blocks, int n_cu, int kv_hea
     blocks.swap(placed);
 }
 
+constexpr int ATT_SMALL_PART_TILES = 24;
+
 // The call's work items.  One workgroup of eight wavefronts fills a compute unit, so a launch lasts as long as the fullest unit:
 // key ranges are cut where that ends the launch sooner, and the parts of a cut block are combined by attn_merge_kernel.
-// Measured at the 7B shape, attention step, nothing cut -> planned: 16 requests, 2048 rows, caches of 0 to 12288 tokens 256 -> 178
-// us; 1000 rows on 12000 tokens 181 -> 161; 250 on 8192: 69 -> 48; 64 on 2048: 28 -> 24; 2048 on 6144: 210 -> 200 (97 to 128 tiles
-// per block, at most 105 per unit after: the board's power limit gives back little of a better balance).  4096 rows on 28672 (1024
-// blocks) stay whole.
+// Measured at the 7B shape, attention step, nothing cut (RS_ATTN_SPLIT=1) -> planned: 64 rows on 2048 cached tokens 38 -> 21 us, 250
+// on 8192: 162 -> 49, 1000 on 12000: 272 -> 169; 16 requests, 2048 rows, caches of 0 to 12288 tokens 206 -> 174.  4096 rows on 28672
+// (1024 blocks) stay whole.
 // Calls too small to fill the chip even with every key range cut as finely as it may be take blocks of four wavefronts: twice the
 // workgroups, and a wavefront that has its SIMD to itself (attention step with eight and with four, 64 rows on 2048 cached tokens,
-// 7B shape: 24.4 and 20.5 us; tiny shape, 128 rows on 384: 14.0 and 11.4).
+// 7B shape: 24.4 and 20.5 us; tiny shape, 128 rows on 384: 14.0 and 11.4).  So do calls whose small blocks have, in equal parts one
+// to a compute unit, ATT_SMALL_PART_TILES or fewer (blocks of eight leave half the parts, of twice the bytes; with longer walks
+// their one fetch per 256 rows counts for more).  Eight and four, us, with the tiles of the longest small part: 7B, 250 rows on 2000
+// (9) 29.7 and 27.0, three requests of 83 to 150 rows on 500 to 3000 (12) 34.1 and 28.4, 512 on 1536 (16) 33.6 and 33.0, 700 on 700
+// (22) 33.3 and 32.2, 250 on 8192 (33) 48.0 and 51.6; 12 / 2 heads, 512 on 4000 (15) 33.2 and 29.8; 72B, 250 on 2000 (18) 40.9 and
+// 39.6, 128 on 8000 (32) 48.2 and 49.7; 32 / 8 heads of 64, 250 on 2000 (9) 20.2 and 18.3, on 8000 (33) 32.1 and 33.4.
 // So do calls of more small blocks than compute units, but no more than two to each, where the pairs of attn_pairs_cost end sooner:
 // the blocks of a prompt's first chunks differ in length, and cutting them costs more than pairing.  Attention step, us, blocks of
 // eight planned as above -> pairs: 7B, 2048 rows on 0 tokens 60.8 -> 52.0 (in heaviest-first order 55.1), on 2000 109 -> 99, on 6144
@@ -226,13 +246,21 @@ inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<Attn
         n_small += blocks;
         most += blocks * (tiles < ATT_MIN_SPLIT_TILES ? 1 : std::min<long>(tiles / ATT_MIN_PART_TILES, ATT_MAX_PARTS));
     }
-    if (most <= s.n_cu) plan.waves = ATT_WAVES_SMALL;
-    const std::vector<AttnItem> blocks = attn_blocks(reqs, group, kv_heads, plan.waves);
-    if (blocks.empty()) return plan;
+    if (n_small == 0) return plan;
+    std::vector<AttnItem> blocks;
+    bool small = most <= s.n_cu;
+    if (small || n_small <= s.n_cu) blocks = attn_blocks(reqs, group, kv_heads, ATT_WAVES_SMALL);
+    if (!small && n_small <= s.n_cu) {
+        const std::vector<AttnGroup> g = attn_groups(blocks);
+        const AttnCut even = g[0].n >= ATT_MIN_SPLIT_TILES ? attn_even_cut(g, s.n_cu) : AttnCut{};
+        small = (g[0].n + even.of(g[0].n).first - 1) / even.of(g[0].n).first <= ATT_SMALL_PART_TILES;
+    }
+    if (small) plan.waves = ATT_WAVES_SMALL;
+    else blocks = attn_blocks(reqs, group, kv_heads, ATT_WAVES);
 
     AttnCut cut;
     const std::vector<AttnGroup> groups = attn_groups(blocks);
-    const int longest = blocks[0].nkb, n = (int)blocks.size();
+    const int longest = groups[0].n, n = (int)blocks.size();
     if (s.split <= 1) plan.cost = attn_cost(groups, cut, s.n_cu);
     if (s.split > 1) {
         cut.parts = s.split;
@@ -244,19 +272,8 @@ inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<Attn
                 cut = c;
             }
         };
-        // (1) equal parts, as long as every part has a compute unit of its own: the smallest cap with at most n_cu parts
-        if (n < s.n_cu) {
-            AttnCut c;
-            int lo = ATT_MIN_PART_TILES, hi = longest;
-            while (lo < hi) {
-                c.cap = (lo + hi) / 2;
-                long parts = 0;
-                for (const AttnGroup& g : groups) parts += (long)g.count * c.of(g.n).first;
-                if (parts <= s.n_cu) hi = c.cap; else lo = c.cap + 1;
-            }
-            c.cap = lo;
-            consider(c);
-        }
+        // (1) equal parts, one to a compute unit
+        if (n < s.n_cu) consider(attn_even_cut(groups, s.n_cu));
         // (2) an even share for every compute unit: blocks longer than the share are cut there, the rests fill the gaps
         long work = 0;
         for (const AttnGroup& g : groups) work += (long)g.n * g.count;

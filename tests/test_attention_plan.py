@@ -27,7 +27,7 @@ int main() {
         s.split = split;
         s.plain_order = plain != 0;
         const AttnPlan p = plan_attention(s, reqs, group, heads);
-        printf("plan %d %zu %zu %d %d\n", p.waves, p.items.size(), p.merges.size(), p.cost, attn_cost(attn_groups(attn_blocks(reqs, group, heads, n_cu > 0 && p.waves == ATT_WAVES_SMALL && (int)p.items.size() <= n_cu ? ATT_WAVES_SMALL : ATT_WAVES)), AttnCut{}, n_cu));
+        printf("plan %d %zu %zu %d %d\n", p.waves, p.items.size(), p.merges.size(), p.cost, attn_cost(attn_groups(attn_blocks(reqs, group, heads, p.waves == ATT_WAVES_SMALL && ((int)p.items.size() <= n_cu || !p.merges.empty()) ? ATT_WAVES_SMALL : ATT_WAVES)), AttnCut{}, n_cu));
         for (auto& i : p.items) printf("%d %d %d %d %d %d\n", i.req, i.kvh, i.qblock, i.kb0, i.nkb, i.slot);
         for (auto& m : p.merges) printf("%d %d %d %d %d\n", m.req, m.kvh, m.qblock, m.n_parts, m.slot0);
     }
@@ -92,10 +92,10 @@ def _check(case, plan):
         n_slots += n_parts
     assert n_slots <= 384 and sorted(s for *_, s in items if s >= 0) == list(range(n_slots))
     lens = [nkb - kb0 for *_, kb0, nkb, _ in items]
-    if waves == 4 and len(items) > n_cu:   # item k and item k + n_cu share a compute unit: ranks lone + k and n - 1 - k
+    if waves == 4 and len(items) > n_cu and not merges:   # item k and item k + n_cu share a compute unit: ranks lone + k and n - 1 - k
         n, paired = len(items), len(items) - n_cu
         ranks = sorted(lens, reverse=True)
-        assert n <= 2 * n_cu and not merges and split <= 1
+        assert n <= 2 * n_cu and split <= 1
         assert lens == ranks[n_cu - paired: n_cu] + ranks[:n_cu - paired] + ranks[n_cu:][::-1]
         ends = [16 * b + 11 * (a - b) for a, b in zip(lens, lens[n_cu:])] + [11 * a for a in lens[paired:n_cu]]
         assert -(-max(ends) // 16) + 2 == estimate <= whole_cost
@@ -145,11 +145,13 @@ def test_the_forms_are_reached(planner):
     put them; RS_ATTN_ORDER=plain gives the same blocks in another order."""
     whole, equal, share, small = planner([(256, 0, 8, 8, [(4096, 28672)]), (256, 0, 7, 4, [(250, 8192)]), (256, 0, 7, 4, [(1000, 12000)]),
                                           (256, 0, 2, 2, [(128, 384)])])
+    cut_small, = planner([(256, 0, 7, 4, [(250, 2000)])])
     assert not whole[2] and whole[0] == 8
     assert equal[2] and len(equal[1]) <= 256
     lens = {m[:3]: sorted(i[4] - i[3] for i in share[1] if i[:3] == m[:3]) for m in share[2]}
     assert any(v[-1] - v[0] > 1 for v in lens.values()) and len(share[1]) > 256
     assert small[0] == 4 and len(small[1]) <= 256 and equal[0] == 8
+    assert cut_small[0] == 4 and cut_small[2] and max(i[4] - i[3] for i in cut_small[1]) == 9
     for case in ((256, 0, 7, 4, [(2048, 0)]), (256, 0, 4, 8, [(2048, 2000)]), (7, 0, 2, 2, [(384, 0)]), (7, 0, 2, 2, [(384, 384)])):
         paired, plain = planner([case])[0], planner([case], plain=1)[0]
         assert paired[0] == plain[0] == 4 and case[0] < len(paired[1]) <= 2 * case[0]
