@@ -30,6 +30,11 @@ RS_DEVICE float wave_sum(float v) {
 RS_DEVICE uint4 ld_global_16(const void* p) { return *reinterpret_cast<const uint4*>(p); }
 RS_DEVICE void st_global_16(void* p, uint4 v) { *reinterpret_cast<uint4*>(p) = v; }
 
+RS_DEVICE void st_global_16_stream(void* p, uint4 v) {   // (for what the launch does not read again)
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+    __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t*>(p));
+}
+
 RS_DEVICE bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 RS_DEVICE uint4 as_uint4(bf16x8 v) { return __builtin_bit_cast(uint4, v); }
 

@@ -1055,7 +1055,7 @@ rs_status rs_weights_pack(rs_ctx* c, const rs_layer_weights* src, void* dst, siz
     RS_HIP(copy(src->ln2_g, H * 2, &o.ln2_g));
     auto pack = [&](const void* m, int rows, int K, const void* gain, int mode, int p0, int p1, const void** slot) -> hipError_t {
         *slot = p;
-        hipLaunchKernelGGL(pack_rows_kernel, dim3(rows / 32, (K + PACK_K - 1) / PACK_K), dim3(256), 0, st, (const bf16*)m, (const bf16*)gain, reinterpret_cast<bf16*>(p), K,
+        hipLaunchKernelGGL(pack_rows_kernel, dim3(rows / 32 * ((K + PACK_K - 1) / PACK_K)), dim3(256), 0, st, (const bf16*)m, (const bf16*)gain, reinterpret_cast<bf16*>(p), K,
                            mode, p0, p1, (int)aligned(m, 16));
         p += align_up((size_t)rows * K * 2, 256);
         return hipGetLastError();
