@@ -4,8 +4,8 @@
 // Bound by HBM: every element is read and written once.  One workgroup moves one 64-token block of one KV head, 8 elements
 // (one 16-byte chunk of bfloat16) per access; K rows are contiguous on both sides, V^T tiles are turned through LDS.  The
 // element-by-element form before it (one thread per element, V^T read or written with a stride of 128 bytes) took
-// 67 us for export, import and export of 8192 tokens at the 7B shape (100 MB moved); this one takes 32 (3.2 TB/s with the three
-// launches in it).  Behind a layer call, 8442 paged tokens: the call and its export 296 -> 273 us; 13000 tokens of 8-bit pages,
+// 67 us for export, import and export of 8192 tokens at the 7B shape (100 MB moved); this one takes 31 (3.2 TB/s with the three
+// launches in it; a thread has one access in flight, and a workgroup of few tiles waits for four or five in a row).  Behind a layer call, 8442 paged tokens: the call and its export 296 -> 273 us; 13000 tokens of 8-bit pages,
 // with the attention kernel's gain: 706 -> 644.
 //
 // The canonical arrays come from the caller and need only their element's alignment: `wide` says that both can be accessed
@@ -34,6 +34,26 @@ RS_DEVICE uint4 convert8(uint2 codes, float scale, bf16*) {   // read an 8-bit c
     return as_uint4(o);
 }
 RS_DEVICE uint2 convert8(uint4 v, float inv, uint8_t*) { return e4m3_from_bf16x8(as_bf16x8(v), inv); }   // store to one
+
+// Eight elements of an LDS tile, element(0) .. element(7), as one value.  (Put together word by word: out of a union of eight bf16 the
+// compiler makes four stores.)
+template <class T, class F>
+RS_DEVICE typename Pack8<T>::type gather8(F&& element) {
+    typename Pack8<T>::type v;
+    uint32_t* w = reinterpret_cast<uint32_t*>(&v);
+    constexpr int PER = 4 / (int)sizeof(T);
+#pragma unroll
+    for (int j = 0; j < 8 / PER; ++j) {
+        w[j] = 0u;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            const T x = element(j * PER + e);
+            if constexpr (sizeof(T) == 2) w[j] |= (uint32_t)__builtin_bit_cast(uint16_t, x) << (16 * e);
+            else w[j] |= (uint32_t)x << (8 * e);
+        }
+    }
+    return v;
+}
 
 // T: the cache's element (bf16, or uint8_t for E4M3 codes), C: the canonical one (bf16, or uint8_t for codes).
 // The K or V^T tile of one KV head and block:
@@ -72,10 +92,8 @@ __global__ __launch_bounds__(256) void kv_export_kernel(ReqDesc rq, Fp8CacheDesc
     __syncthreads();
     for (int i = threadIdx.x; i < left * CPR; i += 256) {
         const int t = i / CPR, ch = i % CPR;
-        union { T e[8]; P v; } u;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u.e[e] = vt[ch * 8 + e][t];
-        store8(v0 + (size_t)t * hkv * D + ch * 8, convert8(u.v, fc.v_scale, (C*)nullptr), wide);
+        const P v = gather8<T>([&](int e) { return vt[ch * 8 + e][t]; });
+        store8(v0 + (size_t)t * hkv * D + ch * 8, convert8(v, fc.v_scale, (C*)nullptr), wide);
     }
 }
 
@@ -107,9 +125,6 @@ __global__ __launch_bounds__(256) void kv_import_kernel(ReqDesc rq, Fp8CacheDesc
     }
     __syncthreads();
     for (int i = threadIdx.x; i < D * 8; i += 256) {   // feature i / 8, tokens 8 (i % 8) ..
-        union { T e[8]; P v; } u;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u.e[e] = rows[(i & 7) * 8 + e][i >> 3];
-        store8(vtile + (size_t)i * 8, u.v, true);
+        store8(vtile + (size_t)i * 8, gather8<T>([&](int e) { return rows[(i & 7) * 8 + e][i >> 3]; }), true);
     }
 }
