@@ -286,8 +286,12 @@ rs_status rs_prefill_model_batch_mrope(rs_ctx* ctx, const rs_layer_weights* pack
  *   w_lm             device bf16 [vocab, H], torch layout, used as is
  *   x                device bf16 [n_rows, H]
  *   logits           device fp32 [n_rows, vocab]:  logits[r, v] = sum_k rmsnorm(x[r])[k] * w_lm[v, k], fp32 accumulation,
- *                    the normalised row kept in fp32
- * workspace: rs_lm_head_workspace_bytes(ctx, n_rows) bytes, 256-byte aligned.  n_rows = 0 is a no-op. */
+ *                    the normalised row kept in fp32 or better
+ * workspace: rs_lm_head_workspace_bytes(ctx, n_rows) bytes, 256-byte aligned.  n_rows = 0 is a no-op.
+ * Calls of three rows and more run on the matrix pipe: a row's logits are then the same bits whatever rows come with it.  Calls of one
+ * or two rows, and calls whose workspace holds 4 hidden bytes per row (rounded up to 256, the least that is accepted) but not what
+ * rs_lm_head_workspace_bytes asks for (64 hidden bytes per 10 rows), run a kernel of another summation order: both are within
+ * 2e-7 of the exact logits (2-norm), but their last bits differ, and with them the winner of a near-tie. */
 size_t rs_lm_head_workspace_bytes(const rs_ctx* ctx, int n_rows);
 rs_status rs_lm_head(rs_ctx* ctx, const void* final_norm_gain_dev, const void* w_lm_dev, int vocab,
                      const void* x_dev, int n_rows, void* logits_dev,

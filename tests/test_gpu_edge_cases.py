@@ -358,8 +358,8 @@ def _same_up_to(kv_a, kv_b, n, shape):
 
 
 def test_attention_item_order_does_not_change_a_bit(monkeypatch):
-    """Between one and two attention blocks per compute unit the host pairs heavy blocks with light ones by compute unit
-    instead of launching them heaviest-first.  Blocks are independent, so the two orders must agree to the bit.  The
+    """Between one and two attention blocks of four wavefronts per compute unit the host pairs heavy blocks with light ones by
+    compute unit instead of launching them heaviest-first.  Blocks are independent, so the two orders must agree to the bit.  The
     compute-unit count is a context setting read from the environment when the context is created: 7 here, so that the
     12 blocks of a 384-row chunk (6 blocks of 128 stacked rows x 2 KV heads) fall between 7 and 14."""
     r = R()
@@ -391,7 +391,7 @@ def test_alternative_kernel_paths_meet_the_same_bar(env):
     """Other split-K factors of the residual GEMMs, and other numbers of strips (RS_NCU stands in for the device's
     compute-unit count: small values give wide strips, i.e. every tile width from 2 to 8 units on these small shapes,
     where the default gives one unit per strip), and a fixed number of parts per attention block (RS_ATTN_SPLIT: 1 never splits a key
-    range, 3 cuts every block with at least 48 key tiles in three and those with at least 32 in two), and the GEMM geometry
+    range, 3 cuts every block with at least 18 key tiles in three and those with at least 12 in two), and the GEMM geometry
     for launches whose strips hold at most two units (RS_NARROW 0: never the narrow one; RS_NARROW_TM 8: also for calls of
     up to 8 token blocks, which with RS_NCU 40 makes strips of one and two units on these shapes; RS_PAIRS 0: never two
     wavefronts per pair of units), and the plain order of the attention work items (RS_ATTN_ORDER; the default order, which

@@ -39,6 +39,15 @@ def test_logits_of_three_rows_and_more(hidden, vocab, n_rows):
     assert err <= 1e-6
 
 
+def test_a_row_has_the_same_logits_in_every_call_of_three_rows_and_more():
+    """One and two groups of rows, passes with a rest, first and last places: bit for bit."""
+    runner, ctx, shape, g, w, x = _head(704, 3000, 23)
+    gd, wd, xd = (runner.to_device_bf16(a) for a in (g, w, x))
+    all_rows = ctx.lm_head(gd, wd, xd)
+    for first, n in ((0, 3), (5, 9), (2, 10), (0, 11), (3, 20), (19, 4)):
+        assert torch.equal(ctx.lm_head(gd, wd, xd[first: first + n].contiguous()), all_rows[first: first + n])
+
+
 def test_a_workspace_of_four_bytes_per_value_is_still_enough():
     """4 H bytes per row (rounded up to 256) is all the fp32 kernel needs; the same call with the full size takes the matrix
     path.  Both meet the bar; a smaller workspace is refused."""
@@ -104,8 +113,8 @@ def test_the_three_pieces_sum_to_the_normalised_value(hidden):
             want = ws1[: hidden * 4].view(torch.float32).double().cpu().numpy() * g.astype(np.float64)
         keep = np.abs(want) <= np.finfo(np.float32).max
         edge += int(np.sum(keep & (np.abs(want) > 3.3961e38)))
-        got = sum(pieces[r // 10, 10 * s + r % 10] for s in range(3))
-        assert np.all(np.abs(got - want)[keep] <= 2.0 ** -26 * np.abs(want)[keep])
+        got = sum(pieces[r // 10, 10 * s + r % 10][keep] for s in range(3))
+        assert np.all(np.abs(got - want[keep]) <= 2.0 ** -26 * np.abs(want)[keep])
     assert edge > 0, "no value between the largest bfloat16 and the largest fp32 number"
 
 
