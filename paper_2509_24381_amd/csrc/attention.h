@@ -427,8 +427,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_prefill_pipelined_kernel(c
 
     const float l_tot = l_run + __shfl_xor(l_run, 32, WAVE);
     if (item.slot >= 0) {
-        // a part of a split block: unnormalised output, reference maximum and row sum go to the slot (all 128 rows of the
-        // block, clamped duplicates included: the merge kernel decides what is stored)
+        // a part of a split block: unnormalised output, reference maximum and row sum go to the slot (all 32 rows of
+        // the wavefront, clamped duplicates included: the merge kernel decides what is stored; wavefronts without rows left above)
         float* const slot = split_buf + (size_t)item.slot * AttnPartial<D>::SLOT_FLOATS;
         const int rs = wave * 32 + l32;  // row inside the block
 #pragma unroll

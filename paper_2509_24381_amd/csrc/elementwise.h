@@ -184,8 +184,8 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const bf16* __restrict__ w
 // barrier; they meet in LDS at the end of a tile.  The accumulators are emptied after every 64 k, and those sums after every
 // 256: short chains keep the error against 64 bits below that of the fp32 kernel above (3584: 1.0e-7 against 1.2e-7;
 // 8192: 1.2e-7 against 1.4e-7).
-// Measured on 152064 x 3584, us (LDS kernel, which streams the vocabulary once per 4 rows -> this one): 2 rows 205 -> 206,
-// 3: 271 -> 210, 8: 609 -> 217 (5.03 TB/s; a copy reaches 4.9), 10: 805 -> 218, 11: 860 -> 257 (a second group's operand comes
+// Measured on 152064 x 3584, us (LDS kernel, which streams the vocabulary once per 4 rows -> this one): 1 row 189 -> 206, 2: 205 -> 206,
+// 3: 271 -> 209, 8: 584 -> 207 (5.3 TB/s; a copy reaches 4.9), 10: 805 -> 217, 11: 860 -> 250 (a second group's operand comes
 // from L2 beside the stream).
 constexpr int LM_MFMA_ROWS = 3;   // from this many rows on
 constexpr int LM_GROUP = 10;      // rows per B operand

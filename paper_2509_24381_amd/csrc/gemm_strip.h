@@ -296,7 +296,7 @@ RS_DEVICE void load_row_factors(const GemmArgs& a, const int (&mj)[NJ], int half
     if (a.rowss == nullptr) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) row_val[j] = a.row_scale[mj[j]];
-    } else if (a.rowss_parts <= 32) {   // (32 strips at 2048 rows: one pass)
+    } else if (a.rowss_parts <= 32) {   // (28 strips at 2048 rows, 7B shape: one pass)
         load_row_sums<NJ, 16>(a, mj, half, row_val);
     } else {                            // (a part per unit from gemm_skinny.h: 112 at the 7B shape, two passes)
         load_row_sums<NJ, 32>(a, mj, half, row_val);

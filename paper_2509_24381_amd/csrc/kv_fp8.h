@@ -62,13 +62,6 @@ RS_DEVICE bf16x4 bf16x4_from_e4m3(uint32_t w, float scale) {
     return o;
 }
 
-RS_DEVICE bf16 bf16_from_e4m3(uint8_t code, float scale) {
-    const f32x2 v = __builtin_amdgcn_cvt_pk_f32_fp8((int)code, false);
-    return f32_to_bf16(v[0] * scale);
-}
-
-RS_DEVICE uint8_t e4m3_from_bf16(bf16 v, float inv) { return (uint8_t)(e4m3_pair(bf16_to_f32(v) * inv, 0.0f) & 0xffu); }
-
 RS_DEVICE size_t fp8_tile_offset(int cap, int c, int block, int D) { return ((size_t)c * (size_t)(cap >> 6) + (size_t)block) * 64 * D; }
 
 // The K (v = false) or V^T (v = true) tile of KV head c and 64-token block `block` of an 8-bit cache.  A page of a paged

@@ -339,6 +339,9 @@ rs_status launch_gemm(const rs_ctx* c, GemmArgs a, int splits, hipStream_t st, i
 // (358k) 26.2 -> 26.6, 72B 16 rows (131k) 47 -> 42, 64 rows (524k) 54 -> 70;  O 20 rows 19.1 -> 14.9, 64 rows 20.2 -> 18.3 but
 // the gate/up kernel then closes 112 parts of its row sums, 2 us;  down 20 rows 37.3 -> 35.6, 64 rows 41 -> 46;  layers as
 // narrow as the tiny shape gain up to 128 rows, and in the gate/up projection too (elsewhere that streams 272 MB: 5 TB/s).
+// Between the shapes the lines were drawn from, layer call, us, strip kernel only -> these rules, at 32 / 64 / 128 rows on 256 tokens:
+// hidden 512 44.6 / 46.2 / 48.4 -> 31.5 / 36.3 / 41.7; 1024 50.2 / 52.8 / 55.1 -> 36.7 / 42.6 / 50.0; 1536 (d 128) 68.3 / 70.5 / 75.8 ->
+// 56.8 / 65.1 / 72.0; 2048 67.4 / 69.1 / 74.0 -> 57.9 / 63.3 / 72.2; 72B 32 / 64 / 128 rows 424 / 441 / 475 -> 362 / 390 / 422.
 constexpr int SKINNY_ROWS = 128;
 bool skinny_qkv(const rs_ctx* c, int M, int K) { return c->gemm_narrow && M <= SKINNY_ROWS && (long)M * K <= 256 * 1024; }
 bool skinny_residual(const rs_ctx* c, int M, int K) { return c->gemm_narrow && (M <= 32 || (M <= SKINNY_ROWS && K <= 1024)); }
@@ -558,7 +561,6 @@ rs_status import_check(const rs_kv* kv, int layer, int n_tokens) {
     return RS_OK;
 }
 
-// Every check of one layer's call; changes nothing.  *total_out receives the number of rows.
 // Runs the export or import kernel over tokens [0, n): in one launch for a contiguous cache, in windows of
 // KV_PAGE_WINDOW blocks (whose page numbers ride in the kernel arguments) for a paged one.
 template <class Launch>
@@ -596,6 +598,7 @@ rs_status check_need(const PoolNeed& need) {
     return RS_OK;
 }
 
+// Every check of one layer's call; changes nothing.  *total_out receives the number of rows.
 rs_status prefill_check(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_kv* const* kvs, const int* lens, int R,
                         const void* x, void* y, void* ws, size_t ws_bytes, int* total_out, const int* positions3 = nullptr,
                         PoolNeed* pages_needed = nullptr) {
