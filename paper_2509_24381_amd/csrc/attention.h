@@ -122,13 +122,17 @@ struct AttnPartial {
 // behind the MFMAs that are left.  The four buffers are separate LDS objects so that the compiler can tell that the
 // fragment reads do not touch the buffers being filled.
 //
-// There is no running maximum in the loop.  A query's reference starts as the exact maximum of its first 32 keys (the lowest
-// finite number if they all score minus infinity) and stays until the probabilities of a half tile sum to more than ATT_RESCALE_SUM in one of the query's two lanes - the row
-// sum is needed anyway -; then (rarely: a request's first tiles) the half's exact maximum becomes the reference, the
-// accumulated output and row sum are rescaled and the half's probabilities are taken again from its raw scores, which are
-// still in registers.  Probabilities thus stay below ATT_RESCALE_SUM, which fp32 sums and bf16's relative rounding do not
-// mind, and the final division by the row sum cancels the reference.
-constexpr float ATT_RESCALE_SUM = 256.0f;
+// There is no running maximum in the loop.  A query's reference starts 2^ATT_HEADROOM_LOG2 above the exact maximum of its first 64
+// keys (at the lowest finite number if they all score minus infinity) and stays until the probabilities of a half tile sum to more
+// than ATT_RESCALE_SUM in one of the query's two lanes - the row sum is needed anyway -; then the reference moves as far above that
+// half's maximum, the accumulated output and row sum are rescaled and the half's probabilities are taken again from its raw scores,
+// which are still in registers.  Probabilities thus stay below ATT_RESCALE_SUM, which fp32 sums and bf16's relative rounding do not
+// mind, the final division by the row sum cancels the reference, and what the headroom costs is range at the far end: weights
+// below 2^-120 of the largest flush to zero.  A move stops all wavefronts of the workgroup at the next barrier, so it has to be
+// rare: without headroom, and with the first 32 keys alone, scores of a standard deviation of 3 (hidden 8192, weights N(0, 0.02))
+// moved some query of a wavefront in each of a request's first tiles.  72B shape, us: 4096 rows on 0 tokens 331 -> 276 (the exact
+// running maximum of the whole-tile kernel: 313), 1200 on 0: 45.7 -> 39.7, 2048 on 2000: 217 -> 206; 7B, 2048 on 0: 47.7 -> 46.0.
+constexpr float ATT_RESCALE_SUM = 256.0f, ATT_HEADROOM_LOG2 = 6.0f;
 
 template <int D, bool MAY_PAGE, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 2) void attn_prefill_pipelined_kernel(const ReqDesc* __restrict__ reqs,
@@ -274,6 +278,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_prefill_pipelined_kernel(c
     f32x16 s0, s1;            // raw scores of the two halves of a tile: register r of half hh holds key
                               // key0 + hh*32 + 16*(r>>3) + 8*half + (r&7)
     bf16x8 pf0[2], pf1[2];    // probabilities of the two halves, as the P.V product wants them
+    const float headroom = ATT_HEADROOM_LOG2 / scale_log2e;   // (raw scores)
     float m_ref;        // reference of this lane's query, raw scores (shared by both half-waves)
     float l_run = 0.0f; // running sum over THIS half-wave's keys
     const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
@@ -311,7 +316,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_prefill_pipelined_kernel(c
         if (__builtin_expect(over != 0, 0)) {
             const bool mine = ((((uint32_t)over | (uint32_t)(over >> 32)) >> l32) & 1u) != 0;   // either half-wave's sum
             const float m_half = half_max(sc);
-            const float m_new = mine ? fmaxf(m_ref, m_half) : m_ref;
+            const float m_new = mine ? fmaxf(m_ref, m_half + headroom) : m_ref;
             const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * scale_log2e);
             m_ref = m_new;
             l_run *= alpha;
@@ -336,10 +341,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_prefill_pipelined_kernel(c
     };
     first_scores(std::integral_constant<int, 0>{}, s0);
     first_scores(std::integral_constant<int, 1>{}, s1);
-    // The first key of a part is visible to every query of the block, but its score, and those of the other 31, may be minus
+    // The first key of a part is visible to every query of the block, but its score, and those of the other 63, may be minus
     // infinity (an infinite key element, an overflow): from the lowest finite reference such keys weigh nothing, and the first
     // finite score moves it.
-    m_ref = fmaxf(half_max(s0), -3.402823466e38f);
+    m_ref = fmaxf(fmaxf(half_max(s0), half_max(s1)) + headroom, -3.402823466e38f);
     l_run = all_exps(s0, pf0);
     __syncthreads();  // every wavefront is done with the first K tile: it may be overwritten
     fetch_k(k_buf0, kb0 + 2, pg_v);

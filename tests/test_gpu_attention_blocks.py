@@ -58,11 +58,11 @@ def test_ends_of_half_tiles_tiles_and_blocks(heads, prior, t_new, n_cu, monkeypa
 
 @pytest.mark.parametrize("n_cu", [None, "1"])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("at", [(31,), (32,), (45,), (64, 100), (63, 159, 160, 255)])
+@pytest.mark.parametrize("at", [(31,), (32,), (45,), (64, 100), (63, 159, 160, 255), (77, 109, 130, 150, 200, 229)])
 def test_scores_that_jump_inside_a_tile(d, at, n_cu, monkeypatch):
     """Single keys whose scores stand far above all before them (by up to 2^25 in the probabilities), in the first and in the
     second half of a tile: the reference has to move at that half, for the queries concerned, without touching the half that is
-    still to be multiplied.  Sharp distributions turn the absolute score error (2.4e-3 of a score of about 15) into the
+    still to be multiplied (keys of the first tile only raise where it starts).  Sharp distributions turn the absolute score error (2.4e-3 of a score of about 15) into the
     weights: 4e-2."""
     if n_cu:
         monkeypatch.setenv("RS_NCU", n_cu)
