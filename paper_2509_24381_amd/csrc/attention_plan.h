@@ -45,7 +45,7 @@ struct AttnPlanSettings {
 };
 struct AttnPlan {
     int waves = ATT_WAVES;
-    int cost = 0;   // estimated duration, in tiles (0 under RS_ATTN_SPLIT > 1)
+    int cost = 0;   // estimated duration, in tiles (0: nothing was weighed)
     std::vector<AttnItem> items;
     std::vector<AttnMergeItem> merges;
 };
@@ -218,6 +218,7 @@ inline void attn_place_pairs(std::vector<AttnItem>& blocks, int n_cu, int kv_hea
     blocks.swap(placed);
 }
 
+constexpr int ATT_SMALL_WALK_TILES = 64;
 constexpr int ATT_SMALL_PART_TILES = 24;
 
 // The call's work items.  One workgroup of eight wavefronts fills a compute unit, so a launch lasts as long as the fullest unit:
@@ -235,8 +236,13 @@ constexpr int ATT_SMALL_PART_TILES = 24;
 // 39.6, 128 on 8000 (32) 48.2 and 49.7; 32 / 8 heads of 64, 250 on 2000 (9) 20.2 and 18.3, on 8000 (33) 32.1 and 33.4.
 // So do calls of more small blocks than compute units, but no more than two to each, where the pairs of attn_pairs_cost end sooner:
 // the blocks of a prompt's first chunks differ in length, and cutting them costs more than pairing.  Attention step, us, blocks of
-// eight planned as above -> pairs: 7B, 2048 rows on 0 tokens 60.8 -> 52.0 (in heaviest-first order 55.1), on 2000 109 -> 99, on 6144
-// 207 -> 202; 32 / 8 heads of 64, 2048 rows on 0: 42.6 -> 35.0, on 2000: 77.4 -> 66.1.
+// eight planned as above -> pairs: 7B, 2048 rows on 0 tokens 55.0 -> 46.7 (in heaviest-first order 50.4), on 2000 101 -> 93, on 6144
+// 198 -> 193; 32 / 8 heads of 64, 2048 rows on 0: 40.9 -> 34.0, on 2000: 77.6 -> 65.0.
+// And calls of more small blocks than that whose walks have at most ATT_SMALL_WALK_TILES: with two blocks on a unit one's first loads
+// and last stores pass behind the other's products, which counts most where walks are short and blocks many; with long walks the
+// fetches count again.  Eight and four, us, with the longest walk: 72B, 16 requests of 200 rows on 200 tokens (7) 96.5 and 79.6, 32 of
+// 100 on 1000 (18) 175 and 154, 1200 rows on 0 (19) 47.0 and 42.0, 3000 on 0 (47) 175 and 165, 3000 on 1000 (63) 303 and 282, 4096 on 0
+// (64) 289 and 286, 2048 on 8000 (157) 526 and 539; 7B, 4096 on 0 (64) 123.5 and 123.6, on 1000 (80) 171 and 177.
 inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<AttnRequest>& reqs, int group, int kv_heads) {
     AttnPlan plan;
     long n_small = 0, most = 0;   // small blocks, parts they could be cut into
@@ -258,6 +264,10 @@ inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<Attn
     if (small) plan.waves = ATT_WAVES_SMALL;
     else blocks = attn_blocks(reqs, group, kv_heads, ATT_WAVES);
 
+    if (s.split <= 1 && (s.split == 1 || blocks[0].nkb < ATT_MIN_SPLIT_TILES) && n_small <= s.n_cu) {   // (nothing to weigh)
+        plan.items.swap(blocks);
+        return plan;
+    }
     AttnCut cut;
     const std::vector<AttnGroup> groups = attn_groups(blocks);
     const int longest = groups[0].n, n = (int)blocks.size();
@@ -282,16 +292,21 @@ inline AttnPlan plan_attention(const AttnPlanSettings& s, const std::vector<Attn
         c.cap = (int)((work + (long)n * ATT_COST_PART) * 102 / 100 / s.n_cu) + 1;
         if (c.cap >= ATT_MIN_PART_TILES && c.cap + ATT_MIN_PART_TILES <= longest) consider(c);
     }
-    if (plan.waves == ATT_WAVES && s.split <= 1 && n_small > s.n_cu && n_small <= 2 * s.n_cu) {
-        std::vector<AttnItem> pairs = attn_blocks(reqs, group, kv_heads, ATT_WAVES_SMALL);
-        const int cost = attn_pairs_cost(pairs, s.n_cu);
-        if (cost < plan.cost) {
-            if (!s.plain_order) attn_place_pairs(pairs, s.n_cu, kv_heads);
+    if (plan.waves == ATT_WAVES && s.split <= 1 && n_small > s.n_cu && (n_small <= 2 * s.n_cu || longest <= ATT_SMALL_WALK_TILES)) {
+        std::vector<AttnItem> small_blocks = attn_blocks(reqs, group, kv_heads, ATT_WAVES_SMALL);
+        const bool pairs = n_small <= 2 * s.n_cu;
+        const int cost = pairs ? attn_pairs_cost(small_blocks, s.n_cu) : attn_cost(attn_groups(small_blocks), AttnCut{}, 2 * s.n_cu);
+        if (!pairs || cost < plan.cost) {
+            if (pairs && !s.plain_order) attn_place_pairs(small_blocks, s.n_cu, kv_heads);
             plan.waves = ATT_WAVES_SMALL;
             plan.cost = cost;
-            plan.items.swap(pairs);
+            plan.items.swap(small_blocks);
             return plan;
         }
+    }
+    if (cut.cap == 0 && cut.parts == 0) {
+        plan.items.swap(blocks);
+        return plan;
     }
     plan.items.reserve(blocks.size() + ATT_SPLIT_SLOTS);
     int slots = 0;

@@ -95,7 +95,10 @@ def _check(case, plan):
     if waves == 4 and len(items) > n_cu and not merges:   # item k and item k + n_cu share a compute unit: ranks lone + k and n - 1 - k
         n, paired = len(items), len(items) - n_cu
         ranks = sorted(lens, reverse=True)
-        assert n <= 2 * n_cu and split <= 1
+        assert split <= 1
+        if n > 2 * n_cu:                   # heaviest first, on two places per compute unit
+            assert lens == ranks and lens[0] <= 64 and estimate == _list_schedule([n + 2 for n in lens], 2 * n_cu)
+            return
         assert lens == ranks[n_cu - paired: n_cu] + ranks[:n_cu - paired] + ranks[n_cu:][::-1]
         ends = [16 * b + 11 * (a - b) for a, b in zip(lens, lens[n_cu:])] + [11 * a for a in lens[paired:n_cu]]
         assert -(-max(ends) // 16) + 2 == estimate <= whole_cost
@@ -103,7 +106,9 @@ def _check(case, plan):
     assert lens == sorted(lens, reverse=True)
     if split == 1 or max(tiles.values()) < 16:
         assert split > 1 or not merges
-    if split <= 1:   # (tiles + 2 per whole item, + 4 per part, 4 and 1 per 36 parts for the merge)
+    if split <= 1 and estimate == 0:   # (too short to cut and no more than a block per compute unit: nothing was weighed)
+        assert not merges and len(items) <= n_cu and (split == 1 or (waves == 4 and lens[0] < 16))
+    elif split <= 1:   # (tiles + 2 per whole item, + 4 per part, 4 and 1 per 36 parts for the merge)
         cost = _list_schedule([nkb - kb0 + (4 if s >= 0 else 2) for *_, kb0, nkb, s in items], n_cu)
         assert cost + (4 + n_slots // 36 if merges else 0) == estimate <= whole_cost
 
@@ -152,6 +157,9 @@ def test_the_forms_are_reached(planner):
     assert any(v[-1] - v[0] > 1 for v in lens.values()) and len(share[1]) > 256
     assert small[0] == 4 and len(small[1]) <= 256 and equal[0] == 8
     assert cut_small[0] == 4 and cut_small[2] and max(i[4] - i[3] for i in cut_small[1]) == 9
+    for reqs, waves in (([(1200, 0)], 4), ([(4096, 0)], 4), ([(4096, 1)], 8), ([(2048, 8000)], 8), ([(200, 200)] * 16, 4)):
+        plan, = planner([(256, 0, 8, 8, reqs)])
+        assert plan[0] == waves and len(plan[1]) > 256
     for case in ((256, 0, 7, 4, [(2048, 0)]), (256, 0, 4, 8, [(2048, 2000)]), (7, 0, 2, 2, [(384, 0)]), (7, 0, 2, 2, [(384, 384)])):
         paired, plain = planner([case])[0], planner([case], plain=1)[0]
         assert paired[0] == plain[0] == 4 and case[0] < len(paired[1]) <= 2 * case[0]

@@ -39,8 +39,9 @@ def _attention_term(shape, reqs, name, tol, capacity):
         off += n
 
 
-# (calls that cannot fill the chip run blocks of 128 rows with four wavefronts, others 256 rows with eight: so does, planned for
-# one compute unit, every call of more than two small blocks, which the second request makes of all of these)
+# (blocks of 256 rows with eight wavefronts run in calls of more than two small blocks per compute unit with a walk of more than 64
+# tiles: planned for one unit, the second request makes that of all of these; without it they run blocks of 128 rows with four)
+LONG = (4200, 40)
 @pytest.mark.parametrize("n_cu", [None, "1"])
 @pytest.mark.parametrize("heads", [(4, 4, 64), (7, 1, 128), (8, 1, 64), (2, 2, 128)])
 @pytest.mark.parametrize("prior, t_new", [(0, 1), (0, 31), (0, 33), (0, 64), (31, 32), (32, 33), (63, 1), (64, 36), (65, 37),
@@ -52,8 +53,8 @@ def test_ends_of_half_tiles_tiles_and_blocks(heads, prior, t_new, n_cu, monkeypa
         monkeypatch.setenv("RS_NCU", n_cu)
     hq, hkv, d = heads
     shape = synth.LayerShape("edge", 256, hq, hkv, d, 256)
-    spec = [(prior, t_new)] + ([(0, 400)] if n_cu else [])
-    _attention_term(shape, _requests(shape, spec, 500 + prior), f"{heads} P={prior} T={t_new}", 2e-2, 512)
+    spec = [(prior, t_new)] + ([LONG] if n_cu else [])
+    _attention_term(shape, _requests(shape, spec, 500 + prior), f"{heads} P={prior} T={t_new}", 2e-2, 4352)
 
 
 @pytest.mark.parametrize("n_cu", [None, "1"])
@@ -72,7 +73,8 @@ def test_scores_that_jump_inside_a_tile(d, at, n_cu, monkeypatch):
         s = np.ones(prior, dtype=np.float32)
         s[list(at)] = 14.0
         return s
-    _attention_term(shape, _requests(shape, [(300, 90)], 600 + at[0], scale), f"d={d} jumps at {at}", 4e-2, 512)
+    spec = [(300, 90)] + ([LONG] if n_cu else [])
+    _attention_term(shape, _requests(shape, spec, 600 + at[0], scale), f"d={d} jumps at {at}", 4e-2, 4352)
 
 
 @pytest.mark.parametrize("n_cu", ["3", "7", "12", "40", "300"])
@@ -81,29 +83,28 @@ def test_key_ranges_cut_for_unequal_requests(n_cu, monkeypatch):
     equal parts, and parts of an even share with a rest, in blocks of eight and of four wavefronts."""
     monkeypatch.setenv("RS_NCU", n_cu)
     shape = synth.LayerShape("small128", 256, 4, 2, 128, 256)
-    spec = [(3000, 40), (0, 70), (900, 33), (1500, 128), (64, 1), (2047, 129)]
-    _attention_term(shape, _requests(shape, spec, 700), f"planned for {n_cu} units", 2e-2, 3200)
+    spec = [(5000, 40), (0, 70), (900, 33), (1500, 128), (64, 1), (2047, 129)]
+    _attention_term(shape, _requests(shape, spec, 700), f"planned for {n_cu} units", 2e-2, 5120)
 
 
-@pytest.mark.parametrize("n_cu, split, t_new", [(None, None, 30), ("1", None, 200), (None, "2", 30)])
+@pytest.mark.parametrize("n_cu, split, prior, t_new", [(None, None, 900, 30), ("1", None, 4200, 200), (None, "2", 900, 30)])
 @pytest.mark.parametrize("d", [64, 128])
-def test_keys_that_score_minus_infinity(d, n_cu, split, t_new, monkeypatch):
+def test_keys_that_score_minus_infinity(d, n_cu, split, prior, t_new, monkeypatch):
     """Cached keys whose score is minus infinity for every query weigh nothing, also where they are the first 32 keys of a
-    cache or of a part (those the reference starts from) and a whole later half tile."""
+    cache or of a part, the first 64 (those the reference starts from), and a whole later half tile."""
     for name, value in (("RS_NCU", n_cu), ("RS_ATTN_SPLIT", split)):
         if value:
             monkeypatch.setenv(name, value)
     shape = synth.LayerShape("minf", 256, 4, 2, d, 256)
-    prior = 900    # with 30 rows 15 tiles: in two parts the second starts at tile 7
     reqs = _requests(shape, [(prior, t_new)], 800)
-    for first in (0, 7 * 64, 600):
-        reqs[0].prior_k[first: first + 32, :, d // 2 - 1] = -np.inf
+    for first in (0, 7 * 64, 600):    # (15 tiles in two parts: the second starts at tile 7)
+        reqs[0].prior_k[first: first + (64 if first == 0 else 32), :, d // 2 - 1] = -np.inf
     # q is its bias alone; its slowest rotary pair is (1, 1), which the rotation at these positions leaves positive
     w = synth.layer_weights(shape, 41, qkv_bias=True, gains="uniform")
     w.wq, w.wd = np.zeros_like(w.wq), np.zeros_like(w.wd)
     bq = w.bq.reshape(shape.n_q_heads, d)
     bq[:, [d // 2 - 1, d - 1]] = 1.0
-    y, y_ref = _run_with_bias(shape, w, reqs, 1152)
+    y, y_ref = _run_with_bias(shape, w, reqs, 4416)
     check(f"d={d} keys at minus infinity", y - reqs[0].rows, y_ref - reqs[0].rows, tol=2e-2)
 
 
