@@ -210,10 +210,14 @@ DescSizes desc_sizes(const rs_ctx* c, int max_tokens, int max_requests) {
 // Strips per 256-row block of a GEMM with `units` 32-feature units: one workgroup per compute unit when there is enough
 // width, never more strips than units, and no more than keep the widest strip as narrow: further ones end no sooner and only
 // fetch the token operand once more each (us, strips as many as units of the chip -> this: QKV 2048 rows, 7B, 32 -> 29 strips
-// 71.5 -> 69.0, O 32 -> 28: 60.5 -> 58.6; layer call of 512 rows 331 -> 318, gate/up 128 -> 119 strips: 124 -> 118).
+// 71.5 -> 69.0, O 32 -> 28: 60.5 -> 58.6; layer call of 512 rows 331 -> 318, gate/up 128 -> 119 strips: 124 -> 118).  Strips of more
+// than 5 units are bound by their MFMAs rather than by that fetch: where hardly any has the full width, the others had better end
+// sooner (72B, 1200 rows, one strip of 51 with 6 units, the others with 5: down 43 -> 51 strips 503 -> 497; 1700 rows, 4 of 36 with 8:
+// O 32 -> 36 strips 209.5 -> 203, down 675 -> 663; but 7B, 1700 rows, O, 4 of 36 with 4 units: 28 strips 52.5, 36 strips 54.9).
 int strips_for(const rs_ctx* c, int tiles_m, int splits, int units) {
     const int most = std::max(1, std::min(units, c->n_cu / std::max(1, tiles_m * splits)));
     const int ups = (units + most - 1) / most;
+    if (ups > 5 && 6 * (units - most * (ups - 1)) < most) return most;
     return (units + ups - 1) / ups;
 }
 
