@@ -3,7 +3,8 @@
 // Work item = (request, KV head, block of 256 query rows).  The g = Hq/Hkv query heads that share a KV head are
 // stacked into the row dimension: row r of a request's chunk means (token r / g, head r % g), so each K / V tile
 // is fetched once per KV head rather than once per query head.  A 512-thread workgroup (8 wavefronts x 32 query
-// rows, one workgroup per compute unit) walks the request's cache in tiles of 64 keys.
+// rows, one workgroup per compute unit; or 256 threads and 128 rows, two per unit, see attention_plan.h) walks the request's cache in
+// tiles of 64 keys.
 //
 // The kernel computes transposed products so that every per-query quantity lives in one lane:
 //   S^T[key, query] = K[key, :] . Q[query, :]      MFMA "A" = K rows from LDS, "B" = Q rows held in registers
