@@ -8,61 +8,74 @@
 // One pass over x: inv_rms[row] = rsqrt(mean(x[row]^2) + eps) (fp32 sums; the factor is applied inside the next GEMM's
 // epilogue), and dst receives x in the GEMMs' token-operand layout: blocks of 32 tokens x 16 features, the two 8-feature
 // halves 512 bytes apart, tokens 16 bytes apart (rows of the last block past `rows` are left untouched: they are never
-// used).  One workgroup handles 8 tokens: 32 threads read 512 contiguous bytes of one token per step, and the 8 tokens'
-// 16-byte chunks of one (k-step, half) land in 128 contiguous bytes (one cache line).
-// The first workgroups of the grid copy the call's descriptors (requests, attention work items, cache blocks, row
+// used).  The first workgroups of the grid copy the call's descriptors (requests, attention work items, cache blocks, row
 // positions) from the pinned host buffer the library filled, which the device reads in place, into the workspace: the
 // later kernels of the call then find them in device memory, and no copy command sits between two calls (a runtime copy
 // of a few tens of KB costs a blit kernel of 13 us plus the gaps around it).
-// REDUCE = true is the same pass with the row taken not from x but from the split-K partial planes of the previous
+// With PLANES it is the same pass with the row taken not from x but from the split-K partial planes of the previous
 // layer's down projection (the layers of one rs_prefill_model_batch call): the row is
 // bf16(resid[m, :] + sum_s partial[s][m][:]), summed and rounded exactly as splitk_reduce_residual_kernel does, stored
 // row-major to y (the previous layer's output, this layer's residual input) and fragment-major to dst, and its 1/rms is
 // taken from the rounded values in the same order as from x - so a stack of layers run this way leaves the same bits
 // as the layers called one by one, without the previous layer's reduction kernel and this layer's pass over its output.
+//
+// The order of a row's sum is one for all forms and sizes (K and V of a token must not depend on the call, to the bit): 16-byte chunk
+// c of the row belongs to lane c % 256; a lane adds its chunks in ascending order, each 64 lanes add up in a butterfly, the four sums
+// in ascending order.  WPR = 4 spreads the 256 lanes over the four wavefronts of a workgroup, a row each: with few rows the kernel is a
+// chain of memory latencies, and this way every load of a row is in flight at once.  WPR = 1 gives a wavefront the whole row, eight
+// rows to a workgroup (their 16-byte chunks of one half k-step are one cache line).
+// Before, 32 lanes shared a row in 14 steps, whatever the call.  us per step between events, 7B shape in a stack (sums of 4 planes): 1 row
+// 14.0 -> 7.1, 64: 19.0 -> 7.9, 250: 19.7 -> 11.5, 512: 19.2 -> 15.4, 1000: 20.9 -> 19.5, 2048: 22.2 -> 21.9; 72B, 64 rows 30.9 -> 10.3.
 struct ReduceSource {
     const float* partial;   // [splits][rows][H] fp32
-    int splits;             // 2..4
+    int splits;             // 2..PLANES
     const bf16* resid;      // [rows, H] fragment-major
     bf16* y;                // [rows, H] row-major
 };
-template <bool REDUCE>
-__global__ __launch_bounds__(256) void rms_and_fragment_major_kernel(const bf16* __restrict__ x, bf16* __restrict__ dst,
+// PLANES = 0 takes the rows from x; else the most planes that are summed.
+constexpr int RMS_ROWS = 8;   // rows per workgroup with WPR = 1
+template <int PLANES, int WPR>
+__global__ __launch_bounds__(WPR == 4 ? 256 : 64 * RMS_ROWS) void rms_and_fragment_major_kernel(const bf16* __restrict__ x, bf16* __restrict__ dst,
                                                                      float* __restrict__ inv_rms, int rows, int H, float eps,
                                                                      const uint4* __restrict__ desc_src,
                                                                      uint4* __restrict__ desc_dst, int desc_chunks,
                                                                      ReduceSource red) {
+    static_assert(WPR == 1 || WPR == 4, "wavefronts per row");
+    constexpr bool REDUCE = PLANES > 0;
     // (the copying workgroups come first in the grid: their reads cross the host link, several microseconds each, and
     // should be under way while the row blocks stream; launched last they were the tail of the kernel)
-    const int desc_blocks = (desc_chunks + 255) >> 8;
+    const int desc_blocks = (desc_chunks + (int)blockDim.x - 1) / (int)blockDim.x;
     if ((int)blockIdx.x < desc_blocks) {
-        const int i = (int)blockIdx.x * 256 + (int)threadIdx.x;
+        const int i = (int)blockIdx.x * (int)blockDim.x + (int)threadIdx.x;
         if (i < desc_chunks) desc_dst[i] = desc_src[i];
         return;
     }
-    const int r = threadIdx.x >> 5, c = threadIdx.x & 31;
-    const int m = ((int)blockIdx.x - desc_blocks) * 8 + r;
-    const int mc = min(m, rows - 1);  // threads of rows past the end follow along (their shuffles are needed) and store nothing
-    const size_t frag_row = ((size_t)(mc >> 5) * (H >> 4) * 2 + c) * 512 + (mc & 31) * 16;   // chunk c of row mc, fragment-major
-    const char* src = REDUCE ? reinterpret_cast<const char*>(red.resid) + frag_row
-                             : reinterpret_cast<const char*>(x + (size_t)mc * H) + c * 16;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = WPR == 4 ? (int)blockIdx.x - desc_blocks : ((int)blockIdx.x - desc_blocks) * RMS_ROWS + wave;
+    if (m >= rows) return;   // (WPR = 4: never; WPR = 1: the whole wavefront)
+    // chunk k of a pass of 256: WPR = 4 has pass u of the wavefront's 64 lanes in flight as chunk u, WPR = 1 the four quarters of one pass
+    constexpr int U = WPR == 4 ? 2 : 4;
+    constexpr int SPAN = WPR == 4 ? U * 256 : 256, STRIDE = WPR == 4 ? 256 : 64;
+    const int c = WPR == 4 ? wave * 64 + lane : lane;
+    const size_t frag_row = (size_t)(m >> 5) * (H >> 4) * 1024 + (size_t)(m & 31) * 16;   // row m in a fragment-major matrix; chunks are 512 bytes apart
+    const char* src = REDUCE ? reinterpret_cast<const char*>(red.resid) + frag_row : reinterpret_cast<const char*>(x + (size_t)m * H);
     constexpr size_t SRC_STEP = REDUCE ? 512 : 16;   // bytes from one 16-byte chunk of the row to the next in the source
-    char* out = reinterpret_cast<char*>(dst) + ((size_t)(m >> 5) * (H >> 4) * 2 + c) * 512 + (m & 31) * 16;
-    float ss = 0.0f;
-    const int chunks = H >> 3;  // 16-byte chunks per row; a step covers 32 of them (256 features = 16 k-steps x 2 halves)
-    constexpr int U = 4;   // chunks in flight per thread (eight measured no faster for either form)
-    for (int c0 = 0; c0 < chunks; c0 += U * 32) {
+    char* out = reinterpret_cast<char*>(dst) + frag_row;
+    float ss[WPR == 4 ? 1 : 4] = {};
+    const int chunks = H >> 3;  // 16-byte chunks per row
+    for (int c0 = c; c0 < chunks; c0 += SPAN) {
         uint4 v[U];
-        f32x4 part[REDUCE ? U : 1][REDUCE ? 4 : 1][2];   // [chunk in flight][plane][half of the 8 features]
+        f32x4 part[REDUCE ? U : 1][REDUCE ? PLANES : 1][2];   // [chunk in flight][plane][half of the 8 features]
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (c0 + u * 32 + c < chunks) {
-                v[u] = ld_global_16(src + (size_t)(c0 + u * 32) * SRC_STEP);
+            if (c0 + u * STRIDE < chunks) {
+                v[u] = ld_global_16(src + (size_t)(c0 + u * STRIDE) * SRC_STEP);
                 if constexpr (REDUCE) {
 #pragma unroll
-                    for (int sp = 0; sp < 4; ++sp)
+                    for (int sp = 0; sp < PLANES; ++sp)
                         if (sp < red.splits) {
-                            const float* pp = red.partial + ((size_t)sp * rows + mc) * H + (size_t)(c0 + u * 32 + c) * 8;
+                            const float* pp = red.partial + ((size_t)sp * rows + m) * H + (size_t)(c0 + u * STRIDE) * 8;
                             part[u][sp][0] = *reinterpret_cast<const f32x4*>(pp);
                             part[u][sp][1] = *reinterpret_cast<const f32x4*>(pp + 4);
                         }
@@ -70,30 +83,38 @@ __global__ __launch_bounds__(256) void rms_and_fragment_major_kernel(const bf16*
             }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (c0 + u * 32 + c < chunks) {
+            if (c0 + u * STRIDE < chunks) {
                 bf16x8 h = as_bf16x8(v[u]);
                 if constexpr (REDUCE) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         float f = bf16_to_f32(h[e]);
 #pragma unroll
-                        for (int sp = 0; sp < 4; ++sp)
+                        for (int sp = 0; sp < PLANES; ++sp)
                             if (sp < red.splits) f += part[u][sp][e >> 2][e & 3];
                         h[e] = f32_to_bf16(f);
                     }
-                    if (m < rows) st_global_16(reinterpret_cast<char*>(red.y + (size_t)m * H) + (size_t)(c0 + u * 32 + c) * 16, as_uint4(h));
+                    st_global_16(reinterpret_cast<char*>(red.y + (size_t)m * H) + (size_t)(c0 + u * STRIDE) * 16, as_uint4(h));
                 }
+                float& s = ss[WPR == 4 ? 0 : u];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float f = bf16_to_f32(h[e]);
-                    ss += f * f;
+                    s = __builtin_fmaf(f, f, s);
                 }
-                if (m < rows) st_global_16(out + (size_t)(c0 + u * 32) * 512, as_uint4(h));
+                st_global_16(out + (size_t)(c0 + u * STRIDE) * 512, as_uint4(h));
             }
     }
-#pragma unroll
-    for (int off = 16; off > 0; off >>= 1) ss += __shfl_xor(ss, off, WAVE);
-    if (c == 0 && m < rows) inv_rms[m] = rsqrtf(ss / (float)H + eps);
+    if constexpr (WPR == 4) {
+        __shared__ float part_sum[4];
+        const float t = wave_sum(ss[0]);
+        if (lane == 0) part_sum[wave] = t;
+        __syncthreads();
+        if (threadIdx.x == 0) inv_rms[m] = rsqrtf((((part_sum[0] + part_sum[1]) + part_sum[2]) + part_sum[3]) / (float)H + eps);
+    } else {
+        const float t0 = wave_sum(ss[0]), t1 = wave_sum(ss[1]), t2 = wave_sum(ss[2]), t3 = wave_sum(ss[3]);
+        if (lane == 0) inv_rms[m] = rsqrtf((((t0 + t1) + t2) + t3) / (float)H + eps);
+    }
 }
 
 // ---------------------------------------------------------------- first-token head: final RMSNorm + vocabulary projection

@@ -263,6 +263,12 @@ int choose_splitk(const rs_ctx* c, int M, int units, int k_steps) {
     return best;
 }
 
+constexpr int MAX_PLANES = 4;   // split-K partial planes
+
+// Rows up to which the first kernel gives a row a workgroup instead of a wavefront.
+// us per step, 7B shape in a stack: 250 rows 16.6 (a wavefront) -> 10.6, 512: 18.2 -> 15.2, 640: 17.5 -> 16.6, 800: 19.1 -> 21.1.
+constexpr int RMS_FEW_ROWS = 704;
+
 struct WorkspaceLayout {
     size_t qkv, xf, attn, r, act, partial, attn_split, inv_rms1, inv_rms2, rowss, desc, total;
 };
@@ -831,17 +837,22 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     tm.begin(RS_STEP_ROW_RMS);
     // and, in the same pass, x in the GEMMs' fragment-major token-operand layout
     const int desc_chunks = (int)(ds.total / 16);
-    if (pending_in && pending_in->splits > 0) {
-        // (the pending sum reads the previous layer's r and partial planes, which this layer overwrites only later)
-        ReduceSource red{pending_in->partial, pending_in->splits, pending_in->resid, pending_in->out};
-        hipLaunchKernelGGL(rms_and_fragment_major_kernel<true>, dim3((T + 7) / 8 + (desc_chunks + 255) / 256), dim3(256), 0, st, xb, xf,
+    // (the pending sum reads the previous layer's r and partial planes, which this layer overwrites only later)
+    const bool pending = pending_in && pending_in->splits > 0;
+    const ReduceSource red = pending ? ReduceSource{pending_in->partial, pending_in->splits, pending_in->resid, pending_in->out} : ReduceSource{};
+    const auto first_kernel = [&](auto planes, auto wpr) {
+        constexpr int WPR = decltype(wpr)::value, THREADS = WPR == 4 ? 256 : 64 * RMS_ROWS;
+        hipLaunchKernelGGL((rms_and_fragment_major_kernel<decltype(planes)::value, WPR>),
+                           dim3((WPR == 4 ? T : (T + RMS_ROWS - 1) / RMS_ROWS) + (desc_chunks + THREADS - 1) / THREADS), dim3(THREADS), 0, st, xb, xf,
                            inv_rms1, T, H, f.rms_eps, reinterpret_cast<const uint4*>(ctx->pinned_dev[slot]),
                            reinterpret_cast<uint4*>(wsb + L.desc), desc_chunks, red);
-    } else {
-        hipLaunchKernelGGL(rms_and_fragment_major_kernel<false>, dim3((T + 7) / 8 + (desc_chunks + 255) / 256), dim3(256), 0, st, xb, xf,
-                           inv_rms1, T, H, f.rms_eps, reinterpret_cast<const uint4*>(ctx->pinned_dev[slot]),
-                           reinterpret_cast<uint4*>(wsb + L.desc), desc_chunks, ReduceSource{});
-    }
+    };
+    const auto first_kernel_planes = [&](auto wpr) {
+        if (!pending) first_kernel(std::integral_constant<int, 0>{}, wpr);
+        else first_kernel(std::integral_constant<int, MAX_PLANES>{}, wpr);
+    };
+    if (T <= RMS_FEW_ROWS) first_kernel_planes(std::integral_constant<int, 4>{});
+    else first_kernel_planes(std::integral_constant<int, 1>{});
     RS_HIP(hipGetLastError());
     if (use % RING_CHECKPOINT == RING_CHECKPOINT - 1) {
         RS_HIP(hipEventRecord(ctx->slot_done[slot], st));
