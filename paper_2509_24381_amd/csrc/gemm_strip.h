@@ -67,6 +67,7 @@ struct GemmArgs {
 };
 
 constexpr int GS_BM = 256;
+constexpr int GS_ONCE = 2;                           // cache policy (nt) of weights that one workgroup reads once
 constexpr int GS_BK = 64;                            // K per pipeline step
 // The kernel comes in two geometries.  Wide: tiles of up to 8 units, a ring of 4 slots of 32 KB (three steps of weight
 // look-ahead), token fragments loaded one step ahead, one workgroup per compute unit with up to 512 registers per lane.
@@ -328,7 +329,8 @@ RS_DEVICE void tie_wait_lgkm0(bf16x8 (&w)[NT]) {
 // strips and tiles are made of groups of WU units.  WT = 2 serves the narrow launches of short calls: a step then moves
 // 16 KB of token fragments and 8 KB of weights through the vector-memory pipe for two units, where 256 rows x one unit
 // move 32 + 4 KB for one.
-template <int EPI, int MAXNT = GS_MAX_NT, int SLOTS = GS_SLOTS, int OCC = 1, int XD = 1, int WT = 4>
+// ONCE: the call has one block of rows, every weight is read by one workgroup: the loads say so (nt), and HBM streams faster.
+template <int EPI, int MAXNT = GS_MAX_NT, int SLOTS = GS_SLOTS, int OCC = 1, int XD = 1, int WT = 4, bool ONCE = false>
 __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     constexpr int WU = 4 / WT;
     constexpr int BM = 64 * WT;
@@ -445,7 +447,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
         constexpr int k = decltype(kc)::value;
         const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + d_slot + wave * 1024 + k * 4096);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr)(uintptr_t)dst, 16, d_vw + k * w_step,
-                                                 __builtin_amdgcn_readfirstlane(d_wsoff + d_koff), 0, 0);
+                                                 __builtin_amdgcn_readfirstlane(d_wsoff + d_koff), 0, ONCE ? GS_ONCE : 0);
     };
 
     const bool wave_has_rows = m0 + tw * 64 < a.M;   // (uniform per wavefront)

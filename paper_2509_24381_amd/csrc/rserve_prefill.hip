@@ -265,6 +265,12 @@ int choose_splitk(const rs_ctx* c, int M, int units, int k_steps) {
 
 constexpr int MAX_PLANES = 4;   // split-K partial planes
 
+// Weights that one workgroup reads once, and that the L2s (32 MB together) could not keep from one call to the next, are loaded with the
+// streaming hint (GS_ONCE): gate/up of 64 rows, 7B (272 MB), 54.2 -> 50.1 us between events, 72B (969 MB) 182 -> 160; smaller ones lose
+// by it (tiny layer, gate/up of 200 rows, 1 MB: 9.3 -> 10.1).
+constexpr size_t STREAM_BYTES = (size_t)32 << 20;
+bool streams_once(int tiles_m, int units, int steps) { return tiles_m == 1 && (size_t)units * steps * 4096 >= STREAM_BYTES; }
+
 // Rows up to which the first kernel gives a row a workgroup instead of a wavefront.
 // us per step, 7B shape in a stack: 250 rows 16.6 (a wavefront) -> 10.6, 512: 18.2 -> 15.2, 640: 17.5 -> 16.6, 800: 19.1 -> 21.1.
 constexpr int RMS_FEW_ROWS = 704;
@@ -329,6 +335,7 @@ rs_status launch_gemm(const rs_ctx* c, GemmArgs a, int splits, hipStream_t st, i
             return RS_OK;
         }
     }
+    constexpr bool once_epi = EPI == EPI_SWIGLU || EPI == EPI_PARTIAL;
     a.strips = strips_for(c, a.tiles_m, splits, units);
     if (columns_out) *columns_out = a.strips;
     dim3 grid(a.tiles_m * a.strips, splits);
@@ -337,6 +344,8 @@ rs_status launch_gemm(const rs_ctx* c, GemmArgs a, int splits, hipStream_t st, i
     if (use_narrow(c, a.tiles_m, splits, units, EPI == EPI_QKV_ROPE ? 2 : 0))
         hipLaunchKernelGGL((gemm_strip_kernel<EPI, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD>), grid, dim3(256),
                            GS_NARROW_LDS_BYTES, st, a);
+    else if (once_epi && streams_once(a.tiles_m, units, steps))
+        hipLaunchKernelGGL((gemm_strip_kernel<EPI, GS_MAX_NT, GS_SLOTS, 1, 1, 4, once_epi>), grid, dim3(256), GS_LDS_BYTES, st, a);
     else
         hipLaunchKernelGGL(gemm_strip_kernel<EPI>, grid, dim3(256), GS_LDS_BYTES, st, a);
     RS_HIP(hipGetLastError());
@@ -1017,6 +1026,8 @@ rs_status rs_ctx_create(const rs_layer_cfg* cfg, rs_ctx** out) {
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_RESIDUAL, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_SWIGLU, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_PARTIAL, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_SWIGLU, GS_MAX_NT, GS_SLOTS, 1, 1, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_PARTIAL, GS_MAX_NT, GS_SLOTS, 1, 1, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
     if (e != hipSuccess) return cleanup(fail(RS_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e)));
     *out = c;
     return RS_OK;
