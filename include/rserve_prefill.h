@@ -99,8 +99,7 @@ typedef struct rs_kv rs_kv;   /* one request's KV cache over n_layers layers; ho
  * not.  Not for production use, and they may change without notice:
  *   RS_SPLITK=n      K ranges of the residual projections (1..4; default: a cost model per call)
  *   RS_NCU=n         compute-unit count the GEMM strips are sized for (default: the device's)
- *   RS_NARROW=0      neither the GEMM kernel for few rows nor the geometry for strips of at most two units;  RS_NARROW_TM=n  use it up to n token blocks
- *   RS_PAIRS=0       never two wavefronts per pair of units in that geometry
+ *   RS_NARROW=0      every projection on the strip GEMM: neither tiles (calls of up to 1024 rows) nor the kernel for few rows
  *   RS_ATTN_SPLIT=n  parts every attention block's key range is cut into (1 = never; default: decided per call)
  *   RS_ATTN_ORDER=plain  attention blocks that share compute units stay in heaviest-first order (default: where two fit a
  *                    unit, the heaviest run alone on theirs and the others are paired heavy with light) */

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64 * TW * KW, (TW * KW + 3) / 4) void gemm_skinny_k
         });
     }
     if constexpr (KW == 1) {
-        gemm_epilogue<EPI, 1, 1, 1>(a, acc, tw * 32, unit, half, l32, split, row_val);
+        gemm_epilogue<EPI, 1, 1>(a, acc, tw * 32, unit, half, l32, split, row_val);
     } else {
 #pragma unroll
         for (int j = 0; j < TB; ++j)
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(64 * TW * KW, (TW * KW + 3) / 4) void gemm_skinny_k
             for (int k = 0; k < KW; ++k) v += skinny_red[(size_t)((k * TB + wave) * 16 + r) * 64 + lane];
             sum[0][0][r] = v;
         }
-        gemm_epilogue<EPI, 1, 1, 1>(a, sum, wave * 32, unit, half, l32, split, row_val);
+        gemm_epilogue<EPI, 1, 1>(a, sum, wave * 32, unit, half, l32, split, row_val);
         if constexpr (EPI == EPI_RESIDUAL) {
             if (a.rowss != nullptr) {   // (as in gemm_strip_kernel: one part per unit here)
                 const float ss = row_val[0] + __shfl_xor(row_val[0], 32, WAVE);

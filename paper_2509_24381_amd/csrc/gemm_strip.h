@@ -18,7 +18,7 @@
 // tile boundaries, so the next tile's first slabs arrive while the current tile's epilogue runs.  A unit's k-step is
 // one contiguous kilobyte in memory and in the slot, which the DMA fills and the fragment reads walk in lane order: no bank
 // conflicts.  (Row-major weights with swizzled slots ran as fast here; gemm_skinny.h needs this order.)  The token rows go
-// global -> registers, XD steps ahead.  Rows past M fall outside the buffer resource and read as zeros.
+// global -> registers, a step ahead.  Rows past M fall outside the buffer resource and read as zeros.
 //
 // The compiler cannot see LDS written by DMA (it would wait for every outstanding load before any LDS read), so the
 // fragment reads are inline ds_read_b128 and the wait for the next weight step is explicit: loads retire in order and
@@ -44,9 +44,8 @@ struct GemmArgs {
     bf16* out;          // [M, ldo], row-major or (out_frag) fragment-major of width ldo
     const bf16* bias;   // [N] in the original feature order, or null
     const bf16* resid;  // [M, ldr], row-major or (resid_frag) fragment-major of width ldr
-    float* rowss;       // EPI_RESIDUAL (output, or null): [parts][M], one sum of squares per row and workgroup column - a strip
-                        // (times the wavefronts that split its units) - over the features of the stored row that the column
-                        // owns; parts = rowss_parts(...) of this launch.  EPI_SWIGLU (input, or null): the same array as the
+    float* rowss;       // EPI_RESIDUAL (output, or null): [parts][M], one sum of squares per row and column of work - a strip, or
+                        // the units of a wavefront - over the features of the stored row that the column owns; parts = rowss_parts(...) of this launch.  EPI_SWIGLU (input, or null): the same array as the
                         // residual GEMM in front left it; the row factor is then rsqrt(sum of the parts / K + rms_eps)
                         // instead of row_scale[m]
     int rowss_parts;    // EPI_SWIGLU: number of parts in rowss
@@ -69,22 +68,13 @@ struct GemmArgs {
 constexpr int GS_BM = 256;
 constexpr int GS_ONCE = 2;                           // cache policy (nt) of weights that one workgroup reads once
 constexpr int GS_BK = 64;                            // K per pipeline step
-// The kernel comes in two geometries.  Wide: tiles of up to 8 units, a ring of 4 slots of 32 KB (three steps of weight
-// look-ahead), token fragments loaded one step ahead, one workgroup per compute unit with up to 512 registers per lane.
-// Narrow, for launches whose strips hold at most 2 units (few token rows spread over the whole chip): a step is then only
-// 8 or 16 MFMAs per wavefront, shorter than the memory latency one step of look-ahead would have to cover, so the ring has
-// 8 slots of 8 KB (seven steps of weight look-ahead) and the token fragments are loaded three steps ahead (the accumulators
-// leave the registers for that).  Both are built for one wavefront per SIMD (OCC = 1: 512 registers per lane); with the
-// budget of two per SIMD the narrow kernel spills its token fragments, and two workgroups per compute unit measured no
-// faster.
-constexpr int GS_MAX_NT = 8;                         // units per tile (wide)
+// Tiles of up to 8 units, a ring of 4 slots of 32 KB (three steps of weight look-ahead), token fragments loaded one step ahead, one
+// workgroup per compute unit with up to 512 registers per lane.  (Calls of some dozens to hundreds of rows, whose strips would hold one
+// or two units, run in gemm_tile.h; a narrow form of this kernel with eight slots and tokens three steps ahead, which they ran in before,
+// fetches two to three times what the tiles do.)
+constexpr int GS_MAX_NT = 8;                         // units per tile
 constexpr int GS_SLOTS = 4;
-constexpr int GS_NARROW_NT = 2;
-constexpr int GS_NARROW_SLOTS = 8;
-constexpr int GS_NARROW_XD = 3;                      // steps the token fragments are loaded ahead (narrow)
-constexpr int gs_lds_bytes(int max_nt, int slots) { return slots * max_nt * 32 * GS_BK * 2; }
-constexpr int GS_LDS_BYTES = gs_lds_bytes(GS_MAX_NT, GS_SLOTS);                    // 128 KB
-constexpr int GS_NARROW_LDS_BYTES = gs_lds_bytes(GS_NARROW_NT, GS_NARROW_SLOTS);   // 64 KB
+constexpr int GS_LDS_BYTES = GS_SLOTS * GS_MAX_NT * 32 * GS_BK * 2;   // 128 KB
 
 // silu(g) = g / (1 + 2^(-g log2 e)) with the raw v_exp_f32 / v_rcp_f32 instructions (1 ulp each; the result is rounded to bf16)
 RS_DEVICE float silu_f32(float g) {
@@ -122,9 +112,10 @@ RS_DEVICE u32x4 pair_runs(bf16x4 even_run, bf16x4 odd_run) {
 // the pipeline's in-flight fragments to scratch memory to make room (about 100 dwords per lane and tile, written and read
 // back).  The empty asm statement at the top of each unit's iteration pins that unit's tile in accumulation registers up to
 // there, so the copies are made 16 registers at a time and nothing spills.
-template <int EPI, int NT, int USTRIDE = 1, int NJ = 2>
+template <int EPI, int NT, int NJ = 2>
 RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_base, int unit0, int half, int l32, int split,
-                             float (&row_val)[NJ]) {
+                             float (&row_val)[NJ], int live = NT) {
+    // only the first `live` units are stored (a tile may reach past the last unit);
     // row_val[j], one value per lane and token block j: EPI_SWIGLU reads the row's factor 1/rms there; EPI_RESIDUAL adds
     // the sum of squares of what it stores of the row (this lane's 16 of each unit's 32 features)
     constexpr int RSRC_FLAGS = 0x00020000;
@@ -140,6 +131,7 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
             const uint32_t oblk = (uint32_t)(m >> 5) * (uint32_t)(a.ldo >> 4) * 1024u + (uint32_t)l32 * 16u + (uint32_t)half * 512u;
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
+                if (i >= live) break;
                 asm volatile("" : "+a"(acc[i][j]));
                 bf16x4 o[2];
 #pragma unroll
@@ -148,7 +140,7 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
                     for (int e = 0; e < 4; ++e)
                         o[q][e] = f32_to_bf16(silu_f32(acc[i][j][4 * q + e] * sc) * (acc[i][j][8 + 4 * q + e] * sc));
                 // lower lanes: features 16u..16u+7 (first half of the k-step), upper lanes: 16u+8..16u+15 (second half)
-                __builtin_amdgcn_raw_buffer_store_b128(pair_runs(o[0], o[1]), r_out, oblk + (uint32_t)(unit0 + i * USTRIDE) * 1024u, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(pair_runs(o[0], o[1]), r_out, oblk + (uint32_t)(unit0 + i) * 1024u, 0, 0);
             }
         } else if constexpr (EPI == EPI_QKV_ROPE) {
             const __amdgpu_buffer_rsrc_t r_out = __builtin_amdgcn_make_buffer_rsrc((void*)a.out, 0, a.M * a.ldo * 2, RSRC_FLAGS);
@@ -163,8 +155,9 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
             const uint32_t orow = (uint32_t)m * (uint32_t)a.ldo * 2u;
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
+                if (i >= live) break;
                 asm volatile("" : "+a"(acc[i][j]));
-                const int gu = unit0 + i * USTRIDE;
+                const int gu = unit0 + i;
                 if (gu * 32 < a.rope_cols) {
                     // rows 0..15 of the unit are features f..f+15 of the head's first half, rows 16..31 their partners
                     const int uh = gu & ((1 << uph_shift) - 1);
@@ -228,13 +221,15 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
                 __builtin_amdgcn_make_buffer_rsrc((void*)(a.partial + (size_t)split * a.M * a.N), 0, a.M * a.N * 4, RSRC_FLAGS);
             const uint32_t orow = (uint32_t)m * (uint32_t)a.N * 4u;
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
+            for (int i = 0; i < NT; ++i) {
+                if (i >= live) break;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int n = (unit0 + i * USTRIDE) * 32 + 8 * q + 4 * half;
+                    const int n = (unit0 + i) * 32 + 8 * q + 4 * half;
                     f32x4 o = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), r_out, orow + (uint32_t)n * 4u, 0, 0);
                 }
+            }
         } else {
             // residual input and output are row-major [M, ld] or fragment-major (blocks of 32 tokens, padded to whole blocks)
             const __amdgpu_buffer_rsrc_t r_out =
@@ -243,12 +238,13 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
                 __builtin_amdgcn_make_buffer_rsrc((void*)a.resid, 0, (a.resid_frag ? m_pad : a.M) * a.ldr * 2, RSRC_FLAGS);
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
+                if (i >= live) break;
                 asm volatile("" : "+a"(acc[i][j]));
                 float ss = 0.0f;
                 bf16x4 o[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const uint32_t n = (uint32_t)((unit0 + i * USTRIDE) * 32 + 8 * q + 4 * half);
+                    const uint32_t n = (uint32_t)((unit0 + i) * 32 + 8 * q + 4 * half);
                     const uint32_t roff = a.resid_frag ? frag_offset_bytes(m, n, a.ldr) : ((uint32_t)m * (uint32_t)a.ldr + n) * 2u;
                     const bf16x4 r4 = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(r_res, roff, 0, 0));
 #pragma unroll
@@ -260,7 +256,7 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
                 }
 #pragma unroll
                 for (int pr = 0; pr < 2; ++pr) {  // lower lanes store the even 8-feature group of the pair, upper lanes the odd one
-                    const uint32_t n = (uint32_t)((unit0 + i * USTRIDE) * 32 + 16 * pr + 8 * half);
+                    const uint32_t n = (uint32_t)((unit0 + i) * 32 + 16 * pr + 8 * half);
                     const uint32_t ooff = a.out_frag ? frag_offset_bytes(m, n, a.ldo) : ((uint32_t)m * (uint32_t)a.ldo + n) * 2u;
                     __builtin_amdgcn_raw_buffer_store_b128(pair_runs(o[2 * pr], o[2 * pr + 1]), r_out, ooff, 0, 0);
                 }
@@ -324,20 +320,10 @@ RS_DEVICE void tie_wait_lgkm0(bf16x8 (&w)[NT]) {
 #pragma unroll
     for (int i = 1; i < NT; ++i) asm volatile("" : "+v"(w[i]));
 }
-// WT of the 4 wavefronts are stacked along the tokens (64 rows each: a workgroup owns a block of 64 WT rows); the other
-// WU = 4 / WT ways they split the units of a tile between them (wavefront (tw, uw) multiplies units uw, uw + WU, ...), and
-// strips and tiles are made of groups of WU units.  WT = 2 serves the narrow launches of short calls: a step then moves
-// 16 KB of token fragments and 8 KB of weights through the vector-memory pipe for two units, where 256 rows x one unit
-// move 32 + 4 KB for one.
 // ONCE: the call has one block of rows, every weight is read by one workgroup: the loads say so (nt), and HBM streams faster.
-template <int EPI, int MAXNT = GS_MAX_NT, int SLOTS = GS_SLOTS, int OCC = 1, int XD = 1, int WT = 4, bool ONCE = false>
-__global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
-    constexpr int WU = 4 / WT;
-    constexpr int BM = 64 * WT;
-    static_assert(WT == 2 || WT == 4, "wavefronts along the tokens");
-    static_assert(MAXNT % WU == 0, "a tile is a whole number of unit groups");
-    static_assert(WT == 4 || MAXNT == 2, "wavefronts split units in the narrow geometry only");
-    constexpr int XB = XD + 1;   // token-fragment buffers: the step being multiplied and the XD steps in flight behind it
+template <int EPI, bool ONCE = false>
+__global__ __launch_bounds__(256, 1) void gemm_strip_kernel(GemmArgs a) {
+    constexpr int MAXNT = GS_MAX_NT, SLOTS = GS_SLOTS;
     constexpr int SLOT_BYTES = MAXNT * 32 * GS_BK * 2;   // up to 32 MAXNT weight rows of one step
     constexpr int RING_BYTES = SLOTS * SLOT_BYTES;       // a power of two
     constexpr int AHEAD = SLOTS - 1;                     // steps the weight stream runs ahead of the multiply
@@ -348,7 +334,6 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tw = wave & (WT - 1), uw = wave / WT;   // place along the tokens and among the unit-splitting wavefronts
     const int half = lane >> 5;
     const int l32 = lane & 31;
 
@@ -362,18 +347,16 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     const int logical = (xcd < wrem ? xcd * (wbase + 1) : wrem * (wbase + 1) + (xcd - wrem) * wbase) + loc;
     const int tm = logical % a.tiles_m;
     const int strip = logical / a.tiles_m;
-    const int m0 = tm * BM;
+    const int m0 = tm * GS_BM;
 
     // ---- the strip's units and its tiles (sizes differ by at most one, smaller ones first: the load stream then never
     //      issues fewer loads per step than the waits of the tile being multiplied assume)
-    //      (counted in groups of WU units from here to the tile loop)
-    const int nu = (a.N >> 5) / WU;
+    const int nu = a.N >> 5;
     const int ub = nu / a.strips, ur = nu % a.strips;
     const int u_first = strip * ub + min(strip, ur);
     const int u_count = ub + (strip < ur ? 1 : 0);
-    if (u_count == 0) return;  // more strips than groups: never launched this way, and uniform for the whole workgroup
-    constexpr int MAXG = MAXNT / WU;
-    const int ntiles = (u_count + MAXG - 1) / MAXG;
+    if (u_count == 0) return;  // more strips than units: never launched this way, and uniform for the whole workgroup
+    const int ntiles = (u_count + MAXNT - 1) / MAXNT;
     const int tb = u_count / ntiles;
     const int n_small = ntiles - u_count % ntiles;  // tiles [0, n_small) have tb units, the rest tb + 1
 
@@ -393,11 +376,11 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     const uint32_t x_block_bytes = (uint32_t)(a.K >> 4) * 1024u;  // one block of 32 tokens, all of K
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, ((a.M + 31) >> 5) * (int)x_block_bytes, 0x00020000);
-    const uint32_t xv0 = (uint32_t)((m0 >> 5) + tw * 2) * x_block_bytes + (uint32_t)half * 512u + (uint32_t)l32 * 16u;
+    const uint32_t xv0 = (uint32_t)((m0 >> 5) + wave * 2) * x_block_bytes + (uint32_t)half * 512u + (uint32_t)l32 * 16u;
     const uint32_t xv1 = xv0 + x_block_bytes;
     uint32_t x_koff = xk0;  // byte offset of the next step to load inside a token block
     int x_s = 0;
-    bf16x8 xbuf[XB][2][4];
+    bf16x8 xbuf[2][2][4];
     auto load_x = [&](auto oc, bf16x8 (&xn)[2][4]) {  // load number o of a step: (j, kk) = (o >> 2, o & 3)
         constexpr int o = decltype(oc)::value;
         const uint32_t voff = ((o >> 2) ? xv1 : xv0) + (uint32_t)((o & 3) * 1024);
@@ -428,8 +411,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     // one store through a selected address, which keeps that state in scratch memory)
     auto stream_enter_tile = [&]() {
         const bool in_strip = d_tile < ntiles;  // past the strip's last tile the remaining loads of the pipeline move nothing
-        const int unit0 = (u_first + d_tile * tb + max(d_tile - n_small, 0)) * WU;
-        d_nt = (tb + (d_tile >= n_small ? 1 : 0)) * WU;
+        const int unit0 = u_first + d_tile * tb + max(d_tile - n_small, 0);
+        d_nt = tb + (d_tile >= n_small ? 1 : 0);
         d_wsoff = in_strip ? (uint32_t)unit0 * 32u * (uint32_t)a.K * 2u : 0u;
         d_vw = in_strip ? vw0 : DEAD;
     };
@@ -450,9 +433,9 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
                                                  __builtin_amdgcn_readfirstlane(d_wsoff + d_koff), 0, ONCE ? GS_ONCE : 0);
     };
 
-    const bool wave_has_rows = m0 + tw * 64 < a.M;   // (uniform per wavefront)
+    const bool wave_has_rows = m0 + wave * 64 < a.M;   // (uniform per wavefront)
 
-    // ---- one value per lane and token block j (token m0 + tw*64 + j*32 + l32): the RMSNorm factor of the row for the
+    // ---- one value per lane and token block j (token m0 + wave*64 + j*32 + l32): the RMSNorm factor of the row for the
     //      SwiGLU epilogue, the running sum of squares of the stored row for the residual epilogue (see gemm_epilogue)
     float row_val[2] = {0.0f, 0.0f};
 
@@ -460,10 +443,10 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
     uint32_t aw[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
-        aw[kk] = lds0 + (uint32_t)uw * 4096u + (uint32_t)kk * 1024u + (uint32_t)lane * 16u;
+        aw[kk] = lds0 + (uint32_t)kk * 1024u + (uint32_t)lane * 16u;
     uint32_t c_slot = 0;  // ring slot of the step being multiplied
 
-    // ---- fill the pipeline: W(0) .. W(AHEAD - 2), X(0) .. X(XD - 1), W(AHEAD - 1)
+    // ---- fill the pipeline: W(0) .. W(AHEAD - 2), X(0), W(AHEAD - 1)
     stream_enter_tile();
     auto prologue_w = [&]() {
         static_for<0, MAXNT>([&](auto kc) {
@@ -472,16 +455,14 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
         stream_advance();
     };
     static_for<0, AHEAD - 1>([&](auto) { prologue_w(); });
-    static_for<0, XD>([&](auto bc) {
-        static_for<0, 8>([&](auto oc) { load_x(oc, xbuf[decltype(bc)::value]); });
-        x_advance();
-    });
+    static_for<0, 8>([&](auto oc) { load_x(oc, xbuf[0]); });
+    x_advance();
     prologue_w();
     if constexpr (EPI == EPI_SWIGLU) {
         // the row factors, behind the pipeline's first loads (and waited for with them)
         int mj[2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) mj[j] = min(m0 + tw * 64 + j * 32 + l32, a.M - 1);   // (rows past M: any valid row, nothing is stored)
+        for (int j = 0; j < 2; ++j) mj[j] = min(m0 + wave * 64 + j * 32 + l32, a.M - 1);   // (rows past M: any valid row, nothing is stored)
         load_row_factors<2>(a, mj, half, row_val);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -489,28 +470,27 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
 
     auto run_tile = [&](auto ntc, const int unit0) {
         constexpr int NT = decltype(ntc)::value;   // units of the tile (= weight DMA instructions per step and wavefront)
-        constexpr int NTW = NT / WU;               // units this wavefront multiplies
-        constexpr int SL = 2 * NTW;  // MFMAs (= slots for memory instructions) per k-step
-        f32x16 acc[NTW][2];
+        constexpr int SL = 2 * NT;   // MFMAs (= slots for memory instructions) per k-step
+        f32x16 acc[NT][2];
 #pragma unroll
-        for (int i = 0; i < NTW; ++i)
+        for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-        bf16x8 wa[NTW], wb[NTW];
+        bf16x8 wa[NT], wb[NT];
 
-        auto read_w = [&](auto ic, bf16x8 (&wf)[NTW], const uint32_t addr) {
+        auto read_w = [&](auto ic, bf16x8 (&wf)[NT], const uint32_t addr) {
             constexpr int i = decltype(ic)::value;
-            RS_DS_READ_B128(wf[i], addr, i * WU * 4096);
+            RS_DS_READ_B128(wf[i], addr, i * 4096);
         };
         // one k-step of 2 NT MFMAs on (wf, xc[.][KK]); memory instruction number o of the phase rides behind MFMA number
         // o (or several per MFMA when there are more instructions than MFMAs): first the NT fragment reads of the next
         // k-step, then the phase's EXTRA loads
-        auto phase = [&](auto kkc, bf16x8 (&wf)[NTW], bf16x8 (&xc)[2][4], bf16x8 (&wnext)[NTW], const uint32_t wnext_addr,
+        auto phase = [&](auto kkc, bf16x8 (&wf)[NT], bf16x8 (&xc)[2][4], bf16x8 (&wnext)[NT], const uint32_t wnext_addr,
                          auto extra_count, auto&& extra) {
             constexpr int KK = decltype(kkc)::value;
-            constexpr int LA = NTW + decltype(extra_count)::value;
+            constexpr int LA = NT + decltype(extra_count)::value;
             static_for<0, SL>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
                 constexpr int i = q >> 1, j = q & 1;
@@ -519,8 +499,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
                 constexpr int o_hi = (LA <= SL) ? (q + 1 < LA ? q + 1 : LA) : ((q + 1) * LA / SL);
                 static_for<o_lo, o_hi>([&](auto oc) {
                     constexpr int o = decltype(oc)::value;
-                    if constexpr (o < NTW) read_w(oc, wnext, wnext_addr);
-                    else extra(std::integral_constant<int, o - NTW>{});
+                    if constexpr (o < NT) read_w(oc, wnext, wnext_addr);
+                    else extra(std::integral_constant<int, o - NT>{});
                 });
                 RS_FENCE();
             });
@@ -530,14 +510,14 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
         // together with the DMA of the weights three steps ahead
         auto step = [&](bf16x8 (&xc)[2][4], bf16x8 (&xn)[2][4]) {
             const uint32_t n_slot = (c_slot + SLOT_BYTES) & (RING_BYTES - 1);
-            tie_wait_lgkm0<NTW>(wa);
+            tie_wait_lgkm0<NT>(wa);
             phase(std::integral_constant<int, 0>{}, wa, xc, wb, aw[1] + c_slot, std::integral_constant<int, 4>{},
                   [&](auto ec) { load_x(ec, xn); });
-            tie_wait_lgkm0<NTW>(wb);
+            tie_wait_lgkm0<NT>(wb);
             phase(std::integral_constant<int, 1>{}, wb, xc, wa, aw[2] + c_slot, std::integral_constant<int, 4>{},
                   [&](auto ec) { load_x(std::integral_constant<int, decltype(ec)::value + 4>{}, xn); });
             x_advance();
-            tie_wait_lgkm0<NTW>(wa);  // also: every LDS read of k-steps 0..2 has landed
+            tie_wait_lgkm0<NT>(wa);  // also: every LDS read of k-steps 0..2 has landed
             // this wavefront's share of the next W step has landed when at most this step's 8 token loads and the loads of
             // the AHEAD - 2 steps before it (NT weight, 8 token) are still in flight
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 + (AHEAD - 2) * (NT + 8)) : "memory");
@@ -546,7 +526,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
             constexpr int W_A = (NT + 1) / 2, W_B = NT - W_A;
             phase(std::integral_constant<int, 2>{}, wa, xc, wb, aw[3] + c_slot, std::integral_constant<int, W_A>{},
                   [&](auto ec) { load_w(ec); });
-            tie_wait_lgkm0<NTW>(wb);
+            tie_wait_lgkm0<NT>(wb);
             // (the stream's bookkeeping - scalar work and a rarely taken branch - rides behind an MFMA in the middle of the
             // phase like a memory instruction: left after the phase's last MFMA it holds up the next step's first one by
             // about 150 clocks, with one wavefront per SIMD and nothing else to issue)
@@ -555,91 +535,15 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
                       if constexpr (decltype(ec)::value < W_B) {
                           load_w(std::integral_constant<int, decltype(ec)::value + W_A>{});
                       } else {
-                          if (__builtin_expect(d_nt > NT, 0))   // the stream is in a wider tile: one more group of units
-                              static_for<0, WU>([&](auto gc) {
-                                  constexpr int k = NT + decltype(gc)::value;
-                                  load_w(std::integral_constant<int, k < MAXNT ? k : 0>{});
-                              });
+                          if (__builtin_expect(d_nt > NT, 0))   // the stream is in a wider tile: one more unit
+                              load_w(std::integral_constant<int, NT < MAXNT ? NT : 0>{});
                           stream_advance();
                       }
                   });
             c_slot = n_slot;
         };
 
-        // The narrow geometry reads the weight fragments of a whole step one step ahead (all four k-steps of step s + 1
-        // behind the MFMAs of the second half of step s, right after the barrier that publishes them): with one or two
-        // units a k-step is 2 or 4 MFMAs, too few to cover the LDS latency of a read issued one k-step ahead, and the
-        // matrix pipe would wait for its operands four times per step.
-        constexpr bool FA = MAXNT == 2;
-        static_assert(!FA || XB % 2 == 0, "the two fragment sets alternate step by step");
-        bf16x8 wcA[4][NTW], wcB[4][NTW];
-        // (inline asm names only its own lambda's parameters: operands taken from an enclosing scope are not captured)
-        auto read_frag = [](auto offc, bf16x8& dst, const uint32_t addr) { RS_DS_READ_B128(dst, addr, decltype(offc)::value); };
-        auto read_step_frags = [&](bf16x8 (&wf)[4][NTW], const uint32_t slot) {
-            static_for<0, 4>([&](auto kc) {
-                static_for<0, NTW>([&](auto ic) {
-                    constexpr int kk = decltype(kc)::value, i = decltype(ic)::value;
-                    read_frag(std::integral_constant<int, i * WU * 4096>{}, wf[kk][i], aw[kk] + slot);
-                });
-            });
-        };
-        auto wait_step_frags = [&](bf16x8 (&wf)[4][NTW]) {   // "s_waitcnt lgkmcnt(0)" tied to the fragments it guards
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(wf[0][0]));
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-                for (int i = 0; i < NTW; ++i) asm volatile("" : "+v"(wf[kk][i]));
-        };
-        // 2 NTW MFMAs of k-step KK with `count` memory operations riding behind them
-        auto phase_fa = [&](auto kkc, bf16x8 (&wf)[NTW], bf16x8 (&xc)[2][4], auto count, auto&& op) {
-            constexpr int KK = decltype(kkc)::value;
-            constexpr int LA = decltype(count)::value;
-            static_for<0, SL>([&](auto qc) {
-                constexpr int q = decltype(qc)::value;
-                constexpr int i = q >> 1, j = q & 1;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i], xc[j][KK], acc[i][j], 0, 0, 0);
-                constexpr int o_lo = (LA <= SL) ? (q < LA ? q : LA) : (q * LA / SL);
-                constexpr int o_hi = (LA <= SL) ? (q + 1 < LA ? q + 1 : LA) : ((q + 1) * LA / SL);
-                static_for<o_lo, o_hi>([&](auto oc) { op(oc); });
-                RS_FENCE();
-            });
-        };
-        auto step_fa = [&](bf16x8 (&xc)[2][4], bf16x8 (&xn)[2][4], bf16x8 (&wc)[4][NTW], bf16x8 (&wn)[4][NTW]) {
-            const uint32_t n_slot = (c_slot + SLOT_BYTES) & (RING_BYTES - 1);
-            wait_step_frags(wc);
-            phase_fa(std::integral_constant<int, 0>{}, wc[0], xc, std::integral_constant<int, 4>{}, [&](auto ec) { load_x(ec, xn); });
-            phase_fa(std::integral_constant<int, 1>{}, wc[1], xc, std::integral_constant<int, 4>{},
-                     [&](auto ec) { load_x(std::integral_constant<int, decltype(ec)::value + 4>{}, xn); });
-            x_advance();
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 + (AHEAD - 2) * (NT + 8)) : "memory");   // (as in step)
-            asm volatile("s_barrier" ::: "memory");
-            RS_FENCE();
-            constexpr int W_A = (NT + 1) / 2, W_B = NT - W_A;
-            constexpr int RD = 2 * NTW;   // fragment reads per half: two k-steps of the next step
-            phase_fa(std::integral_constant<int, 2>{}, wc[2], xc, std::integral_constant<int, RD + W_A>{}, [&](auto ec) {
-                constexpr int e = decltype(ec)::value;
-                if constexpr (e < RD) read_frag(std::integral_constant<int, (e % NTW) * WU * 4096>{}, wn[e / NTW][e % NTW], aw[e / NTW] + n_slot);
-                else load_w(std::integral_constant<int, e - RD>{});
-            });
-            phase_fa(std::integral_constant<int, 3>{}, wc[3], xc, std::integral_constant<int, RD + W_B + 1>{}, [&](auto ec) {
-                constexpr int e = decltype(ec)::value;
-                if constexpr (e < RD) {
-                    read_frag(std::integral_constant<int, (e % NTW) * WU * 4096>{}, wn[2 + e / NTW][e % NTW], aw[2 + e / NTW] + n_slot);
-                } else if constexpr (e - RD < W_B) {
-                    load_w(std::integral_constant<int, e - RD + W_A>{});
-                } else {
-                    if (__builtin_expect(d_nt > NT, 0))   // the stream is in a wider tile: one more group of units
-                        static_for<0, WU>([&](auto gc) {
-                            constexpr int k = NT + decltype(gc)::value;
-                            load_w(std::integral_constant<int, k < MAXNT ? k : 0>{});
-                        });
-                    stream_advance();
-                }
-            });
-            c_slot = n_slot;
-        };
-
-        // tile start: xbuf[0 .. XD - 1] hold (or are receiving) the tile's first token fragments; its first weight step was
+        // tile start: xbuf[0] holds (or is receiving) the tile's first token fragments; its first weight step was
         // published by the previous tile's last barrier (by the prologue for the first tile)
         asm volatile("s_barrier" ::: "memory");
         // A wavefront whose 64 rows all lie past M (a call of few rows, or the ragged end of the last block) only does its
@@ -653,67 +557,33 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
                 asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 2) * NT) : "memory");
                 asm volatile("s_barrier" ::: "memory");
                 static_for<0, NT>([&](auto kc) { load_w(kc); });
-                if (__builtin_expect(d_nt > NT, 0))
-                    static_for<0, WU>([&](auto gc) {
-                        constexpr int k = NT + decltype(gc)::value;
-                        load_w(std::integral_constant<int, k < MAXNT ? k : 0>{});
-                    });
+                if (__builtin_expect(d_nt > NT, 0)) load_w(std::integral_constant<int, NT < MAXNT ? NT : 0>{});
                 stream_advance();
                 c_slot = (c_slot + SLOT_BYTES) & (RING_BYTES - 1);
             }
             return;
         }
-        if constexpr (FA) read_step_frags(wcA, c_slot);
-        else static_for<0, NTW>([&](auto ic) { read_w(ic, wa, aw[0] + c_slot); });
-        // step number s multiplies buffer s mod XB and loads the fragments of step s + XD into the buffer step s - 1 used
-        // (narrow geometry: even steps multiply fragment set A and read set B for the next step, odd steps the reverse)
-        auto do_step = [&](auto uc) {
-            constexpr int u = decltype(uc)::value;
-            if constexpr (!FA) step(xbuf[u], xbuf[(u + XD) % XB]);
-            else if constexpr (u % 2 == 0) step_fa(xbuf[u], xbuf[(u + XD) % XB], wcA, wcB);
-            else step_fa(xbuf[u], xbuf[(u + XD) % XB], wcB, wcA);
-        };
+        static_for<0, NT>([&](auto ic) { read_w(ic, wa, aw[0] + c_slot); });
+        // step number s multiplies buffer s mod 2 and loads the fragments of step s + 1 into the other
         int s = 0;
-        for (; s + XB <= ns; s += XB) static_for<0, XB>([&](auto uc) { do_step(uc); });
-        // the steps left over, then the fragments in flight move to where the next tile expects them (buffer 0 first)
-        static_for<1, XB>([&](auto rc) {
-            constexpr int R = decltype(rc)::value;
-            if (ns - s == R) {
-                static_for<0, R>([&](auto uc) { do_step(uc); });
-                bf16x8 moved[XB][2][4];
-#pragma unroll
-                for (int b = 0; b < XD; ++b)      // (the buffer multiplied last holds nothing that is still needed)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) moved[b][j][kk] = xbuf[(b + R) % XB][j][kk];
-#pragma unroll
-                for (int b = 0; b < XD; ++b)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) xbuf[b][j][kk] = moved[b][j][kk];
-            }
-        });
-        // the look-ahead read behind the last step (discarded: the next tile reads its own)
-        if constexpr (FA) {
-            wait_step_frags(wcA);
-            wait_step_frags(wcB);
-        } else {
-            tie_wait_lgkm0<NTW>(wa);
+        for (; s + 2 <= ns; s += 2) {
+            step(xbuf[0], xbuf[1]);
+            step(xbuf[1], xbuf[0]);
         }
-        gemm_epilogue<EPI, NTW, WU>(a, acc, m0 + tw * 64, unit0 + uw, half, l32, split, row_val);
+        if (s < ns) {   // the step left over, then the fragments in flight move to where the next tile expects them
+            step(xbuf[0], xbuf[1]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) xbuf[0][j][kk] = xbuf[1][j][kk];
+        }
+        tie_wait_lgkm0<NT>(wa);   // the look-ahead read behind the last step (discarded: the next tile reads its own)
+        gemm_epilogue<EPI, NT>(a, acc, m0 + wave * 64, unit0, half, l32, split, row_val);
     };
 
     for (int t = 0; t < ntiles; ++t) {
-        const int nt = (tb + (t >= n_small ? 1 : 0)) * WU;
-        const int unit0 = (u_first + t * tb + max(t - n_small, 0)) * WU;
-        if constexpr (MAXNT == 2 && WU == 2) {
-            run_tile(std::integral_constant<int, 2>{}, unit0);   // one group of two units
-        } else if constexpr (MAXNT == 2) {
-            if (nt == 1) run_tile(std::integral_constant<int, 1>{}, unit0);
-            else run_tile(std::integral_constant<int, 2>{}, unit0);
-        } else
+        const int nt = tb + (t >= n_small ? 1 : 0);
+        const int unit0 = u_first + t * tb + max(t - n_small, 0);
         switch (nt) {
             case 1: run_tile(std::integral_constant<int, 1>{}, unit0); break;
             case 2: run_tile(std::integral_constant<int, 2>{}, unit0); break;
@@ -733,8 +603,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const float ss = row_val[j] + __shfl_xor(row_val[j], 32, WAVE);
-                const int m = m0 + tw * 64 + j * 32 + l32;
-                if (half == 0 && m < a.M) a.rowss[(size_t)(strip * WU + uw) * a.M + m] = ss;
+                const int m = m0 + wave * 64 + j * 32 + l32;
+                if (half == 0 && m < a.M) a.rowss[(size_t)strip * a.M + m] = ss;
             }
         }
     }
@@ -744,7 +614,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_strip_kernel(GemmArgs a) {
 // resid / out are row-major or fragment-major (see frag_offset_bytes); when inv_rms is given it also leaves
 // rsqrt(mean(out[m,:]^2) + eps) of the stored row there.  WPR wavefronts share a row: 1 (a workgroup covers 4 rows), or 4
 // (one row per workgroup, for calls of few rows, which would otherwise occupy a fraction of the chip).
-template <int WPR>
+template <int WPR, int PLANES>
 __global__ __launch_bounds__(256) void splitk_reduce_residual_kernel(const float* __restrict__ partial, int splits,
                                                                      const bf16* __restrict__ resid, int ldr, int resid_frag,
                                                                      bf16* __restrict__ out, int ldo, int out_frag, int M, int N,
@@ -757,12 +627,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_residual_kernel(const float
     constexpr int ROW_LANES = WPR * WAVE;
     if (m >= M) return;  // (uniform for the workgroup when the wavefronts share a row)
     float ss = 0.0f;
-    // four column groups per pass: all their loads are issued before the first sum (the kernel is one pass over
+    // several column groups per pass: all their loads are issued before the first sum (the kernel is one pass over
     // (4 splits + 4) N bytes per row; what it has to hide is latency)
-    constexpr int G = 4;
+    constexpr int G = 16 / PLANES;
     for (int n0 = col * 4; n0 < N; n0 += G * ROW_LANES * 4) {
         bf16x4 r4[G];
-        f32x4 p[G][4];  // at most 4 planes
+        f32x4 p[G][PLANES];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int n = n0 + g * ROW_LANES * 4;
@@ -770,7 +640,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_residual_kernel(const float
                 const size_t roff = resid_frag ? frag_offset_bytes(m, n, ldr) : ((size_t)m * ldr + n) * 2;
                 r4[g] = *reinterpret_cast<const bf16x4*>(reinterpret_cast<const char*>(resid) + roff);
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
+                for (int s = 0; s < PLANES; ++s)
                     if (s < splits) p[g][s] = *reinterpret_cast<const f32x4*>(partial + ((size_t)s * M + m) * N + n);
             }
         }
@@ -780,7 +650,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_residual_kernel(const float
             if (n < N) {
                 float v[4] = {bf16_to_f32(r4[g][0]), bf16_to_f32(r4[g][1]), bf16_to_f32(r4[g][2]), bf16_to_f32(r4[g][3])};
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
+                for (int s = 0; s < PLANES; ++s)
                     if (s < splits) {
                         v[0] += p[g][s][0]; v[1] += p[g][s][1]; v[2] += p[g][s][2]; v[3] += p[g][s][3];
                     }

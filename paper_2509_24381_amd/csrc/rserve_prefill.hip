@@ -21,6 +21,7 @@
 #include "kv_transfer.h"
 #include "gemm_strip.h"
 #include "gemm_skinny.h"
+#include "gemm_tile.h"
 #include "last_error.h"
 
 namespace {
@@ -105,9 +106,7 @@ struct rs_ctx {
     int mrope_b0 = 0, mrope_b1 = 0;  // rotary pair j turns with axis 0 below b0, axis 1 below b1, axis 2 above (set in rs_ctx_create)
     bool attn_plain_order = false;  // RS_ATTN_ORDER=plain: attention blocks that share a compute unit stay heaviest-first (no pairing)
     int attn_split = 0;       // RS_ATTN_SPLIT environment variable: parts a block's key range is cut into (0: decided per call)
-    int gemm_pairs = 1;       // RS_PAIRS environment variable: 0 never lets two wavefronts of a GEMM workgroup split a pair of units
-    int gemm_narrow = 1;      // RS_NARROW environment variable: 0 never uses the narrow GEMM geometry; otherwise launches of at most
-    int narrow_max_tiles_m = 1;  // narrow_max_tiles_m (RS_NARROW_TM) token blocks whose strips would hold at most 2 units use it
+    int gemm_few = 1;         // RS_NARROW environment variable: 0 keeps every call on the strip GEMMs (no tiles, no few-rows kernel)
     int n_cu = 256;           // compute units of the device: the number of strips a GEMM launch is cut into
     bool has_device = false;  // false: created on a host without a GPU; argument checks work, launches return RS_EHIP
     int device = -1;          // the GPU that was current in rs_ctx_create
@@ -221,13 +220,6 @@ int strips_for(const rs_ctx* c, int tiles_m, int splits, int units) {
     return (units + ups - 1) / ups;
 }
 
-// Whether a launch qualifies for the narrow kernel geometry: few token blocks, no strip wider than the narrow tile.
-bool use_narrow(const rs_ctx* c, int tiles_m, int splits, int units, int max_tiles_m = 0) {
-    if (!c->gemm_narrow || tiles_m > std::max(max_tiles_m, c->narrow_max_tiles_m)) return false;
-    const int strips = strips_for(c, tiles_m, splits, units);
-    return (units + strips - 1) / strips <= GS_NARROW_NT;
-}
-
 // Estimated duration (shader clocks) of a residual GEMM cut into `splits` K ranges.  Constants fitted to measurements
 // on MI355X: a step of K = 64 costs 256 clocks of matrix-pipe issue per unit plus about 350 of barrier and issue overhead,
 // a tile about 20000 for pipeline fill and epilogue, and the reduction kernel moves its bytes at about 2 TB/s.
@@ -242,8 +234,7 @@ double gemm_cost_clocks(const rs_ctx* c, int M, int units, int k_steps, int spli
     // (a step of the wide geometry also moves 32 KB of token fragments per workgroup whatever the tile's width: with three
     // units or fewer that, not the MFMAs, sets its duration - about 1200 clocks measured; without this floor calls of 257
     // to 768 rows kept the O projection unsplit, 3 to 8 us slower than in two or three K ranges)
-    double step = 256.0 * nt + 350.0;
-    if (!use_narrow(c, tiles_m, splits, units)) step = std::max(step, 1200.0);
+    const double step = std::max(256.0 * nt + 350.0, 1200.0);
     double clocks = (double)waves * ntiles * (steps * step + 20000.0);
     if (splits > 1) clocks += (double)M * units * 32.0 * (4.0 * splits + 4.0) / 2.0e12 * 1.4e9;
     return clocks;
@@ -263,17 +254,9 @@ int choose_splitk(const rs_ctx* c, int M, int units, int k_steps) {
     return best;
 }
 
-constexpr int MAX_PLANES = 4;   // split-K partial planes
-
-// Weights that one workgroup reads once, and that the L2s (32 MB together) could not keep from one call to the next, are loaded with the
-// streaming hint (GS_ONCE): gate/up of 64 rows, 7B (272 MB), 54.2 -> 50.1 us between events, 72B (969 MB) 182 -> 160; smaller ones lose
-// by it (tiny layer, gate/up of 200 rows, 1 MB: 9.3 -> 10.1).
-constexpr size_t STREAM_BYTES = (size_t)32 << 20;
-bool streams_once(int tiles_m, int units, int steps) { return tiles_m == 1 && (size_t)units * steps * 4096 >= STREAM_BYTES; }
-
-// Rows up to which the first kernel gives a row a workgroup instead of a wavefront.
-// us per step, 7B shape in a stack: 250 rows 16.6 (a wavefront) -> 10.6, 512: 18.2 -> 15.2, 640: 17.5 -> 16.6, 800: 19.1 -> 21.1.
-constexpr int RMS_FEW_ROWS = 704;
+// split-K partial planes: up to 4, in calls of few rows up to 8 (in rows of all planes together; grows with the call)
+constexpr int MAX_PLANES = 4, MAX_PLANES_FEW = 8, FEW_PLANES_ROWS = 256;
+size_t partial_planes_rows(size_t t) { return std::max(MAX_PLANES * t, MAX_PLANES_FEW * std::min<size_t>(t, FEW_PLANES_ROWS)); }
 
 struct WorkspaceLayout {
     size_t qkv, xf, attn, r, act, partial, attn_split, inv_rms1, inv_rms2, rowss, desc, total;
@@ -295,7 +278,7 @@ WorkspaceLayout ws_layout(const rs_ctx* c, int T, int R) {
     w.attn = take(tp * c->q_dim * 2);
     w.r = take(tp * f.hidden * 2);
     w.act = take(tp * f.mlp_inter * 2);
-    w.partial = take(4 * t * f.hidden * 4);  // up to 4 split-K partial planes of [T, H] fp32
+    w.partial = take(partial_planes_rows(t) * f.hidden * 4);  // split-K partial planes of [T, H] fp32
     w.attn_split = take((size_t)ATT_SPLIT_SLOTS * (32 * ATT_WAVES) * (f.head_dim + 2) * 4);  // partial results of split key ranges
     w.inv_rms1 = take(tp * 4);
     w.inv_rms2 = take(tp * 4);
@@ -310,8 +293,103 @@ size_t fp8_expansion_bytes(const rs_ctx* c, long n_tokens) {
     return (size_t)2 * align_up((size_t)n_tokens, 64) * c->kv_dim * 2;
 }
 
-// *columns_out (optional) receives the number of workgroup columns of the launch: strips times the wavefronts that split a
-// strip's units, i.e. the number of parts the residual epilogue leaves in GemmArgs::rowss.
+// Weights that one workgroup reads once, and that the L2s (32 MB together) could not keep from one call to the next, are loaded with the
+// streaming hint (GS_ONCE): gate/up of 64 rows, 7B (272 MB), 54.2 -> 50.1 us between events, 72B (969 MB) 182 -> 160; smaller ones lose
+// by it (tiny layer, gate/up of 200 rows, 1 MB: 9.3 -> 10.1).
+constexpr size_t STREAM_BYTES = (size_t)32 << 20;
+
+// Rows up to which the first kernel gives a row a workgroup instead of a wavefront.
+// us per step, 7B shape in a stack: 250 rows 16.6 (a wavefront) -> 10.6, 512: 18.2 -> 15.2, 640: 17.5 -> 16.6, 800: 19.1 -> 21.1.
+constexpr int RMS_FEW_ROWS = 704;
+
+// ---- calls of up to TILE_ROWS rows: strips or tiles (gemm_tile.h), and into how many K ranges.
+// Estimated ns of a projection: 4.5 us of launch, first loads and epilogue; per step of 64 k the bytes that a workgroup fetches, at the
+// rate a compute unit gets them with all of them walking K in step (50 to 60 per ns: the longer K, the less of the token panel an L2
+// keeps), or its MFMAs; at least the weights at what HBM streams (6.2 TB/s with the streaming hint, 5.3 without); and the reduction.
+// Against measurement (us between events, 3 of them the events'; 7B shape): QKV 250 rows on 64 x 128 27.4 (30.8), 512 on 128 x 96 31
+// (35), 1000 on 128 x 160 38.9 (46.8); O 64 rows on 64 x 64 in 4 ranges 14.6 (15.8), 250 on 64 x 64 19.8 (22.0); down 64 rows on
+// 64 x 128 in 8 ranges 33 (29.5, its reduction not in it), 250 on 128 x 128 in 4 64 (56.5, likewise).  The estimates rank; they do not predict.
+constexpr int TILE_ROWS = 1024;
+constexpr int TILE_SHAPES = 6;
+constexpr int TILE_BLOCKS[TILE_SHAPES] = {2, 2, 4, 4, 4, 4}, TILE_UNITS[TILE_SHAPES] = {2, 4, 2, 3, 4, 5};
+double step_ns(double blocks, double units, int steps) {
+    const double rate = steps <= 64 ? 60.0 : steps <= 128 ? 54.0 : 50.0;
+    return std::max(4096.0 / rate * (blocks + units), 15.3 * blocks * units);
+}
+double reduce_ns(int M, int units, int splits) { return splits > 1 ? 5500.0 + (double)M * units * 32.0 * (4.0 * splits + 4.0) / 6000.0 : 0.0; }
+bool streams_once(int tiles_m, int units, int steps) { return tiles_m == 1 && (size_t)units * steps * 4096 >= STREAM_BYTES; }
+double stream_ns(int tiles_m, int units, int steps) { return 4500.0 + (double)units * steps * 4096.0 / (streams_once(tiles_m, units, steps) ? 6200.0 : 5300.0); }
+// (the row blocks of a ragged call count by their live rows: what some workgroups do not fetch the others get sooner)
+double tile_ns(const rs_ctx* c, int shape, int M, int units, int steps, int splits) {
+    const int b = TILE_BLOCKS[shape], u = TILE_UNITS[shape];
+    const int tiles_m = (M + 32 * b - 1) / (32 * b), wgs = tiles_m * ((units + u - 1) / u) * splits, rounds = (wgs + c->n_cu - 1) / c->n_cu;
+    const double fetch = rounds * (4500.0 + (steps + splits - 1) / splits * step_ns((double)((M + 31) / 32) / tiles_m, u, steps));
+    return std::max(fetch, stream_ns(tiles_m, units, steps)) + reduce_ns(M, units, splits);
+}
+double strip_ns(const rs_ctx* c, int M, int units, int steps, int splits) {
+    const int tiles_m = (M + GS_BM - 1) / GS_BM, strips = strips_for(c, tiles_m, splits, units);
+    const int rounds = (tiles_m * strips * splits + c->n_cu - 1) / c->n_cu;
+    const int ups = (units + strips - 1) / strips, ntiles = (ups + GS_MAX_NT - 1) / GS_MAX_NT;
+    const double b = 2.0 * ((M + 63) / 64) / tiles_m;   // (a wavefront without rows loads none)
+    const double step = std::max(570.0, step_ns(b, (double)ups / ntiles, steps));   // (its loop takes 1200 clocks with few units)
+    return std::max(rounds * (4500.0 + ntiles * ((steps + splits - 1) / splits * step)), stream_ns(tiles_m, units, steps)) + reduce_ns(M, units, splits);
+}
+struct GemmRoute { int shape, splits; };   // shape -1: strips
+// `splits_fixed` > 0: that many K ranges.  `strip_splits`: the K ranges the strips would take.  shapes: the ones that exist for the epilogue
+GemmRoute choose_route(const rs_ctx* c, int M, int units, int steps, int splits_fixed, int strip_splits, std::initializer_list<int> shapes) {
+    GemmRoute best{-1, strip_splits};
+    if (!c->gemm_few || M > TILE_ROWS) return best;
+    // (a tie goes to the strips, which lose less in a longer call's last block; with one block of rows to the tiles: 72B, 128 rows, down
+    // 103.4 -> 97.2, O 44.7 -> 41.3)
+    double best_ns = (M <= 128 ? 1.04 : 0.96) * strip_ns(c, M, units, steps, strip_splits);
+    const int most = M <= FEW_PLANES_ROWS ? MAX_PLANES_FEW : MAX_PLANES;
+    for (const int shape : shapes)
+        for (int s = splits_fixed > 0 ? splits_fixed : 1; s <= (splits_fixed > 0 ? splits_fixed : most); ++s) {
+            if (splits_fixed == 0 && s > 1 && steps / s < 8) break;
+            const double ns = tile_ns(c, shape, M, units, steps, s);
+            if (ns < best_ns) {
+                best_ns = ns;
+                best = GemmRoute{shape, s};
+            }
+        }
+    return best;
+}
+
+template <int EPI, int BMB, int BU>
+rs_status launch_tile_shape(GemmArgs a, int splits, hipStream_t st, int* columns_out) {
+    const int units = a.N / 32, steps = a.K / GS_BK;
+    a.tiles_m = (a.M + 32 * BMB - 1) / (32 * BMB);
+    a.strips = (units + BU - 1) / BU;
+    a.steps_per_split = (steps + splits - 1) / splits;
+    splits = (steps + a.steps_per_split - 1) / a.steps_per_split;
+    if (columns_out) *columns_out = (units + TileShape<BMB, BU>::TN - 1) / TileShape<BMB, BU>::TN;
+    const dim3 grid(a.tiles_m * a.strips * splits);
+    if (streams_once(a.tiles_m, units, steps)) hipLaunchKernelGGL((gemm_tile_kernel<EPI, BMB, BU, true>), grid, dim3(256), (tile_lds_bytes<BMB, BU>()), st, a);
+    else hipLaunchKernelGGL((gemm_tile_kernel<EPI, BMB, BU, false>), grid, dim3(256), (tile_lds_bytes<BMB, BU>()), st, a);
+    RS_HIP(hipGetLastError());
+    return RS_OK;
+}
+template <int EPI>
+rs_status launch_tile(int shape, const GemmArgs& a, int splits, hipStream_t st, int* columns_out = nullptr) {
+    if (shape == 0) return launch_tile_shape<EPI, 2, 2>(a, splits, st, columns_out);
+    if (shape == 1) return launch_tile_shape<EPI, 2, 4>(a, splits, st, columns_out);
+    if constexpr (EPI == EPI_QKV_ROPE) {
+        if (shape == 3) return launch_tile_shape<EPI, 4, 3>(a, splits, st, columns_out);
+        return launch_tile_shape<EPI, 4, 5>(a, splits, st, columns_out);
+    } else {
+        if (shape == 2) return launch_tile_shape<EPI, 4, 2>(a, splits, st, columns_out);
+        return launch_tile_shape<EPI, 4, 4>(a, splits, st, columns_out);
+    }
+}
+constexpr std::initializer_list<int> QKV_SHAPES = {0, 1, 3, 5}, RESIDUAL_SHAPES = {0, 1, 2, 4};
+template <int EPI, int BMB, int BU>
+hipError_t allow_tile_lds(hipError_t e) {
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_tile_kernel<EPI, BMB, BU, true>, hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds_bytes<BMB, BU>());
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_tile_kernel<EPI, BMB, BU, false>, hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds_bytes<BMB, BU>());
+    return e;
+}
+
+// *columns_out (optional) receives the number of strips, i.e. the number of parts the residual epilogue leaves in GemmArgs::rowss.
 template <int EPI>
 rs_status launch_gemm(const rs_ctx* c, GemmArgs a, int splits, hipStream_t st, int* columns_out = nullptr) {
     a.tiles_m = (a.M + GS_BM - 1) / GS_BM;
@@ -319,33 +397,12 @@ rs_status launch_gemm(const rs_ctx* c, GemmArgs a, int splits, hipStream_t st, i
     const int steps = a.K / GS_BK;
     a.steps_per_split = (steps + splits - 1) / splits;
     splits = (steps + a.steps_per_split - 1) / a.steps_per_split;  // no empty K range
-    // A call of 129 to 256 rows whose strips would hold one pair of units each: blocks of 128 rows, two wavefronts along
-    // the rows and two along the pair (16 KB of token fragments per step and workgroup instead of 32; measured: QKV 40 -> 35
-    // us at 256 rows; up to 128 rows, where half the wavefronts of a 256-row block idle anyway, it is slower).
-    if (c->gemm_narrow && c->gemm_pairs && a.M > GS_BM / 2 && a.M <= GS_BM && units % 2 == 0) {
-        const int tiles_m = (a.M + GS_BM / 2 - 1) / (GS_BM / 2);
-        const int strips = strips_for(c, tiles_m, splits, units / 2);
-        if (strips == units / 2) {
-            a.tiles_m = tiles_m;
-            a.strips = strips;
-            if (columns_out) *columns_out = 2 * strips;
-            hipLaunchKernelGGL((gemm_strip_kernel<EPI, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>), dim3(tiles_m * strips, splits),
-                               dim3(256), GS_NARROW_LDS_BYTES, st, a);
-            RS_HIP(hipGetLastError());
-            return RS_OK;
-        }
-    }
     constexpr bool once_epi = EPI == EPI_SWIGLU || EPI == EPI_PARTIAL;
     a.strips = strips_for(c, a.tiles_m, splits, units);
     if (columns_out) *columns_out = a.strips;
     dim3 grid(a.tiles_m * a.strips, splits);
-    // (the QKV projection, which is never split along K, also takes the narrow geometry on two token blocks: 43 -> 38 us
-    // at 320 rows, no change at 512; the residual projections of such calls are better off split along K in the wide one)
-    if (use_narrow(c, a.tiles_m, splits, units, EPI == EPI_QKV_ROPE ? 2 : 0))
-        hipLaunchKernelGGL((gemm_strip_kernel<EPI, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD>), grid, dim3(256),
-                           GS_NARROW_LDS_BYTES, st, a);
-    else if (once_epi && streams_once(a.tiles_m, units, steps))
-        hipLaunchKernelGGL((gemm_strip_kernel<EPI, GS_MAX_NT, GS_SLOTS, 1, 1, 4, once_epi>), grid, dim3(256), GS_LDS_BYTES, st, a);
+    if (once_epi && streams_once(a.tiles_m, units, steps))
+        hipLaunchKernelGGL((gemm_strip_kernel<EPI, once_epi>), grid, dim3(256), GS_LDS_BYTES, st, a);
     else
         hipLaunchKernelGGL(gemm_strip_kernel<EPI>, grid, dim3(256), GS_LDS_BYTES, st, a);
     RS_HIP(hipGetLastError());
@@ -362,9 +419,9 @@ rs_status launch_gemm(const rs_ctx* c, GemmArgs a, int splits, hipStream_t st, i
 // hidden 512 44.6 / 46.2 / 48.4 -> 31.5 / 36.3 / 41.7; 1024 50.2 / 52.8 / 55.1 -> 36.7 / 42.6 / 50.0; 1536 (d 128) 68.3 / 70.5 / 75.8 ->
 // 56.8 / 65.1 / 72.0; 2048 67.4 / 69.1 / 74.0 -> 57.9 / 63.3 / 72.2; 72B 32 / 64 / 128 rows 424 / 441 / 475 -> 362 / 390 / 422.
 constexpr int SKINNY_ROWS = 128;
-bool skinny_qkv(const rs_ctx* c, int M, int K) { return c->gemm_narrow && M <= SKINNY_ROWS && (long)M * K <= 256 * 1024; }
-bool skinny_residual(const rs_ctx* c, int M, int K) { return c->gemm_narrow && (M <= 32 || (M <= SKINNY_ROWS && K <= 1024)); }
-bool skinny_swiglu(const rs_ctx* c, int M, int K) { return c->gemm_narrow && M <= SKINNY_ROWS && K <= 1024; }
+bool skinny_qkv(const rs_ctx* c, int M, int K) { return c->gemm_few && M <= SKINNY_ROWS && (long)M * K <= 256 * 1024; }
+bool skinny_residual(const rs_ctx* c, int M, int K) { return c->gemm_few && (M <= 32 || (M <= SKINNY_ROWS && K <= 1024)); }
+bool skinny_swiglu(const rs_ctx* c, int M, int K) { return c->gemm_few && M <= SKINNY_ROWS && K <= 1024; }
 
 // EPI_QKV_ROPE or EPI_SWIGLU: a wavefront per 32 tokens.
 template <int EPI>
@@ -420,8 +477,14 @@ rs_status gemm_residual(const rs_ctx* c, const bf16* X, const bf16* W, const bf1
     const float eps = c->cfg.rms_eps;
     const bool skinny = skinny_residual(c, M, K);
     int splits = choose_splitk(c, M, N / 32, K / GS_BK);
-    if (skinny && c->splitk_override == 0)   // (a K too long for one compute unit's loads, and units to spare)
+    int shape = -1;
+    if (skinny && c->splitk_override == 0) {   // (a K too long for one compute unit's loads, and units to spare)
         splits = K >= 8192 && 2 * (N / 32) <= c->n_cu ? 2 : 1;
+    } else if (!skinny) {
+        const GemmRoute route = choose_route(c, M, N / 32, K / GS_BK, c->splitk_override > 0 ? splits : 0, splits, RESIDUAL_SHAPES);
+        shape = route.shape;
+        splits = route.splits;
+    }
     if (splits > 1) {
         const int sps = (K / GS_BK + splits - 1) / splits;
         splits = (K / GS_BK + sps - 1) / sps;
@@ -429,21 +492,25 @@ rs_status gemm_residual(const rs_ctx* c, const bf16* X, const bf16* W, const bf1
     if (rowss_parts_out) *rowss_parts_out = 0;
     if (splits == 1) {
         a.rowss = inv_rms_out ? rowss : nullptr;
-        return skinny ? launch_skinny<EPI_RESIDUAL>(c, a, 1, st, inv_rms_out ? rowss_parts_out : nullptr)
-                      : launch_gemm<EPI_RESIDUAL>(c, a, 1, st, inv_rms_out ? rowss_parts_out : nullptr);
+        int* const parts = inv_rms_out ? rowss_parts_out : nullptr;
+        if (shape >= 0) return launch_tile<EPI_RESIDUAL>(shape, a, 1, st, parts);
+        return skinny ? launch_skinny<EPI_RESIDUAL>(c, a, 1, st, parts) : launch_gemm<EPI_RESIDUAL>(c, a, 1, st, parts);
     }
-    rs_status s = skinny ? launch_skinny<EPI_PARTIAL>(c, a, splits, st) : launch_gemm<EPI_PARTIAL>(c, a, splits, st);
+    rs_status s = shape >= 0 ? launch_tile<EPI_PARTIAL>(shape, a, splits, st)
+                : skinny ? launch_skinny<EPI_PARTIAL>(c, a, splits, st) : launch_gemm<EPI_PARTIAL>(c, a, splits, st);
     if (s != RS_OK) return s;
     if (defer && resid_frag && !out_frag && !inv_rms_out) {
         defer->splits = splits; defer->partial = partial; defer->resid = resid; defer->out = out;
         return RS_OK;
     }
-    if (M <= 512)  // few rows: a workgroup per row instead of per four
-        hipLaunchKernelGGL(splitk_reduce_residual_kernel<4>, dim3(M), dim3(256), 0, st, (const float*)partial, splits, resid, N,
-                           resid_frag, out, N, out_frag, M, N, inv_rms_out, eps);
-    else
-        hipLaunchKernelGGL(splitk_reduce_residual_kernel<1>, dim3((M + 3) / 4), dim3(256), 0, st, (const float*)partial, splits, resid, N,
-                           resid_frag, out, N, out_frag, M, N, inv_rms_out, eps);
+    // few rows: a workgroup per row instead of per four
+    const auto reduce = [&](auto wpr, auto planes) {
+        hipLaunchKernelGGL((splitk_reduce_residual_kernel<decltype(wpr)::value, decltype(planes)::value>), dim3(wpr == 4 ? M : (M + 3) / 4), dim3(256), 0, st,
+                           (const float*)partial, splits, resid, N, resid_frag, out, N, out_frag, M, N, inv_rms_out, eps);
+    };
+    if (splits > MAX_PLANES) reduce(std::integral_constant<int, 4>{}, std::integral_constant<int, MAX_PLANES_FEW>{});
+    else if (M <= 512) reduce(std::integral_constant<int, 4>{}, std::integral_constant<int, MAX_PLANES>{});
+    else reduce(std::integral_constant<int, 1>{}, std::integral_constant<int, MAX_PLANES>{});
     RS_HIP(hipGetLastError());
     return RS_OK;
 }
@@ -858,6 +925,7 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     };
     const auto first_kernel_planes = [&](auto wpr) {
         if (!pending) first_kernel(std::integral_constant<int, 0>{}, wpr);
+        else if (red.splits > MAX_PLANES) first_kernel(std::integral_constant<int, MAX_PLANES_FEW>{}, wpr);
         else first_kernel(std::integral_constant<int, MAX_PLANES>{}, wpr);
     };
     if (T <= RMS_FEW_ROWS) first_kernel_planes(std::integral_constant<int, 4>{});
@@ -882,7 +950,13 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         a.rope_cols = ctx->q_dim + ctx->kv_dim; a.head_dim = f.head_dim;
         a.mrope_b0 = ctx->mrope_b0; a.mrope_b1 = ctx->mrope_b1;
         a.M = T; a.N = ctx->qkv_dim; a.K = H;
-        if ((s = skinny_qkv(ctx, T, H) ? launch_skinny_rows<EPI_QKV_ROPE>(a, st) : launch_gemm<EPI_QKV_ROPE>(ctx, a, 1, st)) != RS_OK) return s;
+        if (skinny_qkv(ctx, T, H)) {
+            s = launch_skinny_rows<EPI_QKV_ROPE>(a, st);
+        } else {
+            const int shape = choose_route(ctx, T, ctx->qkv_dim / 32, H / GS_BK, 1, 1, QKV_SHAPES).shape;
+            s = shape >= 0 ? launch_tile<EPI_QKV_ROPE>(shape, a, 1, st) : launch_gemm<EPI_QKV_ROPE>(ctx, a, 1, st);
+        }
+        if (s != RS_OK) return s;
     }
     tm.end(RS_STEP_QKV_GEMM);
     // cache append, attention
@@ -963,9 +1037,7 @@ rs_status rs_ctx_create(const rs_layer_cfg* cfg, rs_ctx** out) {
     c->q_dim = q_dim; c->kv_dim = kv_dim; c->qkv_dim = qkv_dim; c->group = f.n_q_heads / f.n_kv_heads;
     c->mrope_b0 = c->mrope_b1 = f.head_dim / 2;  // 1-D RoPE: every pair turns with the first axis
     if (const char* e = getenv("RS_SPLITK")) c->splitk_override = atoi(e);
-    if (const char* e = getenv("RS_PAIRS")) c->gemm_pairs = atoi(e);
-    if (const char* e = getenv("RS_NARROW")) c->gemm_narrow = atoi(e);
-    if (const char* e = getenv("RS_NARROW_TM")) c->narrow_max_tiles_m = atoi(e);
+    if (const char* e = getenv("RS_NARROW")) c->gemm_few = atoi(e);
     if (const char* e = getenv("RS_ATTN_ORDER")) c->attn_plain_order = strcmp(e, "plain") == 0;
     if (const char* e = getenv("RS_ATTN_SPLIT")) c->attn_split = std::max(0, std::min(atoi(e), ATT_MAX_PARTS));
     auto cleanup = [&](rs_status s) { rs_ctx_destroy(c); return s; };
@@ -1018,16 +1090,11 @@ rs_status rs_ctx_create(const rs_layer_cfg* cfg, rs_ctx** out) {
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_RESIDUAL>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_SWIGLU>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_QKV_ROPE, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_RESIDUAL, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_SWIGLU, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_PARTIAL, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_QKV_ROPE, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_RESIDUAL, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_SWIGLU, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_PARTIAL, GS_NARROW_NT, GS_NARROW_SLOTS, 1, GS_NARROW_XD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_NARROW_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_SWIGLU, GS_MAX_NT, GS_SLOTS, 1, 1, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_PARTIAL, GS_MAX_NT, GS_SLOTS, 1, 1, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_SWIGLU, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_PARTIAL, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
+    e = allow_tile_lds<EPI_QKV_ROPE, 4, 5>(allow_tile_lds<EPI_QKV_ROPE, 4, 3>(allow_tile_lds<EPI_QKV_ROPE, 2, 4>(allow_tile_lds<EPI_QKV_ROPE, 2, 2>(e))));
+    e = allow_tile_lds<EPI_RESIDUAL, 4, 4>(allow_tile_lds<EPI_RESIDUAL, 4, 2>(allow_tile_lds<EPI_RESIDUAL, 2, 4>(allow_tile_lds<EPI_RESIDUAL, 2, 2>(e))));
+    e = allow_tile_lds<EPI_PARTIAL, 4, 4>(allow_tile_lds<EPI_PARTIAL, 4, 2>(allow_tile_lds<EPI_PARTIAL, 2, 4>(allow_tile_lds<EPI_PARTIAL, 2, 2>(e))));
     if (e != hipSuccess) return cleanup(fail(RS_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e)));
     *out = c;
     return RS_OK;
