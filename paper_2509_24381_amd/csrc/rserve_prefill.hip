@@ -254,12 +254,11 @@ int choose_splitk(const rs_ctx* c, int M, int units, int k_steps) {
     return best;
 }
 
-// split-K partial planes: up to 4, in calls of few rows up to 8 (in rows of all planes together; grows with the call)
-constexpr int MAX_PLANES = 4, MAX_PLANES_FEW = 8, FEW_PLANES_ROWS = 256;
-size_t partial_planes_rows(size_t t) { return std::max(MAX_PLANES * t, MAX_PLANES_FEW * std::min<size_t>(t, FEW_PLANES_ROWS)); }
+constexpr int MAX_PLANES = 4, MAX_PLANES_FEW = 8, FEW_PLANES_ROWS = 256;   // split-K partial planes: up to 8 in calls of few rows
 
 struct WorkspaceLayout {
     size_t qkv, xf, attn, r, act, partial, attn_split, inv_rms1, inv_rms2, rowss, desc, total;
+    int planes;   // that partial has room for
 };
 
 WorkspaceLayout ws_layout(const rs_ctx* c, int T, int R) {
@@ -278,8 +277,9 @@ WorkspaceLayout ws_layout(const rs_ctx* c, int T, int R) {
     w.attn = take(tp * c->q_dim * 2);
     w.r = take(tp * f.hidden * 2);
     w.act = take(tp * f.mlp_inter * 2);
-    w.partial = take(partial_planes_rows(t) * f.hidden * 4);  // split-K partial planes of [T, H] fp32
+    w.partial = take(MAX_PLANES * t * f.hidden * 4);  // split-K partial planes of [T, H] fp32, and more of them in attn_split, which is free by then
     w.attn_split = take((size_t)ATT_SPLIT_SLOTS * (32 * ATT_WAVES) * (f.head_dim + 2) * 4);  // partial results of split key ranges
+    w.planes = T <= FEW_PLANES_ROWS && off - w.partial >= MAX_PLANES_FEW * t * f.hidden * 4 ? MAX_PLANES_FEW : MAX_PLANES;
     w.inv_rms1 = take(tp * 4);
     w.inv_rms2 = take(tp * 4);
     w.rowss = take(tp * (f.hidden / 32) * 4);
@@ -335,14 +335,13 @@ double strip_ns(const rs_ctx* c, int M, int units, int steps, int splits) {
     return std::max(rounds * (4500.0 + ntiles * ((steps + splits - 1) / splits * step)), stream_ns(tiles_m, units, steps)) + reduce_ns(M, units, splits);
 }
 struct GemmRoute { int shape, splits; };   // shape -1: strips
-// `splits_fixed` > 0: that many K ranges.  `strip_splits`: the K ranges the strips would take.  shapes: the ones that exist for the epilogue
-GemmRoute choose_route(const rs_ctx* c, int M, int units, int steps, int splits_fixed, int strip_splits, std::initializer_list<int> shapes) {
+// `splits_fixed` > 0: that many K ranges.  `strip_splits`: the K ranges the strips would take.  most: the K ranges there are planes for.  shapes: the ones that exist for the epilogue
+GemmRoute choose_route(const rs_ctx* c, int M, int units, int steps, int splits_fixed, int strip_splits, int most, std::initializer_list<int> shapes) {
     GemmRoute best{-1, strip_splits};
     if (!c->gemm_few || M > TILE_ROWS) return best;
     // (a tie goes to the strips, which lose less in a longer call's last block; with one block of rows to the tiles: 72B, 128 rows, down
     // 103.4 -> 97.2, O 44.7 -> 41.3)
     double best_ns = (M <= 128 ? 1.04 : 0.96) * strip_ns(c, M, units, steps, strip_splits);
-    const int most = M <= FEW_PLANES_ROWS ? MAX_PLANES_FEW : MAX_PLANES;
     for (const int shape : shapes)
         for (int s = splits_fixed > 0 ? splits_fixed : 1; s <= (splits_fixed > 0 ? splits_fixed : most); ++s) {
             if (splits_fixed == 0 && s > 1 && steps / s < 8) break;
@@ -468,7 +467,7 @@ struct PendingReduce {
     bf16* out = nullptr;           // row-major
 };
 rs_status gemm_residual(const rs_ctx* c, const bf16* X, const bf16* W, const bf16* resid, int resid_frag, bf16* out,
-                        int out_frag, int M, int N, int K, float* partial, float* inv_rms_out, float* rowss, int* rowss_parts_out,
+                        int out_frag, int M, int N, int K, float* partial, int planes, float* inv_rms_out, float* rowss, int* rowss_parts_out,
                         hipStream_t st, PendingReduce* defer = nullptr) {
     GemmArgs a{};
     a.X = X; a.W = W; a.out = out; a.ldo = N; a.out_frag = out_frag; a.resid = resid; a.ldr = N; a.resid_frag = resid_frag;
@@ -481,7 +480,7 @@ rs_status gemm_residual(const rs_ctx* c, const bf16* X, const bf16* W, const bf1
     if (skinny && c->splitk_override == 0) {   // (a K too long for one compute unit's loads, and units to spare)
         splits = K >= 8192 && 2 * (N / 32) <= c->n_cu ? 2 : 1;
     } else if (!skinny) {
-        const GemmRoute route = choose_route(c, M, N / 32, K / GS_BK, c->splitk_override > 0 ? splits : 0, splits, RESIDUAL_SHAPES);
+        const GemmRoute route = choose_route(c, M, N / 32, K / GS_BK, c->splitk_override > 0 ? splits : 0, splits, planes, RESIDUAL_SHAPES);
         shape = route.shape;
         splits = route.splits;
     }
@@ -953,7 +952,7 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         if (skinny_qkv(ctx, T, H)) {
             s = launch_skinny_rows<EPI_QKV_ROPE>(a, st);
         } else {
-            const int shape = choose_route(ctx, T, ctx->qkv_dim / 32, H / GS_BK, 1, 1, QKV_SHAPES).shape;
+            const int shape = choose_route(ctx, T, ctx->qkv_dim / 32, H / GS_BK, 1, 1, 1, QKV_SHAPES).shape;
             s = shape >= 0 ? launch_tile<EPI_QKV_ROPE>(shape, a, 1, st) : launch_gemm<EPI_QKV_ROPE>(ctx, a, 1, st);
         }
         if (s != RS_OK) return s;
@@ -970,7 +969,7 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     // r = x + attn Wo^T, and 1/rms of every row of r (the second RMSNorm; its gain lives in the packed W_gate_up)
     tm.begin(RS_STEP_O_GEMM);
     int rowss_parts = 0;
-    if ((s = gemm_residual(ctx, attn, (const bf16*)w->w_o, xb, 0, r, 1, T, H, ctx->q_dim, partial, inv_rms2, rowss, &rowss_parts, st)) != RS_OK) return s;
+    if ((s = gemm_residual(ctx, attn, (const bf16*)w->w_o, xb, 0, r, 1, T, H, ctx->q_dim, partial, L.planes, inv_rms2, rowss, &rowss_parts, st)) != RS_OK) return s;
     tm.end(RS_STEP_O_GEMM);
     // act = silu((r Wg'^T) / rms) * ((r Wu'^T) / rms)
     tm.begin(RS_STEP_GATE_UP_GEMM);
@@ -987,7 +986,7 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     tm.end(RS_STEP_GATE_UP_GEMM);
     // y = r + act Wd^T
     tm.begin(RS_STEP_DOWN_GEMM);
-    if ((s = gemm_residual(ctx, act, (const bf16*)w->w_down, r, 1, yb, 0, T, H, I, partial, nullptr, nullptr, nullptr, st, pending_out)) != RS_OK) return s;
+    if ((s = gemm_residual(ctx, act, (const bf16*)w->w_down, r, 1, yb, 0, T, H, I, partial, L.planes, nullptr, nullptr, nullptr, st, pending_out)) != RS_OK) return s;
     tm.end(RS_STEP_DOWN_GEMM);
 
     for (int i = 0; i < R; ++i) kvs[i]->len[layer] += lens[i];
