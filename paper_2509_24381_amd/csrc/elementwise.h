@@ -147,6 +147,12 @@ __global__ __launch_bounds__(256) void final_norm_kernel(const bf16* __restrict_
 // four weight rows; lanes are reduced at the end of the group.
 constexpr int LM_ROWS = 4;
 constexpr int LM_VGROUP = 4;
+// ONCE: the vocabulary is beyond the 256 MB Infinity Cache (LM_STREAM_BYTES) and loaded with the streaming hint, with which HBM streams
+// faster: 152064 x 3584, 1 row 189 -> 171 us, 8 rows (the kernel below) 210 -> 186; 152064 x 8192, 1 row 450 -> 418.  A smaller one can
+// still be there from the head before, and the hint then loses: 32000 x 3584, 3 rows 42.0 -> 43.9.
+constexpr size_t LM_STREAM_BYTES = (size_t)256 << 20;
+constexpr int LM_ONCE = 2;   // cache policy (nt)
+template <bool ONCE>
 __global__ __launch_bounds__(256) void lm_head_kernel(const bf16* __restrict__ w, const float* __restrict__ h,
                                                       float* __restrict__ logits, int R, int vocab, int H) {
     extern __shared__ __attribute__((aligned(16))) float h_lds[];  // [R][H]
@@ -167,7 +173,10 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const bf16* __restrict__ w
         for (int c = lane; c < H / 8; c += WAVE) {
             bf16x8 wv[LM_VGROUP];
 #pragma unroll
-            for (int j = 0; j < LM_VGROUP; ++j) wv[j] = *reinterpret_cast<const bf16x8*>(wr[j] + c * 8);
+            for (int j = 0; j < LM_VGROUP; ++j) {
+                const bf16x8* const p = reinterpret_cast<const bf16x8*>(wr[j] + c * 8);
+                wv[j] = ONCE ? __builtin_nontemporal_load(p) : *p;
+            }
 #pragma unroll
             for (int r = 0; r < LM_ROWS; ++r)
                 if (r < R) {
@@ -205,9 +214,9 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const bf16* __restrict__ w
 // barrier; they meet in LDS at the end of a tile.  The accumulators are emptied after every 64 k, and those sums after every
 // 256: short chains keep the error against 64 bits below that of the fp32 kernel above (3584: 1.0e-7 against 1.2e-7;
 // 8192: 1.2e-7 against 1.4e-7).
-// Measured on 152064 x 3584, us (LDS kernel, which streams the vocabulary once per 4 rows -> this one): 1 row 189 -> 206, 2: 205 -> 206,
-// 3: 271 -> 209, 8: 584 -> 207 (5.3 TB/s; a copy reaches 4.9), 10: 805 -> 217, 11: 860 -> 250 (a second group's operand comes
-// from L2 beside the stream).
+// Measured on 152064 x 3584, us (LDS kernel, which streams the vocabulary once per 4 rows -> this one; without the streaming hint on both
+// sides): 1 row 189 -> 206, 2: 205 -> 206, 3: 271 -> 209, 8: 584 -> 207, 10: 805 -> 217, 11: 860 -> 250 (a second group's operand comes
+// from L2 beside the stream); now 3 rows 182, 8: 186 (5.9 TB/s), 11: 230, 22: 415, and 1 and 2 rows in the LDS kernel 170 and 177.
 constexpr int LM_MFMA_ROWS = 3;   // from this many rows on
 constexpr int LM_GROUP = 10;      // rows per B operand
 constexpr int LM_MAX_GROUPS = 2;  // B operands per launch (three spill: 525 us for 30 rows, two passes take 470)
@@ -264,7 +273,7 @@ __global__ __launch_bounds__(256) void final_norm_split_kernel(const bf16* __res
 }
 
 constexpr int LM_SLOTS = 4;
-template <int NG>
+template <int NG, bool ONCE>
 __global__ __launch_bounds__(256, 1) void lm_head_mfma_kernel(const bf16* __restrict__ w, const bf16* __restrict__ hb,
                                                               float* __restrict__ logits, int R, int vocab, int H) {
     constexpr int PAD = 33;   // a column's 32 sums, padded: neighbouring columns start in different banks
@@ -321,7 +330,7 @@ __global__ __launch_bounds__(256, 1) void lm_head_mfma_kernel(const bf16* __rest
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr)(uintptr_t)(uint32_t)(uintptr_t)(ring + wave * SLOT + i * 1024), 16,
-                                                     src[i & 1] + off + (uint32_t)(i >> 1) * 16u * row_bytes, 0, 0, 0);
+                                                     src[i & 1] + off + (uint32_t)(i >> 1) * 16u * row_bytes, 0, 0, ONCE ? LM_ONCE : 0);
         if (++l_s == ns4) {
             l_s = 0;
             ++l_tile;

@@ -1614,27 +1614,30 @@ rs_status rs_lm_head(rs_ctx* c, const void* final_norm_gain, const void* w_lm, i
     if (!c->has_device) return fail(RS_EHIP, "no HIP device");
     if (c->lm_rows == 0) {  // first use on this context: opt in to the LDS size once
         const int rows = (int)std::min<size_t>(LM_ROWS, LDS_BYTES / ((size_t)H * 4));
-        RS_HIP(hipFuncSetAttribute((const void*)lm_head_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, rows * H * 4));
+        RS_HIP(hipFuncSetAttribute((const void*)lm_head_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, rows * H * 4));
+        RS_HIP(hipFuncSetAttribute((const void*)lm_head_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, rows * H * 4));
         c->lm_rows = rows;
     }
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     // Three rows and more go through the matrix pipe, up to 20 per pass over the vocabulary.  One or two, which the LDS kernel
-    // streams as fast (189 and 205 us on 152064 x 3584, against 206), and a workspace of 4 H bytes per row, which holds no
+    // streams as fast (170 and 177 us on 152064 x 3584, against 182), and a workspace of 4 H bytes per row, which holds no
     // split rows, take that kernel.
+    const size_t w_bytes = (size_t)vocab * H * 2;
+    const bool once = w_bytes >= LM_STREAM_BYTES;
     if (n_rows >= LM_MFMA_ROWS && workspace_bytes >= lm_head_bytes_split(c, n_rows)) {
         bf16* hb = reinterpret_cast<bf16*>(workspace);
         hipLaunchKernelGGL(final_norm_split_kernel, dim3(LM_GROUP + 1, (n_rows + LM_GROUP - 1) / LM_GROUP), dim3(256), 0, st, (const bf16*)x,
                            (const bf16*)final_norm_gain, hb, n_rows, H, c->cfg.rms_eps);
         RS_HIP(hipGetLastError());
         // (one workgroup per compute unit; more if a share would not fit the kernel's 32-bit offsets)
-        const size_t w_bytes = (size_t)vocab * H * 2;
         const dim3 grid((unsigned)std::min<size_t>(std::max<size_t>(c->n_cu, (w_bytes >> 30) + 1), (vocab + LM_VROWS - 1) / LM_VROWS));
         for (int r0 = 0; r0 < n_rows; r0 += LM_MAX_GROUPS * LM_GROUP) {
             const int R = std::min(LM_MAX_GROUPS * LM_GROUP, n_rows - r0), groups = (R + LM_GROUP - 1) / LM_GROUP;
             const bf16* hg = hb + (size_t)(r0 / LM_GROUP) * H * 32;
             float* lg = reinterpret_cast<float*>(logits) + (size_t)r0 * vocab;
             const auto launch = [&](auto ng) {
-                hipLaunchKernelGGL(lm_head_mfma_kernel<decltype(ng)::value>, grid, dim3(256), 0, st, (const bf16*)w_lm, hg, lg, R, vocab, H);
+                if (once) hipLaunchKernelGGL((lm_head_mfma_kernel<decltype(ng)::value, true>), grid, dim3(256), 0, st, (const bf16*)w_lm, hg, lg, R, vocab, H);
+                else hipLaunchKernelGGL((lm_head_mfma_kernel<decltype(ng)::value, false>), grid, dim3(256), 0, st, (const bf16*)w_lm, hg, lg, R, vocab, H);
             };
             if (groups == 1) launch(std::integral_constant<int, 1>{});
             else launch(std::integral_constant<int, 2>{});
@@ -1649,7 +1652,7 @@ rs_status rs_lm_head(rs_ctx* c, const void* final_norm_gain, const void* w_lm, i
     const int blocks = std::min(4 * c->n_cu, (vocab + 4 * LM_VGROUP - 1) / (4 * LM_VGROUP));
     for (int r0 = 0; r0 < n_rows; r0 += c->lm_rows) {  // the vocabulary matrix is streamed once per group of rows
         const int R = std::min(c->lm_rows, n_rows - r0);
-        hipLaunchKernelGGL(lm_head_kernel, dim3(blocks), dim3(256), (size_t)R * H * 4, st, (const bf16*)w_lm, (const float*)(h + (size_t)r0 * H),
+        hipLaunchKernelGGL(once ? lm_head_kernel<true> : lm_head_kernel<false>, dim3(blocks), dim3(256), (size_t)R * H * 4, st, (const bf16*)w_lm, (const float*)(h + (size_t)r0 * H),
                            reinterpret_cast<float*>(logits) + (size_t)r0 * vocab, R, vocab, H);
         RS_HIP(hipGetLastError());
     }
