@@ -26,6 +26,19 @@
 // rows to a workgroup (their 16-byte chunks of one half k-step are one cache line).
 // Before, 32 lanes shared a row in 14 steps, whatever the call.  us per step between events, 7B shape in a stack (sums of 4 planes): 1 row
 // 14.0 -> 7.1, 64: 19.0 -> 7.9, 250: 19.7 -> 11.5, 512: 19.2 -> 15.4, 1000: 20.9 -> 19.5, 2048: 22.2 -> 21.9; 72B, 64 rows 30.9 -> 10.3.
+// In calls whose QKV projection stores k and v straight into the caches (EPI_QKV_APPEND), the first kernel also copies the rows' places
+// there (KVRow), and zeroes what their last 64-token blocks of V^T hold behind the call's last token: `tails`, one per request, read from
+// the host buffer.
+struct KVTail {
+    uint64_t v;            // the request's last V^T tile [d][64] of KV head 0
+    uint64_t head_bytes;   // from one KV head's tile to the next one's
+    int first, pad_;       // the first place behind the last token: 1..64
+};
+struct AppendPrep {
+    uint4* dst;            // where the chunks behind the descriptors go (first the tails, then the KVRows)
+    int chunks;
+    int tails, hkv, d;     // requests, KV heads, features of a head; tails = 0: nothing to do
+};
 struct ReduceSource {
     const float* partial;   // [splits][rows][H] fp32
     int splits;             // 2..PLANES
@@ -39,15 +52,29 @@ __global__ __launch_bounds__(WPR == 4 ? 256 : 64 * RMS_ROWS) void rms_and_fragme
                                                                      float* __restrict__ inv_rms, int rows, int H, float eps,
                                                                      const uint4* __restrict__ desc_src,
                                                                      uint4* __restrict__ desc_dst, int desc_chunks,
-                                                                     ReduceSource red) {
+                                                                     ReduceSource red, AppendPrep app) {
     static_assert(WPR == 1 || WPR == 4, "wavefronts per row");
     constexpr bool REDUCE = PLANES > 0;
     // (the copying workgroups come first in the grid: their reads cross the host link, several microseconds each, and
     // should be under way while the row blocks stream; launched last they were the tail of the kernel)
-    const int desc_blocks = (desc_chunks + (int)blockDim.x - 1) / (int)blockDim.x;
+    const int desc_blocks = (desc_chunks + app.chunks + (int)blockDim.x - 1) / (int)blockDim.x;
     if ((int)blockIdx.x < desc_blocks) {
         const int i = (int)blockIdx.x * (int)blockDim.x + (int)threadIdx.x;
         if (i < desc_chunks) desc_dst[i] = desc_src[i];
+        else if (i < desc_chunks + app.chunks) app.dst[i - desc_chunks] = desc_src[i];
+        return;
+    }
+    const int row_blocks = WPR == 4 ? rows : (rows + RMS_ROWS - 1) / RMS_ROWS;
+    if ((int)blockIdx.x >= desc_blocks + row_blocks) {   // a request's tail of one KV head
+        const int z = (int)blockIdx.x - desc_blocks - row_blocks;
+        const KVTail tail = reinterpret_cast<const KVTail*>(desc_src + desc_chunks)[z / app.hkv];
+        char* const tile = reinterpret_cast<char*>(tail.v) + (size_t)(z % app.hkv) * tail.head_bytes;
+        for (int i = threadIdx.x; i < app.d * 8; i += (int)blockDim.x) {   // feature i / 8, tokens 8 (i % 8) ..
+            const int t0 = (i & 7) * 8;
+            if (t0 >= tail.first) st_global_16(tile + (size_t)i * 16, make_uint4(0u, 0u, 0u, 0u));
+            else
+                for (int t = max(t0, tail.first); t < t0 + 8; ++t) *reinterpret_cast<bf16*>(tile + (size_t)(i >> 3) * 128 + t * 2) = f32_to_bf16(0.0f);
+        }
         return;
     }
     const int lane = threadIdx.x & 63;

@@ -35,7 +35,14 @@ enum GemmEpilogue {
     EPI_RESIDUAL = 1,  // out = bf16(acc + resid[m, n])
     EPI_SWIGLU = 2,    // each unit holds 16 gate rows then the 16 up rows of the same features:
                        // out[m, 16 unit + f] = bf16(silu(gate * row_scale[m]) * (up * row_scale[m]))
-    EPI_PARTIAL = 3    // split-K: fp32 partial sums to partial[split][m][n]
+    EPI_PARTIAL = 3,   // split-K: fp32 partial sums to partial[split][m][n]
+    EPI_QKV_APPEND = 4 // EPI_QKV_ROPE with the k and v columns stored where the row's token has its place in the cache (kv_rows)
+};
+
+// The place of a row's token in its (bfloat16) cache: addresses of its K row and of its column of the V^T tile, both of KV head 0, and
+// the distance from one KV head to the next.
+struct KVRow {
+    uint64_t k, v, head_bytes;
 };
 
 struct GemmArgs {
@@ -56,6 +63,8 @@ struct GemmArgs {
     int mrope_b0, mrope_b1;  // rotary pair j uses axis 0 if j < b0, axis 1 if j < b1, else axis 2 (1-D RoPE: b0 = b1 = d/2)
     const float2* rope_cs;   // [max_pos][head_dim/2] (cos, sin)
     int rope_cols;           // columns [0, rope_cols) are q and k heads (a multiple of head_dim)
+    const KVRow* kv_rows;    // [M] EPI_QKV_APPEND
+    int q_cols;              // columns [0, q_cols) are q heads (EPI_QKV_APPEND)
     int head_dim;            // 64 or 128
     int ldo, ldr;
     int out_frag, resid_frag;
@@ -142,7 +151,7 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
                 // lower lanes: features 16u..16u+7 (first half of the k-step), upper lanes: 16u+8..16u+15 (second half)
                 __builtin_amdgcn_raw_buffer_store_b128(pair_runs(o[0], o[1]), r_out, oblk + (uint32_t)(unit0 + i) * 1024u, 0, 0);
             }
-        } else if constexpr (EPI == EPI_QKV_ROPE) {
+        } else if constexpr (EPI == EPI_QKV_ROPE || EPI == EPI_QKV_APPEND) {
             const __amdgpu_buffer_rsrc_t r_out = __builtin_amdgcn_make_buffer_rsrc((void*)a.out, 0, a.M * a.ldo * 2, RSRC_FLAGS);
             const __amdgpu_buffer_rsrc_t r_sc = __builtin_amdgcn_make_buffer_rsrc((void*)a.row_scale, 0, a.M * 4, RSRC_FLAGS);
             const __amdgpu_buffer_rsrc_t r_pos = __builtin_amdgcn_make_buffer_rsrc((void*)a.row_pos, 0, a.M * 12, RSRC_FLAGS);
@@ -153,6 +162,9 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
             const int hd2 = a.head_dim >> 1;
             const int uph_shift = (a.head_dim == 128) ? 2 : 1;  // a head is 4 or 2 units
             const uint32_t orow = (uint32_t)m * (uint32_t)a.ldo * 2u;
+            KVRow kv{};
+            if constexpr (EPI == EPI_QKV_APPEND)
+                if ((unit0 + NT) * 32 > a.q_cols) kv = a.kv_rows[min(m, a.M - 1)];
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
                 if (i >= live) break;
@@ -193,9 +205,18 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
                         ohq[q] = oh;
                     }
                     // lower lanes store features 0..7 of the unit's 16, upper lanes 8..15, as whole 16-byte chunks
-                    const uint32_t col = (uint32_t)((gu >> uph_shift) * a.head_dim + uh * 16 + 8 * half);
-                    __builtin_amdgcn_raw_buffer_store_b128(pair_runs(olq[0], olq[1]), r_out, orow + col * 2u, 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b128(pair_runs(ohq[0], ohq[1]), r_out, orow + (col + (uint32_t)hd2) * 2u, 0, 0);
+                    const u32x4 lo = pair_runs(olq[0], olq[1]), hi = pair_runs(ohq[0], ohq[1]);
+                    const uint32_t in_head = (uint32_t)(uh * 16 + 8 * half), col = (uint32_t)((gu >> uph_shift) * a.head_dim) + in_head;
+                    if (EPI == EPI_QKV_APPEND && gu * 32 >= a.q_cols) {   // a K head: into the cache
+                        char* const dst = reinterpret_cast<char*>(kv.k) + (size_t)((gu - (a.q_cols >> 5)) >> uph_shift) * kv.head_bytes + in_head * 2u;
+                        if (m < a.M) {
+                            *reinterpret_cast<u32x4*>(dst) = lo;
+                            *reinterpret_cast<u32x4*>(dst + hd2 * 2) = hi;
+                        }
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b128(lo, r_out, orow + col * 2u, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b128(hi, r_out, orow + (col + (uint32_t)hd2) * 2u, 0, 0);
+                    }
                 } else {
                     bf16x4 o[4];
 #pragma unroll
@@ -210,10 +231,22 @@ RS_DEVICE void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NT][NJ], int m_bas
 #pragma unroll
                         for (int e = 0; e < 4; ++e) o[q][e] = f32_to_bf16(acc[i][j][4 * q + e] * sc + b[e]);
                     }
+                    if constexpr (EPI == EPI_QKV_APPEND) {   // (32 lanes hold consecutive tokens: 64 contiguous bytes per feature and store)
+                        const int vu = gu - (a.rope_cols >> 5);
+                        char* const dst = reinterpret_cast<char*>(kv.v) + (size_t)(vu >> uph_shift) * kv.head_bytes +
+                                          (size_t)((vu & ((1 << uph_shift) - 1)) * 32 + 4 * half) * 128u;
+                        if (m < a.M) {
 #pragma unroll
-                    for (int pr = 0; pr < 2; ++pr)
-                        __builtin_amdgcn_raw_buffer_store_b128(pair_runs(o[2 * pr], o[2 * pr + 1]), r_out,
-                                                               orow + (uint32_t)(gu * 32 + 16 * pr + 8 * half) * 2u, 0, 0);
+                            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) *reinterpret_cast<bf16*>(dst + (8 * q + e) * 128) = o[q][e];
+                        }
+                    } else {
+#pragma unroll
+                        for (int pr = 0; pr < 2; ++pr)
+                            __builtin_amdgcn_raw_buffer_store_b128(pair_runs(o[2 * pr], o[2 * pr + 1]), r_out,
+                                                                   orow + (uint32_t)(gu * 32 + 16 * pr + 8 * half) * 2u, 0, 0);
+                    }
                 }
             }
         } else if constexpr (EPI == EPI_PARTIAL) {

@@ -185,8 +185,11 @@ struct rs_kv {
 
 namespace {
 
+constexpr int TILE_ROWS = 1024;   // rows of the calls whose projections may run on tiles (choose_route)
+
 struct DescSizes {
     size_t reqs, items, vblocks, rowpos, pagetab, mitems, fp8, total;
+    size_t append;   // behind total, in the staging buffer only (KVTails and KVRows)
 };
 
 DescSizes desc_sizes(const rs_ctx* c, int max_tokens, int max_requests) {
@@ -202,6 +205,7 @@ DescSizes desc_sizes(const rs_ctx* c, int max_tokens, int max_requests) {
     d.pagetab = align_up(sizeof(int) * (size_t)std::max(max_requests, 1) * ((size_t)c->cfg.max_pos / 64 + 2), 256);
     d.mitems = align_up(sizeof(AttnMergeItem) * ATT_SPLIT_SLOTS, 256);
     d.fp8 = align_up(sizeof(Fp8CacheDesc) * std::max(max_requests, 1), 256);
+    d.append = align_up(sizeof(KVTail) * std::max(max_requests, 1) + sizeof(KVRow) * std::min(max_tokens, TILE_ROWS), 256);
     d.total = d.reqs + d.items + d.vblocks + d.rowpos + d.pagetab + d.mitems + d.fp8;
     return d;
 }
@@ -309,7 +313,6 @@ constexpr int RMS_FEW_ROWS = 704;
 // Against measurement (us between events, 3 of them the events'; 7B shape): QKV 250 rows on 64 x 128 27.4 (30.8), 512 on 128 x 96 31
 // (35), 1000 on 128 x 160 38.9 (46.8); O 64 rows on 64 x 64 in 4 ranges 14.6 (15.8), 250 on 64 x 64 19.8 (22.0); down 64 rows on
 // 64 x 128 in 8 ranges 33 (29.5, its reduction not in it), 250 on 128 x 128 in 4 64 (56.5, likewise).  The estimates rank; they do not predict.
-constexpr int TILE_ROWS = 1024;
 constexpr int TILE_SHAPES = 6;
 constexpr int TILE_BLOCKS[TILE_SHAPES] = {2, 2, 4, 4, 4, 4}, TILE_UNITS[TILE_SHAPES] = {2, 4, 2, 3, 4, 5};
 double step_ns(double blocks, double units, int steps) {
@@ -372,7 +375,7 @@ template <int EPI>
 rs_status launch_tile(int shape, const GemmArgs& a, int splits, hipStream_t st, int* columns_out = nullptr) {
     if (shape == 0) return launch_tile_shape<EPI, 2, 2>(a, splits, st, columns_out);
     if (shape == 1) return launch_tile_shape<EPI, 2, 4>(a, splits, st, columns_out);
-    if constexpr (EPI == EPI_QKV_ROPE) {
+    if constexpr (EPI == EPI_QKV_ROPE || EPI == EPI_QKV_APPEND) {
         if (shape == 3) return launch_tile_shape<EPI, 4, 3>(a, splits, st, columns_out);
         return launch_tile_shape<EPI, 4, 5>(a, splits, st, columns_out);
     } else {
@@ -535,7 +538,7 @@ template <int D>
 rs_status launch_attention_path(const rs_ctx* c, bf16* qkv, bf16* attn, const ReqDesc* d_reqs,
                                 const AttnItem* d_items, int n_items, int att_waves, const KVBlockItem* d_vb, int n_vb, bool any_paged,
                                 float* split_buf, const AttnMergeItem* d_mitems, int n_mitems, const Fp8CacheDesc* d_fp8, int n_reqs,
-                                int n_xblocks, hipStream_t st, const StepTimer& tm) {
+                                int n_xblocks, bool append, hipStream_t st, const StepTimer& tm) {
     const rs_layer_cfg& f = c->cfg;
     tm.begin(RS_STEP_APPEND_KV);
     if (d_fp8) {  // 8-bit caches: quantise the new rows into them, then expand what the rows can see for the attention kernel
@@ -543,7 +546,7 @@ rs_status launch_attention_path(const rs_ctx* c, bf16* qkv, bf16* attn, const Re
                            d_reqs, d_fp8, d_vb, f.n_q_heads, f.n_kv_heads);
         RS_HIP(hipGetLastError());
         hipLaunchKernelGGL(kv_expand_fp8_kernel<D>, dim3(n_xblocks, f.n_kv_heads), dim3(256), 0, st, d_reqs, d_fp8, n_reqs);
-    } else {
+    } else if (append) {
         hipLaunchKernelGGL(append_kv_kernel<D>, dim3(n_vb, f.n_kv_heads), dim3(256), 0, st, (const bf16*)qkv, c->qkv_dim,
                            d_reqs, d_vb, f.n_q_heads, f.n_kv_heads);
     }
@@ -795,6 +798,13 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     char* wsb = reinterpret_cast<char*>(ws);
     const int* d_pagetab = reinterpret_cast<const int*>(wsb + L.desc + ds.reqs + ds.items + ds.vblocks + ds.rowpos);
     std::vector<AttnRequest> att_reqs;
+    // calls of few rows on bfloat16 caches: k and v go straight from the QKV projection into them
+    const bool qkv_few = skinny_qkv(ctx, T, f.hidden);
+    const int qkv_shape = qkv_few ? -1 : choose_route(ctx, T, ctx->qkv_dim / 32, f.hidden / GS_BK, 1, 1, 1, QKV_SHAPES).shape;
+    const bool fused_append = T <= TILE_ROWS && (qkv_few || qkv_shape >= 0) && !kvs[0]->fp8;
+    std::vector<KVTail> tails;
+    std::vector<KVRow> kv_places;
+    if (fused_append) kv_places.reserve(T);
     int row0 = 0;
     for (int i = 0; i < R; ++i) {
         const int Ti = lens[i];
@@ -829,6 +839,24 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         const int ri = (int)reqs.size();
         reqs.push_back(d);
         att_reqs.push_back(AttnRequest{Ti, P});
+        if (fused_append) {
+            const size_t tile = (size_t)64 * f.head_dim * 2, head = kv->paged() ? tile : (size_t)kv->cap * f.head_dim * 2;
+            KVRow at{};
+            at.head_bytes = head;
+            for (int p = P; p < P + Ti; ++p) {
+                if (p == P || p % 64 == 0) {   // the tiles of token p's block, KV head 0
+                    if (kv->paged()) {
+                        at.k = (uint64_t)(uintptr_t)kv->pool->base + (size_t)kv->pages[layer][p / 64] * kv->pool->page_bytes;
+                        at.v = at.k + (size_t)f.n_kv_heads * tile;
+                    } else {
+                        at.k = (uint64_t)(uintptr_t)kv->k_of(layer) + (size_t)(p / 64) * tile;
+                        at.v = (uint64_t)(uintptr_t)kv->vt_of(layer) + (size_t)(p / 64) * tile;
+                    }
+                }
+                kv_places.push_back(KVRow{at.k + (size_t)(p % 64) * f.head_dim * 2, at.v + (size_t)(p % 64) * 2, head});
+            }
+            tails.push_back(KVTail{at.v, head, (P + Ti - 1) % 64 + 1, 0});
+        }
         for (int b = P / 64; b <= (P + Ti - 1) / 64; ++b) vbs.push_back(KVBlockItem{ri, b});
         for (int t = 0; t < Ti; ++t)
             for (int ax = 0; ax < 3; ++ax) rowpos.push_back(positions3 ? positions3[3 * (size_t)(row0 + t) + ax] : P + t);
@@ -846,7 +874,7 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         sizeof(KVBlockItem) * vbs.size() > ds.vblocks || sizeof(int) * rowpos.size() > ds.rowpos ||
         sizeof(int) * pagetab.size() > ds.pagetab || sizeof(AttnMergeItem) * mitems.size() > ds.mitems ||
         sizeof(Fp8CacheDesc) * fp8s.size() > ds.fp8 || (!fp8s.empty() && fp8s.size() != reqs.size()) ||
-        ds.total > ctx->slot_bytes)
+        sizeof(KVTail) * tails.size() + sizeof(KVRow) * kv_places.size() > ds.append || ds.total + ds.append > ctx->slot_bytes)
         return fail(RS_EINVAL, "internal: descriptor sizing");
 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
@@ -881,6 +909,11 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     memcpy(stage + ds.reqs + ds.items + ds.vblocks + ds.rowpos, pagetab.data(), sizeof(int) * pagetab.size());
     memcpy(stage + ds.reqs + ds.items + ds.vblocks + ds.rowpos + ds.pagetab, mitems.data(), sizeof(AttnMergeItem) * mitems.size());
     memcpy(stage + ds.reqs + ds.items + ds.vblocks + ds.rowpos + ds.pagetab + ds.mitems, fp8s.data(), sizeof(Fp8CacheDesc) * fp8s.size());
+    // (behind the descriptors; the first kernel copies them to where the SwiGLU output will be, which is free until then)
+    const size_t append_bytes = fused_append ? align_up(sizeof(KVTail) * tails.size() + sizeof(KVRow) * kv_places.size(), 16) : 0;
+    memcpy(stage + ds.total, tails.data(), sizeof(KVTail) * tails.size());
+    memcpy(stage + ds.total + sizeof(KVTail) * tails.size(), kv_places.data(), sizeof(KVRow) * kv_places.size());
+    const KVRow* const kv_rows = fused_append ? reinterpret_cast<const KVRow*>(wsb + L.act + sizeof(KVTail) * tails.size()) : nullptr;
     // (the first kernel below copies the staged descriptors into the workspace; the slot is free again once it has run)
     const ReqDesc* d_reqs = reinterpret_cast<const ReqDesc*>(wsb + L.desc);
     const AttnItem* d_items = reinterpret_cast<const AttnItem*>(wsb + L.desc + ds.reqs);
@@ -915,12 +948,13 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     // (the pending sum reads the previous layer's r and partial planes, which this layer overwrites only later)
     const bool pending = pending_in && pending_in->splits > 0;
     const ReduceSource red = pending ? ReduceSource{pending_in->partial, pending_in->splits, pending_in->resid, pending_in->out} : ReduceSource{};
+    const AppendPrep app{reinterpret_cast<uint4*>(wsb + L.act), (int)(append_bytes / 16), (int)tails.size(), f.n_kv_heads, f.head_dim};
     const auto first_kernel = [&](auto planes, auto wpr) {
         constexpr int WPR = decltype(wpr)::value, THREADS = WPR == 4 ? 256 : 64 * RMS_ROWS;
         hipLaunchKernelGGL((rms_and_fragment_major_kernel<decltype(planes)::value, WPR>),
-                           dim3((WPR == 4 ? T : (T + RMS_ROWS - 1) / RMS_ROWS) + (desc_chunks + THREADS - 1) / THREADS), dim3(THREADS), 0, st, xb, xf,
+                           dim3((WPR == 4 ? T : (T + RMS_ROWS - 1) / RMS_ROWS) + (desc_chunks + app.chunks + THREADS - 1) / THREADS + app.tails * app.hkv), dim3(THREADS), 0, st, xb, xf,
                            inv_rms1, T, H, f.rms_eps, reinterpret_cast<const uint4*>(ctx->pinned_dev[slot]),
-                           reinterpret_cast<uint4*>(wsb + L.desc), desc_chunks, red);
+                           reinterpret_cast<uint4*>(wsb + L.desc), desc_chunks, red, app);
     };
     const auto first_kernel_planes = [&](auto wpr) {
         if (!pending) first_kernel(std::integral_constant<int, 0>{}, wpr);
@@ -949,22 +983,20 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         a.rope_cols = ctx->q_dim + ctx->kv_dim; a.head_dim = f.head_dim;
         a.mrope_b0 = ctx->mrope_b0; a.mrope_b1 = ctx->mrope_b1;
         a.M = T; a.N = ctx->qkv_dim; a.K = H;
-        if (skinny_qkv(ctx, T, H)) {
-            s = launch_skinny_rows<EPI_QKV_ROPE>(a, st);
-        } else {
-            const int shape = choose_route(ctx, T, ctx->qkv_dim / 32, H / GS_BK, 1, 1, 1, QKV_SHAPES).shape;
-            s = shape >= 0 ? launch_tile<EPI_QKV_ROPE>(shape, a, 1, st) : launch_gemm<EPI_QKV_ROPE>(ctx, a, 1, st);
-        }
+        a.kv_rows = kv_rows; a.q_cols = ctx->q_dim;
+        if (fused_append) s = qkv_few ? launch_skinny_rows<EPI_QKV_APPEND>(a, st) : launch_tile<EPI_QKV_APPEND>(qkv_shape, a, 1, st);
+        else if (qkv_few) s = launch_skinny_rows<EPI_QKV_ROPE>(a, st);
+        else s = qkv_shape >= 0 ? launch_tile<EPI_QKV_ROPE>(qkv_shape, a, 1, st) : launch_gemm<EPI_QKV_ROPE>(ctx, a, 1, st);
         if (s != RS_OK) return s;
     }
     tm.end(RS_STEP_QKV_GEMM);
     // cache append, attention
     if (f.head_dim == 128)
         s = launch_attention_path<128>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), plan.waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
-                                       attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, st, tm);
+                                       attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, kv_rows == nullptr, st, tm);
     else
         s = launch_attention_path<64>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), plan.waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
-                                      attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, st, tm);
+                                      attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, kv_rows == nullptr, st, tm);
     if (s != RS_OK) return s;
     // r = x + attn Wo^T, and 1/rms of every row of r (the second RMSNorm; its gain lives in the packed W_gate_up)
     tm.begin(RS_STEP_O_GEMM);
@@ -1041,7 +1073,7 @@ rs_status rs_ctx_create(const rs_layer_cfg* cfg, rs_ctx** out) {
     if (const char* e = getenv("RS_ATTN_SPLIT")) c->attn_split = std::max(0, std::min(atoi(e), ATT_MAX_PARTS));
     auto cleanup = [&](rs_status s) { rs_ctx_destroy(c); return s; };
 
-    c->slot_bytes = desc_sizes(c, f.max_tokens_per_call, f.max_requests).total;
+    c->slot_bytes = desc_sizes(c, f.max_tokens_per_call, f.max_requests).total + desc_sizes(c, f.max_tokens_per_call, f.max_requests).append;
     int n_dev = 0;
     if (hipGetDeviceCount(&n_dev) != hipSuccess || n_dev <= 0) {
         (void)hipGetLastError();
@@ -1092,6 +1124,7 @@ rs_status rs_ctx_create(const rs_layer_cfg* cfg, rs_ctx** out) {
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_SWIGLU, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_strip_kernel<EPI_PARTIAL, true>, hipFuncAttributeMaxDynamicSharedMemorySize, GS_LDS_BYTES);
     e = allow_tile_lds<EPI_QKV_ROPE, 4, 5>(allow_tile_lds<EPI_QKV_ROPE, 4, 3>(allow_tile_lds<EPI_QKV_ROPE, 2, 4>(allow_tile_lds<EPI_QKV_ROPE, 2, 2>(e))));
+    e = allow_tile_lds<EPI_QKV_APPEND, 4, 5>(allow_tile_lds<EPI_QKV_APPEND, 4, 3>(allow_tile_lds<EPI_QKV_APPEND, 2, 4>(allow_tile_lds<EPI_QKV_APPEND, 2, 2>(e))));
     e = allow_tile_lds<EPI_RESIDUAL, 4, 4>(allow_tile_lds<EPI_RESIDUAL, 4, 2>(allow_tile_lds<EPI_RESIDUAL, 2, 4>(allow_tile_lds<EPI_RESIDUAL, 2, 2>(e))));
     e = allow_tile_lds<EPI_PARTIAL, 4, 4>(allow_tile_lds<EPI_PARTIAL, 4, 2>(allow_tile_lds<EPI_PARTIAL, 2, 4>(allow_tile_lds<EPI_PARTIAL, 2, 2>(e))));
     if (e != hipSuccess) return cleanup(fail(RS_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e)));
