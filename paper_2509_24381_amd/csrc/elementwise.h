@@ -20,12 +20,14 @@
 // as the layers called one by one, without the previous layer's reduction kernel and this layer's pass over its output.
 //
 // The order of a row's sum is one for all forms and sizes (K and V of a token must not depend on the call, to the bit): 16-byte chunk
-// c of the row belongs to lane c % 256; a lane adds its chunks in ascending order, each 64 lanes add up in a butterfly, the four sums
-// in ascending order.  WPR = 4 spreads the 256 lanes over the four wavefronts of a workgroup, a row each: with few rows the kernel is a
-// chain of memory latencies, and this way every load of a row is in flight at once.  WPR = 1 gives a wavefront the whole row, eight
-// rows to a workgroup (their 16-byte chunks of one half k-step are one cache line).
+// c of the row belongs to place c % 256; a place adds its chunks in ascending order, each 64 places add up in a butterfly, the four sums
+// in ascending order.  LANES = 256 spreads the places over the four wavefronts of a workgroup, a row each: with few rows the kernel is a
+// chain of memory latencies, and this way every load of a row is in flight at once.  LANES = 32 gives a row half a wavefront, whose lanes
+// hold eight places each, and a workgroup eight rows: their 16-byte chunks of one half k-step are one cache line (with a wavefront per
+// row, 64 lines touched by a store, 2048 rows of 8192 took 33 us instead of 25).
 // Before, 32 lanes shared a row in 14 steps, whatever the call.  us per step between events, 7B shape in a stack (sums of 4 planes): 1 row
-// 14.0 -> 7.1, 64: 19.0 -> 7.9, 250: 19.7 -> 11.5, 512: 19.2 -> 15.4, 1000: 20.9 -> 19.5, 2048: 22.2 -> 21.9; 72B, 64 rows 30.9 -> 10.3.
+// 14.0 -> 7.1, 64: 19.0 -> 7.9, 250: 19.7 -> 11.1, 512: 19.2 -> 15.4, 1000: 20.9 -> 19.2, 2048: 23.2 -> 22.1 (14.7 -> 13.4 without a sum);
+// 72B, 64 rows 30.9 -> 8.7, 720 rows 32.1 -> 26.6, 2048 rows without a sum 24.2 -> 23.0.
 // In calls whose QKV projection stores k and v straight into the caches (EPI_QKV_APPEND), the first kernel also copies the rows' places
 // there (KVRow), and zeroes what their last 64-token blocks of V^T hold behind the call's last token: `tails`, one per request, read from
 // the host buffer.
@@ -38,6 +40,7 @@ struct AppendPrep {
     uint4* dst;            // where the chunks behind the descriptors go (first the tails, then the KVRows)
     int chunks;
     int tails, hkv, d;     // requests, KV heads, features of a head; tails = 0: nothing to do
+    KVTail only;           // tails = 1: that one, so that nothing waits for the host link
 };
 struct ReduceSource {
     const float* partial;   // [splits][rows][H] fp32
@@ -46,15 +49,15 @@ struct ReduceSource {
     bf16* y;                // [rows, H] row-major
 };
 // PLANES = 0 takes the rows from x; else the most planes that are summed.
-constexpr int RMS_ROWS = 8;   // rows per workgroup with WPR = 1
-template <int PLANES, int WPR>
-__global__ __launch_bounds__(WPR == 4 ? 256 : 64 * RMS_ROWS) void rms_and_fragment_major_kernel(const bf16* __restrict__ x, bf16* __restrict__ dst,
+constexpr int RMS_ROWS = 8;   // rows per workgroup with LANES = 32
+template <int PLANES, int LANES>
+__global__ __launch_bounds__(256) void rms_and_fragment_major_kernel(const bf16* __restrict__ x, bf16* __restrict__ dst,
                                                                      float* __restrict__ inv_rms, int rows, int H, float eps,
                                                                      const uint4* __restrict__ desc_src,
                                                                      uint4* __restrict__ desc_dst, int desc_chunks,
                                                                      ReduceSource red, AppendPrep app) {
-    static_assert(WPR == 1 || WPR == 4, "wavefronts per row");
-    constexpr bool REDUCE = PLANES > 0;
+    static_assert(LANES == 256 || LANES == 32, "lanes per row");
+    constexpr bool REDUCE = PLANES > 0, FEW = LANES == 256;
     // (the copying workgroups come first in the grid: their reads cross the host link, several microseconds each, and
     // should be under way while the row blocks stream; launched last they were the tail of the kernel)
     const int desc_blocks = (desc_chunks + app.chunks + (int)blockDim.x - 1) / (int)blockDim.x;
@@ -64,10 +67,10 @@ __global__ __launch_bounds__(WPR == 4 ? 256 : 64 * RMS_ROWS) void rms_and_fragme
         else if (i < desc_chunks + app.chunks) app.dst[i - desc_chunks] = desc_src[i];
         return;
     }
-    const int row_blocks = WPR == 4 ? rows : (rows + RMS_ROWS - 1) / RMS_ROWS;
+    const int row_blocks = FEW ? rows : (rows + RMS_ROWS - 1) / RMS_ROWS;
     if ((int)blockIdx.x >= desc_blocks + row_blocks) {   // a request's tail of one KV head
         const int z = (int)blockIdx.x - desc_blocks - row_blocks;
-        const KVTail tail = reinterpret_cast<const KVTail*>(desc_src + desc_chunks)[z / app.hkv];
+        const KVTail tail = app.tails == 1 ? app.only : reinterpret_cast<const KVTail*>(desc_src + desc_chunks)[z / app.hkv];
         char* const tile = reinterpret_cast<char*>(tail.v) + (size_t)(z % app.hkv) * tail.head_bytes;
         for (int i = threadIdx.x; i < app.d * 8; i += (int)blockDim.x) {   // feature i / 8, tokens 8 (i % 8) ..
             const int t0 = (i & 7) * 8;
@@ -77,70 +80,81 @@ __global__ __launch_bounds__(WPR == 4 ? 256 : 64 * RMS_ROWS) void rms_and_fragme
         }
         return;
     }
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int m = WPR == 4 ? (int)blockIdx.x - desc_blocks : ((int)blockIdx.x - desc_blocks) * RMS_ROWS + wave;
-    if (m >= rows) return;   // (WPR = 4: never; WPR = 1: the whole wavefront)
-    // chunk k of a pass of 256: WPR = 4 has pass u of the wavefront's 64 lanes in flight as chunk u, WPR = 1 the four quarters of one pass
-    constexpr int U = WPR == 4 ? 2 : 4;
-    constexpr int SPAN = WPR == 4 ? U * 256 : 256, STRIDE = WPR == 4 ? 256 : 64;
-    const int c = WPR == 4 ? wave * 64 + lane : lane;
+    const int c = (int)threadIdx.x % LANES;
+    const int m = FEW ? (int)blockIdx.x - desc_blocks : ((int)blockIdx.x - desc_blocks) * RMS_ROWS + (int)threadIdx.x / LANES;
+    if (m >= rows) return;   // (whole rows: nobody waits for them)
+    constexpr int HELD = 256 / LANES;                        // places per lane: c + LANES h
+    constexpr int U = FEW ? 2 : REDUCE ? 4 : 8;              // chunks in flight per lane
+    constexpr int PASS = FEW ? 2 * 256 : 256;                // chunks per turn of the loop: U at a time
     const size_t frag_row = (size_t)(m >> 5) * (H >> 4) * 1024 + (size_t)(m & 31) * 16;   // row m in a fragment-major matrix; chunks are 512 bytes apart
     const char* src = REDUCE ? reinterpret_cast<const char*>(red.resid) + frag_row : reinterpret_cast<const char*>(x + (size_t)m * H);
     constexpr size_t SRC_STEP = REDUCE ? 512 : 16;   // bytes from one 16-byte chunk of the row to the next in the source
     char* out = reinterpret_cast<char*>(dst) + frag_row;
-    float ss[WPR == 4 ? 1 : 4] = {};
+    float ss[HELD] = {};
     const int chunks = H >> 3;  // 16-byte chunks per row
-    for (int c0 = c; c0 < chunks; c0 += SPAN) {
-        uint4 v[U];
-        f32x4 part[REDUCE ? U : 1][REDUCE ? PLANES : 1][2];   // [chunk in flight][plane][half of the 8 features]
+    for (int c0 = c; c0 < chunks; c0 += PASS)
+        static_for<0, PASS / LANES / U>([&](auto gc) RS_INLINE {
+            constexpr int g = decltype(gc)::value;
+            uint4 v[U];
+            f32x4 part[REDUCE ? U : 1][REDUCE ? PLANES : 1][2];   // [chunk in flight][plane][half of the 8 features]
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (c0 + u * STRIDE < chunks) {
-                v[u] = ld_global_16(src + (size_t)(c0 + u * STRIDE) * SRC_STEP);
-                if constexpr (REDUCE) {
-#pragma unroll
-                    for (int sp = 0; sp < PLANES; ++sp)
-                        if (sp < red.splits) {
-                            const float* pp = red.partial + ((size_t)sp * rows + m) * H + (size_t)(c0 + u * STRIDE) * 8;
-                            part[u][sp][0] = *reinterpret_cast<const f32x4*>(pp);
-                            part[u][sp][1] = *reinterpret_cast<const f32x4*>(pp + 4);
-                        }
-                }
-            }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (c0 + u * STRIDE < chunks) {
-                bf16x8 h = as_bf16x8(v[u]);
-                if constexpr (REDUCE) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        float f = bf16_to_f32(h[e]);
+            for (int u = 0; u < U; ++u) {
+                const int ch = c0 + (g * U + u) * LANES;
+                if (ch < chunks) {
+                    v[u] = ld_global_16(src + (size_t)ch * SRC_STEP);
+                    if constexpr (REDUCE) {
 #pragma unroll
                         for (int sp = 0; sp < PLANES; ++sp)
-                            if (sp < red.splits) f += part[u][sp][e >> 2][e & 3];
-                        h[e] = f32_to_bf16(f);
+                            if (sp < red.splits) {
+                                const float* pp = red.partial + ((size_t)sp * rows + m) * H + (size_t)ch * 8;
+                                part[u][sp][0] = *reinterpret_cast<const f32x4*>(pp);
+                                part[u][sp][1] = *reinterpret_cast<const f32x4*>(pp + 4);
+                            }
                     }
-                    st_global_16(reinterpret_cast<char*>(red.y + (size_t)m * H) + (size_t)(c0 + u * STRIDE) * 16, as_uint4(h));
                 }
-                float& s = ss[WPR == 4 ? 0 : u];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float f = bf16_to_f32(h[e]);
-                    s = __builtin_fmaf(f, f, s);
-                }
-                st_global_16(out + (size_t)(c0 + u * STRIDE) * 512, as_uint4(h));
             }
-    }
-    if constexpr (WPR == 4) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int ch = c0 + (g * U + u) * LANES;
+                if (ch < chunks) {
+                    bf16x8 h = as_bf16x8(v[u]);
+                    if constexpr (REDUCE) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            float f = bf16_to_f32(h[e]);
+#pragma unroll
+                            for (int sp = 0; sp < PLANES; ++sp)
+                                if (sp < red.splits) f += part[u][sp][e >> 2][e & 3];
+                            h[e] = f32_to_bf16(f);
+                        }
+                        st_global_16(reinterpret_cast<char*>(red.y + (size_t)m * H) + (size_t)ch * 16, as_uint4(h));
+                    }
+                    float& s = ss[(g * U + u) % HELD];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float f = bf16_to_f32(h[e]);
+                        s = __builtin_fmaf(f, f, s);
+                    }
+                    st_global_16(out + (size_t)ch * 512, as_uint4(h));
+                }
+            }
+        });
+    if constexpr (FEW) {
         __shared__ float part_sum[4];
         const float t = wave_sum(ss[0]);
-        if (lane == 0) part_sum[wave] = t;
+        if ((threadIdx.x & 63) == 0) part_sum[threadIdx.x >> 6] = t;
         __syncthreads();
         if (threadIdx.x == 0) inv_rms[m] = rsqrtf((((part_sum[0] + part_sum[1]) + part_sum[2]) + part_sum[3]) / (float)H + eps);
     } else {
-        const float t0 = wave_sum(ss[0]), t1 = wave_sum(ss[1]), t2 = wave_sum(ss[2]), t3 = wave_sum(ss[3]);
-        if (lane == 0) inv_rms[m] = rsqrtf((((t0 + t1) + t2) + t3) / (float)H + eps);
+        float total = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {   // places 64 j .. 64 j + 63: the butterfly's first step is between two places of a lane
+            float t = ss[(2 * j) % HELD] + ss[(2 * j + 1) % HELD];
+#pragma unroll
+            for (int off = 16; off > 0; off >>= 1) t += __shfl_xor(t, off, WAVE);
+            total = j == 0 ? t : total + t;
+        }
+        if (c == 0) inv_rms[m] = rsqrtf(total / (float)H + eps);
     }
 }
 

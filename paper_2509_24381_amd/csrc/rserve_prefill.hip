@@ -302,9 +302,9 @@ size_t fp8_expansion_bytes(const rs_ctx* c, long n_tokens) {
 // by it (tiny layer, gate/up of 200 rows, 1 MB: 9.3 -> 10.1).
 constexpr size_t STREAM_BYTES = (size_t)32 << 20;
 
-// Rows up to which the first kernel gives a row a workgroup instead of a wavefront.
-// us per step, 7B shape in a stack: 250 rows 16.6 (a wavefront) -> 10.6, 512: 18.2 -> 15.2, 640: 17.5 -> 16.6, 800: 19.1 -> 21.1.
-constexpr int RMS_FEW_ROWS = 704;
+// Rows up to which the first kernel gives a row a workgroup instead of half a wavefront.
+// us per step, 7B shape in a stack: a workgroup / half a wavefront: 520 rows 15.7 / 16.9, 600 17.5 / 17.8, 700 18.8 / 17.5.
+constexpr int RMS_FEW_ROWS = 608;
 
 // ---- calls of up to TILE_ROWS rows: strips or tiles (gemm_tile.h), and into how many K ranges.
 // Estimated ns of a projection: 4.5 us of launch, first loads and epilogue; per step of 64 k the bytes that a workgroup fetches, at the
@@ -948,21 +948,21 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
     // (the pending sum reads the previous layer's r and partial planes, which this layer overwrites only later)
     const bool pending = pending_in && pending_in->splits > 0;
     const ReduceSource red = pending ? ReduceSource{pending_in->partial, pending_in->splits, pending_in->resid, pending_in->out} : ReduceSource{};
-    const AppendPrep app{reinterpret_cast<uint4*>(wsb + L.act), (int)(append_bytes / 16), (int)tails.size(), f.n_kv_heads, f.head_dim};
-    const auto first_kernel = [&](auto planes, auto wpr) {
-        constexpr int WPR = decltype(wpr)::value, THREADS = WPR == 4 ? 256 : 64 * RMS_ROWS;
-        hipLaunchKernelGGL((rms_and_fragment_major_kernel<decltype(planes)::value, WPR>),
-                           dim3((WPR == 4 ? T : (T + RMS_ROWS - 1) / RMS_ROWS) + (desc_chunks + app.chunks + THREADS - 1) / THREADS + app.tails * app.hkv), dim3(THREADS), 0, st, xb, xf,
-                           inv_rms1, T, H, f.rms_eps, reinterpret_cast<const uint4*>(ctx->pinned_dev[slot]),
+    const AppendPrep app{reinterpret_cast<uint4*>(wsb + L.act), (int)(append_bytes / 16), (int)tails.size(), f.n_kv_heads, f.head_dim, tails.empty() ? KVTail{} : tails[0]};
+    const auto first_kernel = [&](auto planes, auto lanes) {
+        constexpr int LANES = decltype(lanes)::value;
+        hipLaunchKernelGGL((rms_and_fragment_major_kernel<decltype(planes)::value, LANES>),
+                           dim3((LANES == 256 ? T : (T + RMS_ROWS - 1) / RMS_ROWS) + (desc_chunks + app.chunks + 255) / 256 + app.tails * app.hkv), dim3(256),
+                           0, st, xb, xf, inv_rms1, T, H, f.rms_eps, reinterpret_cast<const uint4*>(ctx->pinned_dev[slot]),
                            reinterpret_cast<uint4*>(wsb + L.desc), desc_chunks, red, app);
     };
-    const auto first_kernel_planes = [&](auto wpr) {
-        if (!pending) first_kernel(std::integral_constant<int, 0>{}, wpr);
-        else if (red.splits > MAX_PLANES) first_kernel(std::integral_constant<int, MAX_PLANES_FEW>{}, wpr);
-        else first_kernel(std::integral_constant<int, MAX_PLANES>{}, wpr);
+    const auto first_kernel_planes = [&](auto lanes) {
+        if (!pending) first_kernel(std::integral_constant<int, 0>{}, lanes);
+        else if (red.splits > MAX_PLANES) first_kernel(std::integral_constant<int, MAX_PLANES_FEW>{}, lanes);
+        else first_kernel(std::integral_constant<int, MAX_PLANES>{}, lanes);
     };
-    if (T <= RMS_FEW_ROWS) first_kernel_planes(std::integral_constant<int, 4>{});
-    else first_kernel_planes(std::integral_constant<int, 1>{});
+    if (T <= RMS_FEW_ROWS) first_kernel_planes(std::integral_constant<int, 256>{});
+    else first_kernel_planes(std::integral_constant<int, 32>{});
     RS_HIP(hipGetLastError());
     if (use % RING_CHECKPOINT == RING_CHECKPOINT - 1) {
         RS_HIP(hipEventRecord(ctx->slot_done[slot], st));

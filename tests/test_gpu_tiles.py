@@ -9,7 +9,7 @@ from test_gpu_parity import check
 
 pytestmark = pytest.mark.gpu
 
-ROWS = (33, 64, 65, 129, 200, 256, 257, 300, 511, 704, 705, 1024)
+ROWS = (33, 64, 65, 129, 200, 256, 257, 300, 511, 608, 609, 1024)
 
 
 @pytest.mark.parametrize("n_cu", [None, "24", "80"])
