@@ -472,8 +472,14 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_prefill_pipelined_kernel(c
 // workgroup y handle the block's rows and the chunks y, y + ATT_MERGE_Y, ... of their D/4 chunks of 4 features - one or two
 // chunks, so all of a thread's loads are in flight together (one workgroup per block walking all its chunks one after the
 // other took 13 us, more than a short key range saves).  Every workgroup computes the rows' weights.
+// MAXP: no block has more parts.  EARLY: the outputs are loaded with the references and row sums, ahead of the weights; it takes 10
+// registers per part, so with many parts only launches that are resident at once anyway gain by it.  us, late with room for 16 -> now:
+// 64 rows on 2048 (256 workgroups) 6.1 -> 3.9, 250 on 8192 (448) 10.4 -> 8.4; up to 4 parts, 512 on 1536 (1792) 7.1 -> 6.0, 1000 on 12000
+// 10.3 -> 10.4 (early with room for 16: 8.7 and 13.0).
 constexpr int ATT_MERGE_Y = 16;
-template <int D, int WAVES>
+constexpr int ATT_FEW_PARTS = 4;
+constexpr int ATT_MERGE_EARLY_WAVES = 12;   // wavefronts per compute unit that the early form's registers leave room for
+template <int D, int WAVES, int MAXP, bool EARLY>
 __global__ __launch_bounds__(32 * WAVES) void attn_merge_kernel(const ReqDesc* __restrict__ reqs, const AttnMergeItem* __restrict__ items,
                                                          const float* __restrict__ split_buf, bf16* __restrict__ out, int ld_out,
                                                          int g, float scale_log2e) {
@@ -487,24 +493,30 @@ __global__ __launch_bounds__(32 * WAVES) void attn_merge_kernel(const ReqDesc* _
     const int head = item.kvh * g + (row - tok * g);
     const float* const base = split_buf + (size_t)item.slot0 * AttnPartial<D>::SLOT_FLOATS;
     // (all loads of a round are issued together: absent parts read as m = -inf, l = 0 and get weight 0)
-    float mp[ATT_MAX_PARTS], lp[ATT_MAX_PARTS];
+    static_assert(AttnPartial<D>::CHUNKS % ATT_MERGE_Y == 0, "chunks divide among the merge workgroups");
+    constexpr int MY = AttnPartial<D>::CHUNKS / ATT_MERGE_Y;   // chunks of a thread
+    float mp[MAXP], lp[MAXP];
+    f32x4 o[EARLY ? MY : 1][EARLY ? MAXP : 1];
 #pragma unroll
-    for (int p = 0; p < ATT_MAX_PARTS; ++p) {
+    for (int p = 0; p < MAXP; ++p) {
         mp[p] = -INFINITY;
         lp[p] = 0.0f;
         if (p < item.n_parts) {
             const float* sp = base + p * AttnPartial<D>::SLOT_FLOATS;
             mp[p] = sp[(size_t)D * ROWS + rs];
             lp[p] = sp[(size_t)(D + 1) * ROWS + rs];
+            if constexpr (EARLY)
+#pragma unroll
+                for (int k = 0; k < MY; ++k) o[k][p] = *reinterpret_cast<const f32x4*>(sp + ((size_t)(blockIdx.y + k * ATT_MERGE_Y) * ROWS + rs) * 4);
         }
     }
     float m_all = -INFINITY;
 #pragma unroll
-    for (int p = 0; p < ATT_MAX_PARTS; ++p) m_all = fmaxf(m_all, mp[p]);
+    for (int p = 0; p < MAXP; ++p) m_all = fmaxf(m_all, mp[p]);
     float l_all = 0.0f;
-    float w[ATT_MAX_PARTS];
+    float w[MAXP];
 #pragma unroll
-    for (int p = 0; p < ATT_MAX_PARTS; ++p) {
+    for (int p = 0; p < MAXP; ++p) {
         w[p] = 0.0f;
         if (p < item.n_parts) {
             w[p] = __builtin_amdgcn_exp2f((mp[p] - m_all) * scale_log2e);
@@ -515,17 +527,17 @@ __global__ __launch_bounds__(32 * WAVES) void attn_merge_kernel(const ReqDesc* _
     const uint32_t m = (uint32_t)(rq.row0 + tok);
     char* const op = reinterpret_cast<char*>(out) + (size_t)(m >> 5) * (size_t)(ld_out >> 4) * 1024 + (m & 31u) * 16u;
     const int ks0 = (head * D) >> 4;
-    static_assert(AttnPartial<D>::CHUNKS % ATT_MERGE_Y == 0, "chunks divide among the merge workgroups");
 #pragma unroll
-    for (int k = 0; k < AttnPartial<D>::CHUNKS / ATT_MERGE_Y; ++k) {
+    for (int k = 0; k < MY; ++k) {
         const int c = blockIdx.y + k * ATT_MERGE_Y;
         f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int p = 0; p < ATT_MAX_PARTS; ++p)
+        for (int p = 0; p < MAXP; ++p)
             if (p < item.n_parts) {
-                const f32x4 o = *reinterpret_cast<const f32x4*>(base + p * AttnPartial<D>::SLOT_FLOATS + ((size_t)c * ROWS + rs) * 4);
+                const f32x4 part = EARLY ? o[EARLY ? k : 0][EARLY ? p : 0]
+                                        : *reinterpret_cast<const f32x4*>(base + p * AttnPartial<D>::SLOT_FLOATS + ((size_t)c * ROWS + rs) * 4);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] += w[p] * o[e];
+                for (int e = 0; e < 4; ++e) acc[e] += w[p] * part[e];
             }
         bf16x4 o4;
 #pragma unroll

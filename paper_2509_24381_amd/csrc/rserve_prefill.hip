@@ -537,7 +537,7 @@ struct StepTimer {
 template <int D>
 rs_status launch_attention_path(const rs_ctx* c, bf16* qkv, bf16* attn, const ReqDesc* d_reqs,
                                 const AttnItem* d_items, int n_items, int att_waves, const KVBlockItem* d_vb, int n_vb, bool any_paged,
-                                float* split_buf, const AttnMergeItem* d_mitems, int n_mitems, const Fp8CacheDesc* d_fp8, int n_reqs,
+                                float* split_buf, const AttnMergeItem* d_mitems, int n_mitems, int most_parts, const Fp8CacheDesc* d_fp8, int n_reqs,
                                 int n_xblocks, bool append, hipStream_t st, const StepTimer& tm) {
     const rs_layer_cfg& f = c->cfg;
     tm.begin(RS_STEP_APPEND_KV);
@@ -558,9 +558,14 @@ rs_status launch_attention_path(const rs_ctx* c, bf16* qkv, bf16* attn, const Re
         constexpr int W = decltype(waves)::value;
         hipLaunchKernelGGL((attn_prefill_pipelined_kernel<D, decltype(paged)::value, W>), dim3(n_items), dim3(64 * W), 0, st, d_reqs, d_items,
                            (const bf16*)qkv, c->qkv_dim, attn, c->q_dim, c->group, scale_log2e, split_buf);
-        if (n_mitems > 0)
-            hipLaunchKernelGGL((attn_merge_kernel<D, W>), dim3(n_mitems, ATT_MERGE_Y), dim3(32 * W), 0, st, d_reqs, d_mitems,
-                               (const float*)split_buf, attn, c->q_dim, c->group, scale_log2e);
+        const auto merge = [&](auto max_parts, auto early) {
+            hipLaunchKernelGGL((attn_merge_kernel<D, W, decltype(max_parts)::value, decltype(early)::value>), dim3(n_mitems, ATT_MERGE_Y), dim3(32 * W), 0, st, d_reqs,
+                               d_mitems, (const float*)split_buf, attn, c->q_dim, c->group, scale_log2e);
+        };
+        if (n_mitems == 0) return;
+        if (most_parts <= ATT_FEW_PARTS) merge(std::integral_constant<int, ATT_FEW_PARTS>{}, std::true_type{});
+        else if (n_mitems * ATT_MERGE_Y * (W / 2) <= ATT_MERGE_EARLY_WAVES * c->n_cu) merge(std::integral_constant<int, ATT_MAX_PARTS>{}, std::true_type{});
+        else merge(std::integral_constant<int, ATT_MAX_PARTS>{}, std::false_type{});
     };
     const auto attend_waves = [&](auto paged) {
         if (att_waves == ATT_WAVES) attend(paged, std::integral_constant<int, ATT_WAVES>{});
@@ -990,13 +995,15 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
         if (s != RS_OK) return s;
     }
     tm.end(RS_STEP_QKV_GEMM);
+    int most_parts = 0;
+    for (const AttnMergeItem& item : mitems) most_parts = std::max(most_parts, item.n_parts);
     // cache append, attention
     if (f.head_dim == 128)
         s = launch_attention_path<128>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), plan.waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
-                                       attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, kv_rows == nullptr, st, tm);
+                                       attn_split, d_mitems, (int)mitems.size(), most_parts, d_fp8, (int)reqs.size(), n_xblocks, kv_rows == nullptr, st, tm);
     else
         s = launch_attention_path<64>(ctx, qkv, attn, d_reqs, d_items, (int)items.size(), plan.waves, d_vb, (int)vbs.size(), !pagetab.empty() && fp8s.empty(),
-                                      attn_split, d_mitems, (int)mitems.size(), d_fp8, (int)reqs.size(), n_xblocks, kv_rows == nullptr, st, tm);
+                                      attn_split, d_mitems, (int)mitems.size(), most_parts, d_fp8, (int)reqs.size(), n_xblocks, kv_rows == nullptr, st, tm);
     if (s != RS_OK) return s;
     // r = x + attn Wo^T, and 1/rms of every row of r (the second RMSNorm; its gain lives in the packed W_gate_up)
     tm.begin(RS_STEP_O_GEMM);
