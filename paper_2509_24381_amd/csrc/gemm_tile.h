@@ -10,8 +10,9 @@
 // units, chosen per call from that sum (tile_ns in rserve_prefill.hip).  Both operands go global -> LDS by DMA, each byte once per
 // workgroup, through a ring of SLOTS steps of 64 k; a wavefront reads the fragments of a whole step into registers while it multiplies
 // those of the step before, so that neither the LDS latency nor the one barrier of a step shows.
-// Measured beside the strips they replace, us per step between events (7B shape, weights from HBM): QKV 250 rows 33.7 -> 30.4, 512
-// rows 45.5 -> 35, 1000 rows 51.0 -> 46.8; O 250 rows 27.6 -> 19.5, 512 rows 34.2 -> 26, 1000 rows 43.2 -> 39.6.
+// Measured beside the strips they replace, us per step between events (7B shape in a stack, weights from HBM): QKV 250 rows 33.9 -> 31.0,
+// 512 rows 45.1 -> 34.9, 1000 rows 51.4 -> 47.4; O 64 rows 20.3 -> 15.7, 250 rows 27.8 -> 21.7, 512 rows 34.5 -> 29.6; down 64 rows 37.4 ->
+// 32.5, 250 rows 62.5 -> 56.7.
 #pragma once
 #include "common.h"
 #include "gemm_strip.h"

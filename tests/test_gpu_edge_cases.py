@@ -391,10 +391,9 @@ def test_alternative_kernel_paths_meet_the_same_bar(env):
     """Other split-K factors of the residual GEMMs, and other numbers of strips (RS_NCU stands in for the device's
     compute-unit count: small values give wide strips, i.e. every tile width from 2 to 8 units on these small shapes,
     where the default gives one unit per strip), and a fixed number of parts per attention block (RS_ATTN_SPLIT: 1 never splits a key
-    range, 3 cuts every block with at least 18 key tiles in three and those with at least 12 in two), and the GEMM geometry
-    for launches whose strips hold at most two units (RS_NARROW 0: never the narrow one; RS_NARROW_TM 8: also for calls of
-    up to 8 token blocks, which with RS_NCU 40 makes strips of one and two units on these shapes; RS_PAIRS 0: never two
-    wavefronts per pair of units), and the plain order of the attention work items (RS_ATTN_ORDER; the default order, which
+    range, 3 cuts every block with at least 18 key tiles in three and those with at least 12 in two), the projections
+    on strips alone (RS_NARROW 0; with RS_NCU 40 they choose other tiles; RS_NARROW_TM and RS_PAIRS steered a geometry that is gone and
+    change nothing), and the plain order of the attention work items (RS_ATTN_ORDER; the default order, which
     depends on the compute-unit count, also runs under every RS_NCU value above) are selectable by
     environment variable; each must pass the
     workload-1 parity test on its own (run in a child process because the choice is read once per process)."""
