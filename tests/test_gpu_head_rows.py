@@ -48,6 +48,30 @@ def test_a_row_has_the_same_logits_in_every_call_of_three_rows_and_more():
         assert torch.equal(ctx.lm_head(gd, wd, xd[first: first + n].contiguous()), all_rows[first: first + n])
 
 
+@pytest.mark.parametrize("n_rows", [1, 2, 3, 10, 11, 21])
+def test_a_vocabulary_that_is_streamed(n_rows):
+    """Vocabularies of 256 MiB and more are loaded with the streaming hint: every logit has the bits that a call on a part of the
+    vocabulary below that size gives, in either kernel, and sampled words (first, last, and across the parts' border) meet the oracle."""
+    from paper_2509_24381_amd import runner
+    hidden, vocab, part = 1024, 131201, 70001
+    shape = synth.LayerShape("lm", hidden, 2, 1, 64, 64)
+    ctx = runner.Context(runner.config_for(shape, max_tokens=32, max_requests=1, max_pos=64))
+    assert part * hidden * 2 < 1 << 28 <= vocab * hidden * 2
+    rng = np.random.default_rng(73)
+    g = synth.bf16_round(rng.uniform(0.5, 1.5, hidden).astype(np.float32))
+    x = synth.bf16_round(rng.standard_normal((n_rows, hidden)).astype(np.float32))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(74)
+    wd = (torch.randn(vocab, hidden, device="cuda", generator=gen) * 0.02).to(torch.bfloat16)
+    gd, xd = runner.to_device_bf16(g), runner.to_device_bf16(x)
+    got = ctx.lm_head(gd, wd, xd)
+    for first, end in ((0, part), (part, vocab)):
+        assert torch.equal(got[:, first:end], ctx.lm_head(gd, wd[first:end].contiguous(), xd))
+    words = np.unique(np.concatenate([[0, 1, part - 1, part, vocab - 2, vocab - 1], rng.integers(0, vocab, 500)]))
+    want = first_token_logits(x, g, runner.to_numpy_f32(wd[torch.from_numpy(words).cuda()]), shape.rms_eps)
+    assert rel_fro(got[:, torch.from_numpy(words).cuda()].cpu().numpy(), want) <= 1e-6
+
+
 def test_a_workspace_of_four_bytes_per_value_is_still_enough():
     """4 H bytes per row (rounded up to 256) is all the fp32 kernel needs; the same call with the full size takes the matrix
     path.  Both meet the bar; a smaller workspace is refused."""
