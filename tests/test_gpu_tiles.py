@@ -15,8 +15,8 @@ ROWS = (33, 64, 65, 129, 200, 256, 257, 300, 511, 608, 609, 1024)
 @pytest.mark.parametrize("n_cu", [None, "24", "80"])
 @pytest.mark.parametrize("hidden, hq, hkv, d, inter", [(64, 2, 1, 64, 64), (320, 6, 2, 64, 2112), (192, 4, 2, 128, 8256), (1344, 10, 2, 128, 448)])
 def test_tiles_against_the_oracle_and_the_strips(hidden, hq, hkv, d, inter, n_cu, monkeypatch):
-    """Each row count against the oracle (bar of the layer, 1e-2), and K and V bit-identical to those that the strip kernel leaves (RS_NARROW=0):
-    both accumulate along K in one order.  The compute-unit count steers which shape and how many K ranges are chosen."""
+    """Each row count against the oracle (bar of the layer, 1e-2), and K and V bit-identical to those that the strip kernel leaves (RS_NARROW=0)
+    and to the same rows' of the longest call: all accumulate along K in one order.  The compute-unit count steers which shape and how many K ranges are chosen."""
     from paper_2509_24381_amd import runner as r
     shape = synth.LayerShape("tiles", hidden, hq, hkv, d, inter)
     w = synth.layer_weights(shape, 91, qkv_bias=True, gains="uniform")
@@ -42,7 +42,11 @@ def test_tiles_against_the_oracle_and_the_strips(hidden, hq, hkv, d, inter, n_cu
             out.append((y, *(r.to_numpy_f32(c) for c in kv.export(0))))
         return out
     env = {} if n_cu is None else {"RS_NCU": n_cu}
-    for t, tiles, strips in zip(ROWS, calls(**env), calls(RS_NARROW="0", **env)):
+    of_tiles = calls(**env)
+    longest_call = of_tiles[-1]
+    for t, tiles, strips in zip(ROWS, of_tiles, calls(RS_NARROW="0", **env)):
         check(f"{t} rows of H={hidden} I={inter}", tiles[0], want[:t])
         np.testing.assert_array_equal(tiles[1], strips[1])
         np.testing.assert_array_equal(tiles[2], strips[2])
+        np.testing.assert_array_equal(tiles[1], longest_call[1][:prior + t])
+        np.testing.assert_array_equal(tiles[2], longest_call[2][:prior + t])
