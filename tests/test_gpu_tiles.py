@@ -50,3 +50,40 @@ def test_tiles_against_the_oracle_and_the_strips(hidden, hq, hkv, d, inter, n_cu
         np.testing.assert_array_equal(tiles[2], strips[2])
         np.testing.assert_array_equal(tiles[1], longest_call[1][:prior + t])
         np.testing.assert_array_equal(tiles[2], longest_call[2][:prior + t])
+
+
+@pytest.mark.parametrize("lens", [(1, 2, 27), (63, 65, 130, 1), (200, 7, 500, 317)])
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_caches_that_the_projection_fills(d, paged, lens, monkeypatch):
+    """Several requests at once: the projection's epilogue and the first kernel's zeros leave every byte of the caches' slabs as the append
+    kernel (RS_NARROW=0) does, from slabs that start as NaN patterns, at first rows inside, at the start and at the end of a block of
+    64 tokens."""
+    import torch
+    from paper_2509_24381_amd import runner as r
+    priors = (0, 61, 64, 130)[:len(lens)]
+    shape = synth.LayerShape("append", 192, 4, 2, d, 448)
+    w = synth.layer_weights(shape, 105, qkv_bias=True, gains="uniform")
+    x = r.to_device_bf16(synth.prompt_rows([("image", sum(lens))], shape.hidden, 106))
+
+    def run():
+        stack = r.LayerStack(shape, [w], max_tokens=1024, max_requests=4, max_pos=2048, qkv_bias=True)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(107)
+        pool = stack.new_pool(40) if paged else None
+        kvs = [pool.new_cache(1) if paged else stack.new_cache(p + n) for p, n in zip(priors, lens)]
+        slabs = [pool.slab] if paged else [kv.slab for kv in kvs]
+        for s in slabs:
+            s.view(torch.int16).fill_(0x7FC1)
+        for kv, p in zip(kvs, priors):
+            if p:
+                k, v = (torch.randn(p, 2, d, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+                kv.import_(0, k, v)
+        y = stack.prefill_batch(0, kvs, list(lens), x)
+        return y, slabs
+    y, slabs = run()
+    monkeypatch.setenv("RS_NARROW", "0")
+    want_y, want = run()
+    check("rows", r.to_numpy_f32(y), r.to_numpy_f32(want_y))
+    for a, b in zip(slabs, want):
+        assert torch.equal(a, b)
