@@ -321,13 +321,13 @@ double step_ns(double blocks, double units, int steps) {
 }
 double reduce_ns(int M, int units, int splits) { return splits > 1 ? 5500.0 + (double)M * units * 32.0 * (4.0 * splits + 4.0) / 6000.0 : 0.0; }
 bool streams_once(int tiles_m, int units, int steps) { return tiles_m == 1 && (size_t)units * steps * 4096 >= STREAM_BYTES; }
-double stream_ns(int tiles_m, int units, int steps) { return 4500.0 + (double)units * steps * 4096.0 / (streams_once(tiles_m, units, steps) ? 6200.0 : 5300.0); }
+double stream_ns(int units, int steps, bool hint) { return 4500.0 + (double)units * steps * 4096.0 / (hint ? 6200.0 : 5300.0); }
 // (the row blocks of a ragged call count by their live rows: what some workgroups do not fetch the others get sooner)
 double tile_ns(const rs_ctx* c, int shape, int M, int units, int steps, int splits) {
     const int b = TILE_BLOCKS[shape], u = TILE_UNITS[shape];
     const int tiles_m = (M + 32 * b - 1) / (32 * b), wgs = tiles_m * ((units + u - 1) / u) * splits, rounds = (wgs + c->n_cu - 1) / c->n_cu;
     const double fetch = rounds * (4500.0 + (steps + splits - 1) / splits * step_ns((double)((M + 31) / 32) / tiles_m, u, steps));
-    return std::max(fetch, stream_ns(tiles_m, units, steps)) + reduce_ns(M, units, splits);
+    return std::max(fetch, stream_ns(units, steps, streams_once(tiles_m, units, steps))) + reduce_ns(M, units, splits);
 }
 double strip_ns(const rs_ctx* c, int M, int units, int steps, int splits) {
     const int tiles_m = (M + GS_BM - 1) / GS_BM, strips = strips_for(c, tiles_m, splits, units);
@@ -335,7 +335,8 @@ double strip_ns(const rs_ctx* c, int M, int units, int steps, int splits) {
     const int ups = (units + strips - 1) / strips, ntiles = (ups + GS_MAX_NT - 1) / GS_MAX_NT;
     const double b = 2.0 * ((M + 63) / 64) / tiles_m;   // (a wavefront without rows loads none)
     const double step = std::max(570.0, step_ns(b, (double)ups / ntiles, steps));   // (its loop takes 1200 clocks with few units)
-    return std::max(rounds * (4500.0 + ntiles * ((steps + splits - 1) / splits * step)), stream_ns(tiles_m, units, steps)) + reduce_ns(M, units, splits);
+    const bool hint = splits > 1 && streams_once(tiles_m, units, steps);   // (of the strips compared here launch_gemm gives it to partial sums only)
+    return std::max(rounds * (4500.0 + ntiles * ((steps + splits - 1) / splits * step)), stream_ns(units, steps, hint)) + reduce_ns(M, units, splits);
 }
 struct GemmRoute { int shape, splits; };   // shape -1: strips
 // `splits_fixed` > 0: that many K ranges.  `strip_splits`: the K ranges the strips would take.  most: the K ranges there are planes for.  shapes: the ones that exist for the epilogue
