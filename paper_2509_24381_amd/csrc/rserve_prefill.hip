@@ -962,13 +962,14 @@ rs_status prefill_enqueue(rs_ctx* ctx, const rs_layer_weights* w, int layer, rs_
                            0, st, xb, xf, inv_rms1, T, H, f.rms_eps, reinterpret_cast<const uint4*>(ctx->pinned_dev[slot]),
                            reinterpret_cast<uint4*>(wsb + L.desc), desc_chunks, red, app);
     };
-    const auto first_kernel_planes = [&](auto lanes) {
-        if (!pending) first_kernel(std::integral_constant<int, 0>{}, lanes);
-        else if (red.splits > MAX_PLANES) first_kernel(std::integral_constant<int, MAX_PLANES_FEW>{}, lanes);
-        else first_kernel(std::integral_constant<int, MAX_PLANES>{}, lanes);
+    static_assert(FEW_PLANES_ROWS <= RMS_FEW_ROWS, "more than MAX_PLANES planes: a workgroup per row");
+    const auto first_kernel_lanes = [&](auto planes) {
+        if (T <= RMS_FEW_ROWS) first_kernel(planes, std::integral_constant<int, 256>{});
+        else first_kernel(planes, std::integral_constant<int, 32>{});
     };
-    if (T <= RMS_FEW_ROWS) first_kernel_planes(std::integral_constant<int, 256>{});
-    else first_kernel_planes(std::integral_constant<int, 32>{});
+    if (!pending) first_kernel_lanes(std::integral_constant<int, 0>{});
+    else if (red.splits > MAX_PLANES) first_kernel(std::integral_constant<int, MAX_PLANES_FEW>{}, std::integral_constant<int, 256>{});
+    else first_kernel_lanes(std::integral_constant<int, MAX_PLANES>{});
     RS_HIP(hipGetLastError());
     if (use % RING_CHECKPOINT == RING_CHECKPOINT - 1) {
         RS_HIP(hipEventRecord(ctx->slot_done[slot], st));
