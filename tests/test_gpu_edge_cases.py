@@ -386,14 +386,14 @@ def test_attention_item_order_does_not_change_a_bit(monkeypatch):
 @pytest.mark.parametrize("env", [{"RS_SPLITK": "1"}, {"RS_SPLITK": "2"}, {"RS_SPLITK": "3"},
                                  {"RS_NCU": "1"}, {"RS_NCU": "3"}, {"RS_NCU": "7", "RS_SPLITK": "2"},
                                  {"RS_ATTN_SPLIT": "1"}, {"RS_ATTN_SPLIT": "3"}, {"RS_ATTN_ORDER": "plain", "RS_NCU": "7"},
-                                 {"RS_NARROW": "0"}, {"RS_NARROW": "1", "RS_NARROW_TM": "8", "RS_NCU": "40"}, {"RS_PAIRS": "0"}])
+                                 {"RS_NARROW": "0"}, {"RS_NCU": "40"}, {"RS_NCU": "8"}])
 def test_alternative_kernel_paths_meet_the_same_bar(env):
     """Other split-K factors of the residual GEMMs, and other numbers of strips (RS_NCU stands in for the device's
     compute-unit count: small values give wide strips, i.e. every tile width from 2 to 8 units on these small shapes,
     where the default gives one unit per strip), and a fixed number of parts per attention block (RS_ATTN_SPLIT: 1 never splits a key
     range, 3 cuts every block with at least 18 key tiles in three and those with at least 12 in two), the projections
-    on strips alone (RS_NARROW 0; with RS_NCU 40 they choose other tiles; RS_NARROW_TM and RS_PAIRS steered a geometry that is gone and
-    change nothing), and the plain order of the attention work items (RS_ATTN_ORDER; the default order, which
+    on strips alone (RS_NARROW 0) or on other tiles than the device's size asks for (RS_NCU 40: QKV 64 x 128 and 128 x 96; 8: O and
+    down 128 x 128), and the plain order of the attention work items (RS_ATTN_ORDER; the default order, which
     depends on the compute-unit count, also runs under every RS_NCU value above) are selectable by
     environment variable; each must pass the
     workload-1 parity test on its own (run in a child process because the choice is read once per process)."""
