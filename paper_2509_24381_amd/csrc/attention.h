@@ -18,8 +18,8 @@
 // Cache layout (private to the library): K is [Hkv][capacity][d]; V is stored transposed in blocks of 64 tokens,
 // [Hkv][capacity/64][d][64], so that a V^T tile is one contiguous 64*d*2-byte run with the key index innermost,
 // which is what the MFMA A operand needs.  A paged cache keeps the same 64-token tiles, gathered per page instead of per
-// plane (see KVHeadTiles).  Positions >= len inside the last V block hold zeros (the append and import kernels
-// maintain this), so masked probabilities (exact zeros) never meet NaN bit patterns.
+// plane (see KVHeadTiles).  Positions >= len inside the last V block hold zeros (the append and import kernels, and
+// the first kernel of calls whose QKV projection fills the caches, maintain this), so masked probabilities (exact zeros) never meet NaN bit patterns.
 #pragma once
 #include <type_traits>
 

@@ -190,7 +190,9 @@ constexpr int LM_ROWS = 4;
 constexpr int LM_VGROUP = 4;
 // ONCE: the vocabulary is beyond the 256 MB Infinity Cache (LM_STREAM_BYTES) and loaded with the streaming hint, with which HBM streams
 // faster: 152064 x 3584, 1 row 189 -> 171 us, 8 rows (the kernel below) 210 -> 186; 152064 x 8192, 1 row 450 -> 418.  A smaller one can
-// still be there from the head before, and the hint then loses: 32000 x 3584, 3 rows 42.0 -> 43.9.
+// still be there from the head before, and the hint then loses: 32000 x 3584, 3 rows 42.0 -> 43.9.  Head after head, the line lies at 270
+// to 290 MB (152064 x 896, 272 MB, 8 rows 52 -> 54; 100000 x 1536, 307 MB, 1.05x to 1.13x faster); behind a
+// fill of 1 GB every size from 57 MB on gains, 1.1x to 2x.
 constexpr size_t LM_STREAM_BYTES = (size_t)256 << 20;
 constexpr int LM_ONCE = 2;   // cache policy (nt)
 template <bool ONCE>

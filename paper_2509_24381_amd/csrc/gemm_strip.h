@@ -51,15 +51,16 @@ struct GemmArgs {
     bf16* out;          // [M, ldo], row-major or (out_frag) fragment-major of width ldo
     const bf16* bias;   // [N] in the original feature order, or null
     const bf16* resid;  // [M, ldr], row-major or (resid_frag) fragment-major of width ldr
-    float* rowss;       // EPI_RESIDUAL (output, or null): [parts][M], one sum of squares per row and column of work - a strip, or
-                        // the units of a wavefront - over the features of the stored row that the column owns; parts = rowss_parts(...) of this launch.  EPI_SWIGLU (input, or null): the same array as the
-                        // residual GEMM in front left it; the row factor is then rsqrt(sum of the parts / K + rms_eps)
-                        // instead of row_scale[m]
+    float* rowss;       // EPI_RESIDUAL (output, or null): [parts][M], one sum of squares per row and column of work (a strip, the
+                        // units of a tile's wavefront, or a unit of the few-rows kernel) over the features of the stored row that
+                        // the column owns; the launcher says how many parts there are.  EPI_SWIGLU (input, or null): the same
+                        // array as the residual GEMM in front left it; the row factor is then rsqrt(sum of the parts / K +
+                        // rms_eps) instead of row_scale[m]
     int rowss_parts;    // EPI_SWIGLU: number of parts in rowss
     float rms_eps;      // EPI_SWIGLU with rowss
     float* partial;     // [splits, M, N]
-    const float* row_scale;  // [M] 1/rms of the row (EPI_QKV_ROPE, EPI_SWIGLU)
-    const int* row_pos;      // [M][3] rotary position of the row on the (temporal, height, width) axes (EPI_QKV_ROPE)
+    const float* row_scale;  // [M] 1/rms of the row (EPI_QKV_ROPE, EPI_QKV_APPEND, EPI_SWIGLU)
+    const int* row_pos;      // [M][3] rotary position of the row on the (temporal, height, width) axes (EPI_QKV_ROPE, EPI_QKV_APPEND)
     int mrope_b0, mrope_b1;  // rotary pair j uses axis 0 if j < b0, axis 1 if j < b1, else axis 2 (1-D RoPE: b0 = b1 = d/2)
     const float2* rope_cs;   // [max_pos][head_dim/2] (cos, sin)
     int rope_cols;           // columns [0, rope_cols) are q and k heads (a multiple of head_dim)
@@ -69,9 +70,10 @@ struct GemmArgs {
     int ldo, ldr;
     int out_frag, resid_frag;
     int M, N, K;
-    int tiles_m;             // ceil(M / 256)
-    int strips;              // strips per 256-row block; grid.x = tiles_m * strips
-    int steps_per_split;     // K/64 steps handled by one blockIdx.y
+    int tiles_m;             // row blocks: of 256 rows (strips), of 64 or 128 (tiles); the few-rows kernel has none
+    int strips;              // ranges of units per row block: strips, or a tile's units each.  Strips: grid = (tiles_m * strips,
+                             // K ranges); tiles: all three factors in grid.x; the few-rows kernel: grid = (units, K ranges)
+    int steps_per_split;     // K/64 steps of one K range
 };
 
 constexpr int GS_BM = 256;

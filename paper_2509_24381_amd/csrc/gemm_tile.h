@@ -2,7 +2,7 @@
 // the epilogues and, along K, the order of accumulation of gemm_strip.h (the same bits, whichever runs).
 //
 // What bounds these calls is what a compute unit can fetch.  All workgroups walk K in step, so every line a workgroup asks for is
-// still on its way from memory for all of them, and a compute unit sustains about 51 bytes per ns however many loads it keeps in
+// still on its way from memory for all of them, and a compute unit sustains 50 to 60 bytes per ns however many loads it keeps in
 // flight beyond 32 KB and whichever way they go (LDS or registers, with the MFMAs or without, measured on 36 to 224 compute units;
 // L2-resident lines 126).  A projection's time is then the bytes of ONE workgroup, K (rows + features) 2, over that rate, plus 4 to
 // 5 us, and the shape of the tile is what matters: a block of 256 rows by one or two units of 32 features (what strips of a short

@@ -235,7 +235,7 @@ double gemm_cost_clocks(const rs_ctx* c, int M, int units, int k_steps, int spli
     const int ntiles = (ups + GS_MAX_NT - 1) / GS_MAX_NT;
     const double nt = (double)ups / ntiles;
     const int steps = (k_steps + splits - 1) / splits;
-    // (a step of the wide geometry also moves 32 KB of token fragments per workgroup whatever the tile's width: with three
+    // (a step also moves 32 KB of token fragments per workgroup whatever the tile's width: with three
     // units or fewer that, not the MFMAs, sets its duration - about 1200 clocks measured; without this floor calls of 257
     // to 768 rows kept the O projection unsplit, 3 to 8 us slower than in two or three K ranges)
     const double step = std::max(256.0 * nt + 350.0, 1200.0);
@@ -299,17 +299,24 @@ size_t fp8_expansion_bytes(const rs_ctx* c, long n_tokens) {
 
 // Weights that one workgroup reads once, and that the L2s (32 MB together) could not keep from one call to the next, are loaded with the
 // streaming hint (GS_ONCE): gate/up of 64 rows, 7B (272 MB), 54.2 -> 50.1 us between events, 72B (969 MB) 182 -> 160; smaller ones lose
-// by it (tiny layer, gate/up of 200 rows, 1 MB: 9.3 -> 10.1).
+// by it (tiny layer, gate/up of 200 rows, 1 MB: 9.3 -> 10.1).  In a stack, whose layers together exceed the 256 MB Infinity Cache; one
+// layer of hidden 2048 (135 MB) called again and again is still there and loses 3 us (16 rows on 500, 8-bit cache: 73.4 -> 76.6).
 constexpr size_t STREAM_BYTES = (size_t)32 << 20;
 
 // Rows up to which the first kernel gives a row a workgroup instead of half a wavefront.
-// us per step, 7B shape in a stack: a workgroup / half a wavefront: 520 rows 15.7 / 16.9, 600 17.5 / 17.8, 700 18.8 / 17.5.
+// us per step between events, a workgroup / half a wavefront.  With the sum of planes, hidden 896 at 500 and 600 rows 8.7 / 9.2 and 9.2 /
+// 8.9, 2048: 11.6 / 12.0 and 12.6 / 12.1, 3584: 14.1 / 14.5 and 14.4 / 14.3, 5120 at 600 and 700: 19.2 / 19.6 and 21.0 / 20.5, 8192: 26.5 /
+// 28.3 and 29.7 / 29.6; without, 3584 at 600: 10.0 / 10.0, 8192 at 500 and 600: 16.4 / 18.0 and 18.7 / 18.0.  The crossing moves from about 530
+// rows (narrow layers, or no planes) to 700 (8192 with planes); what one line for all costs is 1.9 us at most (8192, 650 rows).
 constexpr int RMS_FEW_ROWS = 608;
 
 // ---- calls of up to TILE_ROWS rows: strips or tiles (gemm_tile.h), and into how many K ranges.
 // Estimated ns of a projection: 4.5 us of launch, first loads and epilogue; per step of 64 k the bytes that a workgroup fetches, at the
 // rate a compute unit gets them with all of them walking K in step (50 to 60 per ns: the longer K, the less of the token panel an L2
 // keeps), or its MFMAs; at least the weights at what HBM streams (6.2 TB/s with the streaming hint, 5.3 without); and the reduction.
+// Row blocks of a ragged call count by the average of their live rows.  That is a fit, and ragged launches lie on either side of it: five
+// blocks of 64 rows x 128 features, QKV 7B, full (320 rows) 28.8 us, with one row in the last (257) 26.1, which the average puts at 28.0;
+// two blocks of 256 and 77 rows on strips, gate/up 7B, 95 to 99, between the average (89) and the fuller block's bytes (104).
 // Against measurement (us between events, 3 of them the events'; 7B shape): QKV 250 rows on 64 x 128 27.4 (30.8), 512 on 128 x 96 31
 // (35), 1000 on 128 x 160 38.9 (46.8); O 64 rows on 64 x 64 in 4 ranges 14.6 (15.8), 250 on 64 x 64 19.8 (22.0); down 64 rows on
 // 64 x 128 in 8 ranges 33 (29.5, its reduction not in it), 250 on 128 x 128 in 4 64 (56.5, likewise).  The estimates rank; they do not predict.
@@ -322,7 +329,6 @@ double step_ns(double blocks, double units, int steps) {
 double reduce_ns(int M, int units, int splits) { return splits > 1 ? 5500.0 + (double)M * units * 32.0 * (4.0 * splits + 4.0) / 6000.0 : 0.0; }
 bool streams_once(int tiles_m, int units, int steps) { return tiles_m == 1 && (size_t)units * steps * 4096 >= STREAM_BYTES; }
 double stream_ns(int units, int steps, bool hint) { return 4500.0 + (double)units * steps * 4096.0 / (hint ? 6200.0 : 5300.0); }
-// (the row blocks of a ragged call count by their live rows: what some workgroups do not fetch the others get sooner)
 double tile_ns(const rs_ctx* c, int shape, int M, int units, int steps, int splits) {
     const int b = TILE_BLOCKS[shape], u = TILE_UNITS[shape];
     const int tiles_m = (M + 32 * b - 1) / (32 * b), wgs = tiles_m * ((units + u - 1) / u) * splits, rounds = (wgs + c->n_cu - 1) / c->n_cu;
@@ -339,7 +345,8 @@ double strip_ns(const rs_ctx* c, int M, int units, int steps, int splits) {
     return std::max(rounds * (4500.0 + ntiles * ((steps + splits - 1) / splits * step)), stream_ns(units, steps, hint)) + reduce_ns(M, units, splits);
 }
 struct GemmRoute { int shape, splits; };   // shape -1: strips
-// `splits_fixed` > 0: that many K ranges.  `strip_splits`: the K ranges the strips would take.  most: the K ranges there are planes for.  shapes: the ones that exist for the epilogue
+// `splits_fixed` > 0: that many K ranges.  `strip_splits`: the K ranges the strips would take.  `most`: the K ranges there are planes for.
+// `shapes`: the ones that exist for the epilogue.
 GemmRoute choose_route(const rs_ctx* c, int M, int units, int steps, int splits_fixed, int strip_splits, int most, std::initializer_list<int> shapes) {
     GemmRoute best{-1, strip_splits};
     if (!c->gemm_few || M > TILE_ROWS) return best;
@@ -1600,7 +1607,7 @@ static rs_status model_batch(rs_ctx* ctx, const rs_layer_weights* packed_layers,
     if (T == 0) return RS_OK;
     // Layer 0 reads x; later layers work on y in place.  Between two layers the split-K sum of the down projection, the
     // pass that takes the next layer's norm factors and the copy into its GEMMs' operand layout are one kernel (see
-    // rms_and_fragment_major_kernel<true>): the bits are those of the layers called one by one.
+    // rms_and_fragment_major_kernel with planes): the bits are those of the layers called one by one.
     // The attention plan of one layer serves the next while their caches are equally long (planning takes 2 to 15 us of host
     // time, of about 30 per layer).
     PendingReduce pending;

@@ -277,8 +277,8 @@ def test_a_capturing_stream_is_refused_and_nothing_changes():
 @pytest.mark.parametrize("shape_name", ["small128", "wide_mlp"])
 def test_row_counts_around_every_wavefront_and_block_boundary(shape_name):
     """The GEMMs choose their geometry and the work of their wavefronts by the row count of the call: wavefronts whose 64
-    rows lie past the end idle, calls of 129 to 256 rows on narrow strips run in blocks of 128 rows with the units of a
-    pair split between wavefronts, longer calls in blocks of 256.  One call per row count on a prior cache of 100 tokens,
+    rows lie past the end idle, calls of up to 1024 rows run in blocks of 64 or 128 rows, the gate/up projection (beyond 128 rows) in
+    blocks of 256.  One call per row count on a prior cache of 100 tokens,
     each against the oracle, and each bit-identical to the same rows taken from a longer call (a row's result does not
     depend on how many rows the call has)."""
     r = R()

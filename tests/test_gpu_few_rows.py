@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("hidden, inter, d", [(64, 64, 64), (192, 4096, 128), (128, 8256, 64), (1088, 320, 128), (2304, 1024, 64)])
 def test_few_rows_against_the_oracle_and_a_longer_call(hidden, inter, d):
     """Each row count against the oracle (bar of the layer, 1e-2), and K and V bit-identical to the same rows' of a 300-row
-    call, which runs in the strip kernel: the QKV projection accumulates along K in one order whatever the call's size."""
+    call, which runs on tiles: the QKV projection accumulates along K in one order whatever the call's size."""
     from paper_2509_24381_amd import runner as r
     shape = synth.LayerShape("few", hidden, 4, 2, d, inter)
     w = synth.layer_weights(shape, 88, qkv_bias=True, gains="uniform")
